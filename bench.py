@@ -53,8 +53,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "MLUPS + % HBM peak, D3Q27 256^3 FP32 vs FP64; warm-start steps-to-steady"
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, vendor figure
-KERNEL_SOURCES = ["paper_1806_10247_amd/csrc/kernels.hip", "paper_1806_10247_amd/csrc/lattice.hpp",
-                  "paper_1806_10247_amd/csrc/common.hpp"]
+KERNEL_SOURCES = ["paper_1806_10247_amd/csrc/kernels.hip", "paper_1806_10247_amd/csrc/node.hpp",
+                  "paper_1806_10247_amd/csrc/lattice.hpp", "paper_1806_10247_amd/csrc/common.hpp"]
 
 
 def log(*a):

@@ -244,7 +244,9 @@ int lb_set_source_field(lb_ctx* ctx, const void* S, int32_t dtype, int32_t mem);
 int lb_set_source_time(lb_ctx* ctx, int32_t mode, double omega);
 
 /* Enqueues nsteps >= 0 time steps on the context's stream (one fused kernel
- * launch per step, plus a reduction every residual_interval steps).  Returns
+ * launch per step, plus a reduction every residual_interval steps; on a 2D
+ * lattice whose launch shape is left automatic (block_x, rows_per_thread and
+ * x_pairs 0) several steps per launch, with bit-identical results).  Returns
  * LB_ENONFINITE if a residual check that has already completed found a NaN or
  * infinity (the steps are then not enqueued). */
 int lb_step(lb_ctx* ctx, int64_t nsteps);

@@ -60,6 +60,10 @@ struct lb_ctx {
         uint64_t used = 0;
         StepArgs args[2];
     };
+    // several steps per launch (2D lattices): tiling per number of steps, the best number
+    MultiShape multi[kMultiMaxSteps + 1];
+    bool multi_ok[kMultiMaxSteps + 1] = {};
+    int multi_most = 0, multi_fields = -1;   // fields the choice was made for (bit 0 force, bit 1 source)
     static constexpr int kGraphCache = 8;
     StepGraph graphs[kGraphCache];
     uint64_t graph_clock = 0;
@@ -827,6 +831,151 @@ static int graph_for(lb_ctx* c, int p, int n, hipGraphExec_t* out) {
     return LB_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Several steps of a 2D lattice per launch: the choice of tile and steps
+// ---------------------------------------------------------------------------
+// A launch of K steps on tiles of tx x ty nodes costs about
+//   4 us                           launch, first loads, last stores, and the longer of
+//   K (0.2 + 0.4 w) us             w = wavefronts per SIMD (the halo's included): 230
+//                                  vector instructions per node and step on the coupled
+//                                  lattice, 0.65 of that on D2Q9
+//   bytes / 5.5 TB/s               the region and its rim read, the tile written, a
+//                                  quarter more when the tile's rows are not whole
+//                                  64-byte pieces,
+// (float64, whose registers leave one workgroup per CU: the two overlap less and are
+// added).  Measured on MI355X against one step per launch, us per step, D2Q9 + D2Q5 with
+// fields: float32 64^2 3.27 -> 1.27 (4 x 4 tiles, K = 7), 256^2 4.30 -> 2.2 (16 x 16, 4),
+// 1000^2 29.1 -> 11.4 and 4096^2 356 -> 168 (32 x 20, 4); float64 4096^2 784 -> 356
+// (26 x 26, 4); float16 4096^2 216 -> 159 (32 x 24, 3).  The model is within 20% of the
+// measured times over these sizes; the least modelled time per step is taken.
+struct MultiChoice {
+    MultiShape shape;
+    double us;
+};
+
+static bool multi_tile(const lb_ctx* c, int steps, int block, int tx, MultiChoice* out) {
+    const int nx = (int)c->cfg.nx, ny = (int)c->cfg.ny, halo = steps - 1;
+    MultiShape t{};
+    t.block = block;
+    t.steps = steps;
+    t.tx = tx;
+    t.hx = tx == nx ? 0 : halo;
+    t.w = t.tx + 2 * t.hx;
+    if (t.tx < 1 || t.w > block || t.hx > nx || halo > ny) return false;
+    const int rows = block / t.w;
+    if (ny <= rows) {
+        t.ty = ny;
+    } else {
+        if (rows <= 2 * halo) return false;
+        t.ty = rows - 2 * halo;
+        t.hy = halo;
+        const int tiles_y = (ny + t.ty - 1) / t.ty;
+        t.ty = (ny + tiles_y - 1) / tiles_y;   // even tiles
+    }
+    t.h = t.ty + 2 * t.hy;
+    const int64_t tiles_x = (nx + t.tx - 1) / t.tx, tiles_y = (ny + t.ty - 1) / t.ty;
+    const int64_t tiles = tiles_x * tiles_y * c->cfg.nz;
+    if (tiles > (1 << 28)) return false;
+    t.tiles_x = (uint32_t)tiles_x;
+    t.per_slice = (uint32_t)(tiles_x * tiles_y);
+    t.tiles = (uint32_t)tiles;
+    t.div_w = FastDiv((uint32_t)t.w);
+    t.div_per_slice = FastDiv(t.per_slice);
+    t.div_tiles_x = FastDiv(t.tiles_x);
+    const double waves = (double)((tiles + 255) / 256) * block / 256;
+    const double rim = (double)(t.w + (t.hx ? 2 : 0)) * (t.h + (t.hy ? 2 : 0));
+    const double fields = (c->force_field ? 2 : 0) + (c->source_field ? 1 : 0);
+    double mem = tiles * (rim * (c->q + c->qs) * c->elem + (double)t.w * t.h * fields * c->real_bytes +
+                          (double)t.tx * t.ty * (c->q + c->qs) * c->elem) / 5.5e6;
+    if (t.hx && t.tx * c->elem % 64) mem *= 1.25;
+    const double valu = steps * (0.2 + 0.4 * waves) * (c->qs ? 1.0 : 0.65);
+    out->us = (4.0 + (c->elem == 8 ? 0.75 * mem + 1.1 * valu : std::max(mem, valu))) / steps;
+    out->shape = t;
+    return true;
+}
+
+// The least modelled time per step of exactly `steps` steps in one launch.
+static bool multi_best(const lb_ctx* c, int steps, MultiChoice* best) {
+    const int nx = (int)c->cfg.nx;
+    bool found = false;
+    for (int block : {256, 512, 1024}) {
+        const int side = block == 256 ? 16 : (block == 512 ? 22 : 32);
+        const int widths[4] = {nx, side - 2 * (steps - 1), 16, 32};
+        for (int tx : widths) {
+            MultiChoice m;
+            if (tx > nx || !multi_tile(c, steps, block, tx, &m)) continue;
+            if (!found || m.us < best->us) *best = m;
+            found = true;
+        }
+    }
+    return found;
+}
+
+// Whether the lattice is stepped several steps per launch: 2D, no debugging fill, the
+// launch shape left to the library, every byte offset within 32 bits.
+static bool multi_applies(const lb_ctx* c) {
+    return c->dims == 2 && !(c->cfg.flags & LB_FLAG_DEBUG_POISON) && !c->cfg.block_x && !c->cfg.rows_per_thread &&
+           !c->cfg.x_pairs && (uint64_t)c->plane * (c->q + c->qs) * c->elem < (1ull << 32) &&
+           (uint64_t)c->plane * 2 * c->real_bytes < (1ull << 32);
+}
+
+// Tiling for the next of `plain` >= 2 steps (false: one step per launch), chosen on first
+// use and again when a field is set or cleared.
+static bool multi_shape(lb_ctx* c, int64_t plain, MultiShape* out) {
+    if (plain < 2 || !multi_applies(c)) return false;
+    const int fields = (c->force_field ? 1 : 0) + (c->source_field ? 2 : 0);
+    if (c->multi_fields != fields) {
+        c->multi_fields = fields;
+        c->multi_most = 0;
+        double us = 1e30;
+        for (int k = 2; k <= kMultiMaxSteps; ++k) {
+            MultiChoice m;
+            c->multi_ok[k] = multi_best(c, k, &m);
+            if (!c->multi_ok[k]) continue;
+            c->multi[k] = m.shape;
+            if (m.us < us) {
+                us = m.us;
+                c->multi_most = k;
+            }
+        }
+    }
+    if (c->multi_most < 2) return false;
+    // as few launches as the best length allows, of about equal length
+    const int64_t launches = (plain + c->multi_most - 1) / c->multi_most;
+    int k = (int)((plain + launches - 1) / launches);
+    while (k >= 2 && !c->multi_ok[k]) --k;
+    if (k < 2) return false;
+    *out = c->multi[k];
+    // a lattice held by its tiles whole needs no halo: nothing bounds its steps but the
+    // tables of what changes from step to step
+    if (!out->hx && !out->hy && c->force_mode == LB_TIME_CONSTANT && c->source_mode == LB_TIME_CONSTANT &&
+        !stochastic_rounding(c))
+        out->steps = (int)std::min<int64_t>(plain, 256);
+    return true;
+}
+
+static int multi_step(lb_ctx* c, const MultiShape& t) {
+    MultiArgs m;
+    memset(&m, 0, sizeof(m));
+    m.step = make_args(c, c->geo_step, c->step);
+    m.shape = t;
+    m.rates32 = node_rates<float>(m.step);
+    m.rates64 = node_rates<double>(m.step);
+    m.varying = c->force_mode != LB_TIME_CONSTANT || c->source_mode != LB_TIME_CONSTANT;
+    for (int s = 0; s < std::min(t.steps, kMultiMaxSteps); ++s) {
+        const StepArgs a = make_args(c, c->geo_step, c->step + s);
+        m.factors[s][0] = a.f_pre;
+        m.factors[s][1] = a.f_tot;
+        m.factors[s][2] = a.s_pre;
+        m.factors[s][3] = a.s_tot;
+        m.seeds[s] = a.sr_seed;
+    }
+    HIP_OR_FAIL(c, launch_multistep(c->cfg.lattice, c->cfg.storage, m, c->stream));
+    c->step += t.steps;
+    c->cur ^= 1;   // one launch, one swap
+    return LB_OK;
+}
+
 int lb_step(lb_ctx* c, int64_t nsteps) {
     if (!c) return LB_EINVAL;
     if (nsteps < 0) return fail(c, LB_EINVAL, "nsteps must be >= 0");
@@ -838,10 +987,18 @@ int lb_step(lb_ctx* c, int64_t nsteps) {
                     (long long)c->check_step);
     const int K = c->cfg.residual_interval;
     for (int64_t s = 0; s < nsteps; ++s) {
+        // plain steps before the next residual check (or the end of the call)
+        int64_t plain = nsteps - s;
+        if (K > 0) plain = std::min(plain, (int64_t)(K - 1 - c->step % K));
+        MultiShape shape;
+        while (multi_shape(c, plain, &shape)) {
+            const int rc = multi_step(c, shape);
+            if (rc) return rc;
+            s += shape.steps;
+            plain -= shape.steps;
+        }
+        if (s >= nsteps) break;
         if (graphs_apply(c)) {
-            // plain steps before the next residual check (or the end of the call)
-            int64_t plain = nsteps - s;
-            if (K > 0) plain = std::min(plain, (int64_t)(K - 1 - c->step % K));
             while (plain >= kGraphMinSteps) {
                 const int n = (int)std::min<int64_t>(plain, kGraphSteps);
                 hipGraphExec_t ge = nullptr;

@@ -84,4 +84,43 @@ struct StepArgs {
 };
 constexpr int kWallTable = 16;
 
+// Relaxation rates and time factors of a step in the arithmetic type.
+template <class Real>
+struct NodeRates {
+    Real rho0, shear, bulk, third, fourth, phi, phi_high, lorentz;
+    Real f_pre, f_tot, s_pre, s_tot, heat;
+};
+
+template <class Real>
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline NodeRates<Real> node_rates(const StepArgs& a) {
+    return {Real(a.rho0), Real(a.w_shear), Real(a.w_bulk), Real(a.w_third), Real(a.w_fourth), Real(a.w_phi),
+            Real(a.w_phi_high), Real(a.lorentz), Real(a.f_pre), Real(a.f_tot), Real(a.s_pre), Real(a.s_tot),
+            Real(a.heat)};
+}
+
+// Several steps of a 2D lattice per launch (casclb_multistep).
+constexpr int kMultiMaxSteps = 16;
+
+// Tiling of one slice: a workgroup of `block` threads owns tx x ty nodes and
+// steps the region w x h = (tx + 2 hx) x (ty + 2 hy) <= block around them, the
+// halo hx, hy being steps - 1 nodes, or 0 on an axis the tile covers whole.
+struct MultiShape {
+    int32_t tx, ty, hx, hy, w, h, steps, block;
+    uint32_t tiles, per_slice, tiles_x;   // workgroups in all, per slice and along x
+    FastDiv div_w, div_per_slice, div_tiles_x;
+};
+
+struct MultiArgs {
+    StepArgs step;               // src, dst, fields and settings; the factors of the first step
+    MultiShape shape;
+    NodeRates<float> rates32;    // the step's rates in the arithmetic type
+    NodeRates<double> rates64;
+    int32_t varying;             // 1: factors[s] = f_pre, f_tot, s_pre, s_tot of step s
+    double factors[kMultiMaxSteps][4];
+    uint32_t seeds[kMultiMaxSteps];   // stochastic rounding: sr_seed of step s
+};
+
 }  // namespace casclb
