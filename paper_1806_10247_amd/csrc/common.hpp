@@ -46,6 +46,7 @@ struct Geometry {
     int32_t xpair;        // 1: 16-bit storage, a thread updates nodes 2t, 2t+1 (x_blocks counts pairs)
     FastDiv div_xb;       // division by x_blocks
     FastDiv div_ny;       // division by ny
+    int32_t flat;         // 1: threads take consecutive flat nodes (casclb_step_flat), not rows
 };
 
 // Arguments of the fused step kernel (passed by value).
@@ -80,6 +81,7 @@ struct StepArgs {
     // 0 = rounded to nearest
     int32_t sr;
     uint32_t sr_seed;
+    FastDiv div_nx;        // division by nx (flat launches)
     double lorentz;        // 2D lattices: s of the velocity-dependent x-force -s u_x (0: none)
 };
 constexpr int kWallTable = 16;

@@ -25,30 +25,6 @@
 
 namespace casclb {
 
-// FP64 sum over the block of kDiagSlots values; thread 0 of the block gets the result.
-__device__ __forceinline__ void block_sum(double (&v)[kDiagSlots], double* out) {
-    __shared__ double red[kMaxBlock / 64][kDiagSlots];
-    static_for<kDiagSlots>([&](auto cc) {
-        constexpr int C = decltype(cc)::value;
-        double s = v[C];
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        v[C] = s;
-    });
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0)
-        static_for<kDiagSlots>([&](auto cc) {   // compile-time indices keep v in registers
-            constexpr int C = decltype(cc)::value;
-            red[wave][C] = v[C];
-        });
-    __syncthreads();
-    if (threadIdx.x < kDiagSlots) {
-        double s = 0.0;
-        const int nw = (blockDim.x + 63) >> 6;
-        for (int w = 0; w < nw; ++w) s += red[w][threadIdx.x];
-        out[threadIdx.x] = s;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // the fused step
 // ---------------------------------------------------------------------------
@@ -188,11 +164,6 @@ __device__ __forceinline__ PairPos pair_position(const Geometry& g) {
     return q;
 }
 
-__device__ __forceinline__ _Float16 half_lo(uint32_t w) { return __builtin_bit_cast(_Float16, (uint16_t)w); }
-__device__ __forceinline__ _Float16 half_hi(uint32_t w) {
-    return __builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
-}
-
 // The pull (eq. 22b, halfway bounce-back at y / z walls) of population
 // `plane_self` with velocity (EX, EY, EZ) for both nodes of the pair.
 template <int EX, int EY, int EZ>
@@ -232,12 +203,6 @@ __device__ __forceinline__ void pull_pair(const uint32_t* __restrict__ src, cons
         v0 = wall ? half_lo(wa) : half_hi(wa);
         v1 = wall ? half_hi(wb) : half_lo(wb);
     }
-}
-
-__device__ __forceinline__ uint32_t pack_halves(float lo, float hi) {
-    const uint16_t a = __builtin_bit_cast(uint16_t, static_cast<_Float16>(lo));
-    const uint16_t b = __builtin_bit_cast(uint16_t, static_cast<_Float16>(hi));
-    return (uint32_t)a | ((uint32_t)b << 16);
 }
 
 template <int LAT, bool DIAG, bool EXT, bool SR>
@@ -755,6 +720,7 @@ hipError_t launch_step_t(const StepArgs& a, int block, bool diag, hipStream_t s)
 }  // namespace
 
 hipError_t launch_step(int lat, int storage, const StepArgs& a, int block, bool diag, hipStream_t s) {
+    if (a.geo.flat) return launch_step_flat(lat, storage, a, block, diag, s);
     switch (lat * 3 + storage) {
         case kD2Q9 * 3 + kF64: return launch_step_t<kD2Q9, double, double>(a, block, diag, s);
         case kD2Q9 * 3 + kF32Dev: return launch_step_t<kD2Q9, float, float>(a, block, diag, s);

@@ -11,6 +11,8 @@ namespace casclb {
 // Fused step: one launch of a.geo.grid_blocks blocks of `block` threads.
 // diag = true also updates the residual record (u_prev, partials).
 hipError_t launch_step(int lattice, int storage, const StepArgs& a, int block, bool diag, hipStream_t s);
+// The step of a 3D lattice over flat node indices (a.geo.flat).
+hipError_t launch_step_flat(int lattice, int storage, const StepArgs& a, int block, bool diag, hipStream_t s);
 // a.shape.steps steps of a 2D lattice in one launch (no residual record).
 hipError_t launch_multistep(int lattice, int storage, const MultiArgs& a, hipStream_t s);
 // Sums `blocks` diagnostic partial records into out[kDiagSlots].

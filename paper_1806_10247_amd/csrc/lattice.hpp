@@ -153,6 +153,13 @@ __device__ __forceinline__ void shift(Real (&m)[Flow<D>::Q], const Real (&u)[3])
     });
 }
 
+// Where a sum has two products, or a product formed elsewhere, which of them the
+// compiler fuses depends on the rest of the kernel.  In float64 on D3Q27 it chose
+// differently by rows and over flat indices, so these are fused explicitly there;
+// the other lattices' kernels and float32 agree without.
+template <int D, class Real>
+constexpr bool explicit_fma = D == 3 && sizeof(Real) == 8;
+
 // Raw moment k of (equilibrium at (rho, u)) - (rest equilibrium at rho0),
 // with per-axis factors b = (1, 0, 1/3) (rest) and c = (1, u, 1/3 + u^2):
 // E = drho * prod b + rho * (prod c - prod b), the bracket telescoped axis by
@@ -172,12 +179,14 @@ __device__ __forceinline__ Real eq_deviation(Real drho, Real rho, const Real (&u
             pb = Real(0);
         } else {
             const Real third = Real(1) / Real(3);
-            diff = diff * third + pc * usq[AX];
+            if constexpr (explicit_fma<D, Real>) diff = fma(diff, third, pc * usq[AX]);
+            else diff = diff * third + pc * usq[AX];
             pc = pc * (third + usq[AX]);
             pb = pb * third;
         }
     });
-    return drho * pb + rho * diff;
+    if constexpr (explicit_fma<D, Real>) return fma(drho, pb, rho * diff);
+    else return drho * pb + rho * diff;
 }
 
 // Coefficient of F_tot[axis] in raw moment K of the kick F_tot . e_a / <e_x|e_x>:
@@ -282,7 +291,8 @@ __device__ __forceinline__ void collide_flow(Real (&m)[Flow<D>::Q], Real rho0, c
                 if constexpr (kick_nonzero<D, K, AX>()) {
                     constexpr int n23 = kick_twothirds_power<D, K, AX>();
                     const Real c = n23 == 0 ? Real(1) : (n23 == 1 ? Real(2) / Real(3) : Real(4) / Real(9));
-                    v = v + c * ftot[AX];
+                    if constexpr (explicit_fma<D, Real>) v = fma(c, ftot[AX], v);
+                    else v = v + c * ftot[AX];
                 }
             });
             m[K] = v;

@@ -38,15 +38,6 @@ namespace casclb {
 
 namespace {
 
-// a value the optimiser may not treat as the same from one step to the next:
-// products with it are then formed (and fused) where the one-step kernel forms
-// them, not once outside the loop
-template <class Real>
-__device__ __forceinline__ Real per_step(Real v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 template <class T>
 __device__ __forceinline__ T load_at(const void* base, uint32_t byte_offset) {
     return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + byte_offset);
@@ -155,7 +146,7 @@ __global__ void __launch_bounds__(BLOCK) casclb_multistep(const MultiArgs ma) {
             k.s_pre = Real(ma.factors[s][2]);
             k.s_tot = Real(ma.factors[s][3]);
         }
-        const Real fs[3] = {per_step(fb[0]), per_step(fb[1]), Real(0)}, ss = per_step(sb);
+        const Real fs[3] = {pinned(fb[0]), pinned(fb[1]), Real(0)}, ss = pinned(sb);
         NodeResult<Real> r;
         collide_values<LAT, Real, EXT>(a, k, p, fs, [&] { return ss; }, m, sc, r);
         // the stored values, as the one-step kernels store them

@@ -81,6 +81,17 @@ __device__ __forceinline__ _Float16 half_sr(float v, uint32_t r) {
     return o[0];
 }
 
+__device__ __forceinline__ _Float16 half_lo(uint32_t w) { return __builtin_bit_cast(_Float16, (uint16_t)w); }
+__device__ __forceinline__ _Float16 half_hi(uint32_t w) {
+    return __builtin_bit_cast(_Float16, (uint16_t)(w >> 16));
+}
+
+__device__ __forceinline__ uint32_t pack_halves(float lo, float hi) {
+    const uint16_t a = __builtin_bit_cast(uint16_t, static_cast<_Float16>(lo));
+    const uint16_t b = __builtin_bit_cast(uint16_t, static_cast<_Float16>(hi));
+    return (uint32_t)a | ((uint32_t)b << 16);
+}
+
 struct RowPos {
     int y, z;            // block-uniform
     int64_t row;         // block-uniform: nx*(y + ny*z)
@@ -294,6 +305,15 @@ __device__ __forceinline__ void scalar_walls(const StepArgs& a, const RowPos& p,
     });
 }
 
+// A value the optimiser may not move computations on ahead of this point: the
+// products with it are formed (and fused with the sums they enter) in the
+// collision, as in the kernels of one step, not once outside a loop over steps.
+template <class Real>
+__device__ __forceinline__ Real pinned(Real v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // What a node's collision leaves besides its populations.
 template <class Real>
 struct NodeResult {
@@ -443,6 +463,30 @@ __device__ __forceinline__ void collide_node(const StepArgs& a, const RowPos& p,
 // Random key of one node's stores in this step (stochastic rounding).
 __device__ __forceinline__ uint32_t sr_node_key(const StepArgs& a, const RowPos& p) {
     return mix32(((uint32_t)p.node * 0x9E3779B1u) ^ a.sr_seed);
+}
+
+// FP64 sum over the block of kDiagSlots values; thread 0 of the block gets the result.
+__device__ __forceinline__ void block_sum(double (&v)[kDiagSlots], double* out) {
+    __shared__ double red[kMaxBlock / 64][kDiagSlots];
+    static_for<kDiagSlots>([&](auto cc) {
+        constexpr int C = decltype(cc)::value;
+        double s = v[C];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        v[C] = s;
+    });
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0)
+        static_for<kDiagSlots>([&](auto cc) {   // compile-time indices keep v in registers
+            constexpr int C = decltype(cc)::value;
+            red[wave][C] = v[C];
+        });
+    __syncthreads();
+    if (threadIdx.x < kDiagSlots) {
+        double s = 0.0;
+        const int nw = (blockDim.x + 63) >> 6;
+        for (int w = 0; w < nw; ++w) s += red[w][threadIdx.x];
+        out[threadIdx.x] = s;
+    }
 }
 
 }  // namespace casclb
