@@ -109,217 +109,6 @@ __global__ void __launch_bounds__(256) conv3x3_mfma(ConvArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// forward convolution with the input tile in LDS
-// ---------------------------------------------------------------------------
-// Workgroup = 4 wavefronts = one TH x TW pixel tile of one image (TW = 32,
-// TH = 8, or TW = 16, TH = 16).  The tile plus a one-pixel circular halo is
-// staged once in LDS as bf16 (pixel stride ci_pad + 8 elements: the 16 lanes
-// reading 16 consecutive pixels hit distinct banks).  Wave w owns R = 64/TW
-// rows, i.e. four 16-pixel matrix-core tiles; per 32-wide K slice a lane reads
-// its four A fragments from LDS and one B fragment (8 weights of one output
-// channel) per 16-channel output tile from global memory, each B feeding four
-// products.  The output tiles are taken NU at a time (NU = min(tiles, 4)): the
-// accumulators of a pass are 16 NU registers, so a 16-channel layer keeps
-// enough waves per SIMD to overlap one workgroup's staging with another's
-// products.  Epilogue: bias, ReLU, store; with `pool`, the 2 x 2 means of the
-// bf16-rounded outputs (the two pixels of a row pair are in one lane, the two
-// rows in tiles t and t + TW/16 of the same lane), in the order of avgpool_k.
-template <int TW, int XMODE, bool YF32, int NU, int PF>
-__global__ void __launch_bounds__(256) conv3x3_tiled(ConvArgs a) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    bf16_t* tile = reinterpret_cast<bf16_t*>(lds_raw);
-    constexpr int R = 64 / TW, TH = 4 * R, HW = TW + 2, HH = TH + 2, NP = HW * HH, TPR = TW / 16;
-    using DivHW = SmallDiv<HW, NP>;
-    // addresses are 32-bit element offsets with 24-bit multiplies (conv_tiled_offsets_fit
-    // checks on the host that every tensor and row stride fits)
-    const uint32_t ps = a.ci_pad + 8;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, col = lane & 15;
-    const int tiles_x = a.w / TW, tiles_y = a.h / TH;
-    int b = blockIdx.x;
-    const int tx = b % tiles_x;
-    b /= tiles_x;
-    const int ty = b % tiles_y;
-    const uint32_t img = b / tiles_y;
-    const int x0 = tx * TW, y0 = ty * TH;
-    const uint32_t cpp = a.ci_pad / 8;   // 8-channel chunks per pixel
-    const float inv_cpp = 1.0f / (float)cpp;
-    const PixelOffsets src = pixel_offsets(img, a.h, a.w, XMODE == 0 ? a.x.cs : a.cin_raw, XMODE == 0 ? a.x.co : 0);
-    const PixelOffsets src2 = pixel_offsets(img, a.h >> 1, a.w >> 1, a.x2.cs, a.x2.co);
-    // staged in rounds of SB chunks per thread, all loads of a round issued
-    // before its LDS stores (one memory latency per round, not per chunk)
-    constexpr int SB = 8;
-    if constexpr (XMODE == 2) {
-        // raw fp32 input, cin_raw floats per pixel: the lanes read consecutive floats of
-        // each tile row (one halo row = HW pixels, contiguous in memory unless it wraps),
-        // and the channels from cin_raw to ci_pad are zeroed apart
-        const uint32_t cr = a.cin_raw, seg = HW * cr, total = HH * seg;
-        const float inv_cr = 1.0f / (float)cr, inv_seg = 1.0f / (float)seg;
-        for (uint32_t f0 = 0; f0 < total; f0 += SB * 256) {
-            float v[SB];
-            uint32_t at_lds[SB];
-#pragma unroll
-            for (int r = 0; r < SB; ++r) {
-                const uint32_t f = f0 + r * 256 + threadIdx.x;
-                if (f < total) {
-                    const uint32_t row = div_by_inv(f, inv_seg), fr = f - mul24(row, seg);
-                    const uint32_t qx = div_by_inv(fr, inv_cr), c = fr - mul24(qx, cr);
-                    const int yy = wrap(y0 - 1 + (int)row, a.h), xx = wrap(x0 - 1 + (int)qx, a.w);
-                    v[r] = a.xin[src.at(yy, xx, c)];
-                    at_lds[r] = mul24(row * HW + qx, ps) + c;
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < SB; ++r)
-                if (f0 + r * 256 + threadIdx.x < total) tile[at_lds[r]] = __builtin_bit_cast(bf16_t, (__bf16)v[r]);
-        }
-        const uint32_t padc = a.ci_pad - cr;
-        if (padc > 0) {
-            const float inv_pad = 1.0f / (float)padc;
-            for (uint32_t z = threadIdx.x; z < NP * padc; z += 256) {
-                const uint32_t q = div_by_inv(z, inv_pad), c = cr + z - mul24(q, padc);
-                tile[mul24(q, ps) + c] = 0;
-            }
-        }
-    }
-    for (int e0 = 0; XMODE == 0 && e0 < NP * (int)cpp; e0 += SB * 256) {   // bf16 input (XMODE 0)
-        bf16x8 v[SB];
-#pragma unroll
-        for (int r = 0; r < SB; ++r) {
-            const uint32_t e = e0 + r * 256 + threadIdx.x;
-            if (e < NP * cpp) {
-                uint32_t q, c0;
-                chunk_of(e, cpp, inv_cpp, q, c0);
-                const uint32_t qy = DivHW::div(q), qx = q - qy * HW;
-                const int yy = wrap(y0 - 1 + (int)qy, a.h), xx = wrap(x0 - 1 + (int)qx, a.w);
-                const bf16_t* xb = reinterpret_cast<const bf16_t*>(a.x.base);
-                const bf16_t* x2b = reinterpret_cast<const bf16_t*>(a.x2.base);
-                if ((int)c0 < a.c_split)
-                    v[r] = *reinterpret_cast<const bf16x8*>(xb + src.at(yy, xx, c0));
-                else
-                    v[r] = *reinterpret_cast<const bf16x8*>(x2b + src2.at(yy >> 1, xx >> 1, c0 - a.c_split));
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < SB; ++r) {
-            const uint32_t e = e0 + r * 256 + threadIdx.x;
-            if (e < NP * cpp) {
-                uint32_t q, c0;
-                chunk_of(e, cpp, inv_cpp, q, c0);
-                *reinterpret_cast<bf16x8*>(tile + mul24(q, ps) + c0) = v[r];
-            }
-        }
-    }
-    __syncthreads();
-    const int ktot = 9 * a.ci_pad;
-    const int co16 = (a.co + 15) >> 4;
-    // LDS element offset of this lane's A row (halo coordinates) in pixel tile t
-    uint32_t lp[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) lp[t] = mul24((wave * R + t / TPR) * HW + 16 * (t % TPR) + col, ps);
-    const PixelOffsets dst = pixel_offsets(img, a.h, a.w, a.y.cs, a.y.co);
-    const PixelOffsets dpool = pixel_offsets(img, a.h >> 1, a.w >> 1, a.pool.cs, a.pool.co);
-    for (int cg = 0; cg < co16; cg += NU) {
-        f32x4 acc[4][NU];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int u = 0; u < NU; ++u) acc[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const bf16_t* wrow = a.wt + (int64_t)(cg * 16 + col) * a.kpad + 8 * grp;
-        // B fragments of the next PF K slices are in flight while the current one is used
-        // (slice s in bq[s % PF]; the loop is unrolled by PF so the ring is indexed statically)
-        bf16x8 bq[PF][NU];
-#pragma unroll
-        for (int q = 0; q < PF; ++q)
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-                if (cg + u < co16 && 32 * q < a.kpad)
-                    bq[q][u] = *reinterpret_cast<const bf16x8*>(wrow + (int64_t)u * 16 * a.kpad + 32 * q);
-        // tap and channel of this lane's K index 8 grp + 32 s in slice s
-        TapCursor kc;
-        kc.start(8 * grp, a.ci_pad);
-        for (int k = 0; k < a.kpad; k += 32 * PF) {
-#pragma unroll
-            for (int q = 0; q < PF; ++q) {
-                const int kq = k + 32 * q;
-                if (kq >= a.kpad) break;
-                const int k0 = kq + 8 * grp;
-                bf16x8 bc[NU];
-#pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    bc[u] = bq[q][u];
-                    if (cg + u < co16 && kq + 32 * PF < a.kpad)
-                        bq[q][u] = *reinterpret_cast<const bf16x8*>(wrow + (int64_t)u * 16 * a.kpad + kq + 32 * PF);
-                }
-                bf16x8 av[4];
-                if (k0 < ktot) {
-                    const uint32_t dy = tap_row(kc.tap), dx = kc.tap - 3 * dy;
-                    const uint32_t off = mul24(dy * HW + dx, ps) + kc.c;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) av[t] = *reinterpret_cast<const bf16x8*>(tile + lp[t] + off);
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) av[t][i] = (__bf16)0.0f;
-                }
-                kc.advance32(a.ci_pad);
-#pragma unroll
-                for (int u = 0; u < NU; ++u) {
-                    if (cg + u < co16) {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[t], bc[u], acc[t][u], 0, 0, 0);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int o = (cg + u) * 16 + col;
-            if (cg + u >= co16 || o >= a.co) continue;
-            const float bias = a.bias ? a.bias[o] : 0.0f;
-            float v[4][4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int row = y0 + wave * R + t / TPR;
-                const uint32_t base = dst.at(row, x0 + 16 * (t % TPR) + 4 * grp, o);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float x = acc[t][u][j] + bias;
-                    if (a.relu) x = fmaxf(x, 0.0f);
-                    const uint32_t off = base + j * dst.cs;
-                    if constexpr (YF32) {
-                        float* d = reinterpret_cast<float*>(a.y.base) + off;
-                        *d = a.accumulate ? *d + x : x;
-                    } else {
-                        const bf16_t hb = f2bf(x);
-                        reinterpret_cast<bf16_t*>(a.y.base)[off] = hb;
-                        x = bf2f(hb);
-                    }
-                    v[t][j] = x;
-                }
-            }
-            if constexpr (!YF32) {
-                if (a.pool.base) {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        if ((t / TPR) % 2) continue;   // the upper row of each row pair
-                        const int t2 = t + TPR;
-                        const int prow = (y0 + wave * R + t / TPR) >> 1;
-#pragma unroll
-                        for (int j = 0; j < 4; j += 2) {
-                            const float sum = (v[t][j] + v[t][j + 1]) + (v[t2][j] + v[t2][j + 1]);
-                            const int px = (x0 + 16 * (t % TPR) + 4 * grp + j) >> 1;
-                            reinterpret_cast<bf16_t*>(a.pool.base)[dpool.at(prow, px, o)] = f2bf(0.25f * sum);
-                        }
-                    }
-                }
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
 // weight gradient
 // ---------------------------------------------------------------------------
 // Workgroup = one (16 outputs o, 16 inputs c) tile, all 9 taps, and one split
@@ -652,10 +441,6 @@ __global__ void pack_input_k(const float* x, int cin, View dst, int cpad, int64_
     }
 }
 
-__global__ void unpack_output_k(View src, int c, float* y, int64_t pixels) {
-    GRID_STRIDE(i, pixels * c) y[i] = *at<const float>(src, i / c, (int)(i % c));
-}
-
 __global__ void __launch_bounds__(256) mse_k(View y, const float* t, int c, int64_t pixels, View grad,
                                              double* partials, float weight) {
     __shared__ double red[256];
@@ -746,85 +531,6 @@ hipError_t launch_conv(const ConvArgs& a_in, bool x_f32, bool y_f32, hipStream_t
     return hipGetLastError();
 }
 
-// Dynamic LDS above the default limit needs the kernel attribute (once per instance).
-template <int TW, int XMODE, bool YF32, int NU, int PF>
-hipError_t conv_tiled_lds_limit(size_t lds) {
-    static bool done = false;
-    if (lds <= 65536 || done) return hipSuccess;
-    const hipError_t e = hipFuncSetAttribute((const void*)conv3x3_tiled<TW, XMODE, YF32, NU, PF>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    done = e == hipSuccess;
-    return e;
-}
-
-template <int TW, int NU, int PF>
-hipError_t launch_conv_tiled_nu(const ConvArgs& a, bool raw, bool y_f32, dim3 grid, size_t lds, hipStream_t s) {
-    hipError_t e = hipSuccess;
-    if (raw && y_f32) e = conv_tiled_lds_limit<TW, 2, true, NU, PF>(lds);
-    else if (raw) e = conv_tiled_lds_limit<TW, 2, false, NU, PF>(lds);
-    else if (y_f32) e = conv_tiled_lds_limit<TW, 0, true, NU, PF>(lds);
-    else e = conv_tiled_lds_limit<TW, 0, false, NU, PF>(lds);
-    if (e != hipSuccess) return e;
-    const dim3 blk(256);
-    if (raw && y_f32) hipLaunchKernelGGL((conv3x3_tiled<TW, 2, true, NU, PF>), grid, blk, lds, s, a);
-    else if (raw) hipLaunchKernelGGL((conv3x3_tiled<TW, 2, false, NU, PF>), grid, blk, lds, s, a);
-    else if (y_f32) hipLaunchKernelGGL((conv3x3_tiled<TW, 0, true, NU, PF>), grid, blk, lds, s, a);
-    else hipLaunchKernelGGL((conv3x3_tiled<TW, 0, false, NU, PF>), grid, blk, lds, s, a);
-    return hipGetLastError();
-}
-
-// Weight fragments in flight: one K slice ahead where the grid fills the chip (the
-// other workgroups hide the latency), kDeepPrefetch slices where a few workgroups
-// each run a long K loop alone.
-constexpr int kDeepPrefetch = 4;
-constexpr int64_t kDeepPrefetchBlocks = 512;
-
-template <int TW, int NU>
-hipError_t launch_conv_tiled_pf(const ConvArgs& a, bool raw, bool y_f32, dim3 grid, size_t lds, hipStream_t s) {
-    if (grid.x <= kDeepPrefetchBlocks) return launch_conv_tiled_nu<TW, NU, kDeepPrefetch>(a, raw, y_f32, grid, lds, s);
-    return launch_conv_tiled_nu<TW, NU, 1>(a, raw, y_f32, grid, lds, s);
-}
-
-template <int TW>
-hipError_t launch_conv_tiled_tw(const ConvArgs& a, bool raw, bool y_f32, dim3 grid, size_t lds, hipStream_t s) {
-    switch ((a.co + 15) >> 4) {
-        case 1: return launch_conv_tiled_pf<TW, 1>(a, raw, y_f32, grid, lds, s);
-        case 2: return launch_conv_tiled_pf<TW, 2>(a, raw, y_f32, grid, lds, s);
-        case 3: return launch_conv_tiled_pf<TW, 3>(a, raw, y_f32, grid, lds, s);
-        default: return launch_conv_tiled_pf<TW, 4>(a, raw, y_f32, grid, lds, s);
-    }
-}
-
-bool conv_tiled_fits(int32_t h, int32_t w, int32_t ci_pad) {
-    if (ci_pad < 16 || ci_pad > 128 || ci_pad % 8) return false;
-    return (w % 32 == 0 && h % 8 == 0) || (w % 16 == 0 && h % 16 == 0);
-}
-
-bool conv_tiled_offsets_fit(const ConvArgs& a) {
-    // every tensor the kernel addresses in 32-bit element offsets, and every row
-    // stride and coordinate within the 24-bit multiplies
-    const int64_t px = (int64_t)a.n * a.h * a.w;
-    const int64_t lim = (int64_t)1 << 31, lim24 = (int64_t)1 << 24;
-    const int64_t cs[5] = {a.x.base ? a.x.cs : 0, a.y.cs, a.x2.base ? a.x2.cs : 0, a.pool.base ? a.pool.cs : 0,
-                           a.xin ? a.cin_raw : 0};
-    if (a.h >= lim24 || a.w >= lim24 || a.n >= lim24) return false;
-    for (int64_t c : cs)
-        if (px * (c + 8) >= lim || (int64_t)a.w * (c + 8) >= lim24) return false;
-    return true;
-}
-
-hipError_t launch_conv_tiled(const ConvArgs& a, bool y_f32, hipStream_t s) {
-    if (!conv_tiled_fits(a.h, a.w, a.ci_pad) || !conv_tiled_offsets_fit(a)) return hipErrorInvalidValue;
-    const bool wide = a.w % 32 == 0 && a.h % 8 == 0;
-    const int tw = wide ? 32 : 16, th = wide ? 8 : 16;
-    const int64_t blocks = (int64_t)a.n * (a.h / th) * (a.w / tw);
-    const size_t lds = (size_t)(tw + 2) * (th + 2) * (a.ci_pad + 8) * sizeof(bf16_t);
-    const dim3 grid((unsigned)blocks);
-    const bool raw = a.xin != nullptr;
-    return wide ? launch_conv_tiled_tw<32>(a, raw, y_f32, grid, lds, s)
-                : launch_conv_tiled_tw<16>(a, raw, y_f32, grid, lds, s);
-}
-
 int32_t wgrad_splits(int64_t pixels, int32_t* chunks_per_wave) {
     // about 512 pixels per wavefront (each feeds 9 products per chunk), at least one split
     int32_t cpw = 16;
@@ -902,11 +608,6 @@ hipError_t launch_relu_mask(View g, View act, int64_t pixels, int32_t c, hipStre
 
 hipError_t launch_pack_input(const float* x, int32_t cin, View dst, int32_t cpad, int64_t pixels, hipStream_t s) {
     hipLaunchKernelGGL(pack_input_k, dim3(grid_for(pixels * cpad)), dim3(256), 0, s, x, cin, dst, cpad, pixels);
-    return hipGetLastError();
-}
-
-hipError_t launch_unpack_output(View src, int32_t c, float* y, int64_t pixels, hipStream_t s) {
-    hipLaunchKernelGGL(unpack_output_k, dim3(grid_for(pixels * c)), dim3(256), 0, s, src, c, y, pixels);
     return hipGetLastError();
 }
 

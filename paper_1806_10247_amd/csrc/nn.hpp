@@ -33,26 +33,27 @@ struct ConvArgs {
     int32_t n, h, w;
     int32_t ci_pad, kpad, co, co_pad32;
     int32_t relu, accumulate;
-    // tiled kernel only (launch_conv_tiled):
+    // launch_conv_lds only:
     View x2;            // base != null: input channels [c_split, ci_pad) come from this bf16 view at half
                         // resolution (nearest 2x upsampling fused into the load), [0, c_split) from x
-    int32_t c_split;
+    int32_t c_split;    // ci_pad without x2
     View pool;          // base != null: also write the 2x2 means of the bf16 output here (half resolution)
-    const float* xin;   // != null: the input is this raw fp32 [pixels][cin_raw] array (zeros past cin_raw)
+    const float* xin;   // != null: the input is this raw fp32 [pixels][cin_raw] array, 16-byte aligned (zeros
+                        // past cin_raw <= 16, ci_pad 16)
     int32_t cin_raw;
-    FastDiv div_w, div_h;   // plain kernel only, set by launch_conv
+    View mask;          // base != null (fp32 output): results where this bf16 view is not > 0 are set to 0
+    // set by the launchers
+    int32_t y_vec;      // fp32 output: 16-byte stores are aligned
+    FastDiv div_w, div_h, div_raw, div_cin;
 };
 hipError_t launch_conv(const ConvArgs& a, bool x_f32, bool y_f32, hipStream_t s);
 
-// The same convolution (bf16 or raw fp32 input, bf16 or fp32 output) with the
-// input tile and its circular halo staged in LDS: a workgroup computes an
-// 8 x 32 (or 16 x 16) pixel tile of one image for all output channels.  Needs
-// w a multiple of 16 and h of 16 (or w of 32 and h of 8) and ci_pad <= 128;
-// returns hipErrorInvalidValue otherwise (use launch_conv).
-bool conv_tiled_fits(int32_t h, int32_t w, int32_t ci_pad);
-// Whether the tensors and strides of a tiled convolution fit its 32-bit offsets and 24-bit multiplies.
-bool conv_tiled_offsets_fit(const ConvArgs& a);
-hipError_t launch_conv_tiled(const ConvArgs& a, bool y_f32, hipStream_t s);
+// The same convolution (bf16, fp32 or raw fp32 input, bf16 or fp32 output) with
+// the input tile and its circular halo staged in LDS.  Needs w a multiple of 16,
+// h of 8, ci_pad a multiple of 16 up to 128 (or 160, 192) and no accumulation
+// (conv_lds_fits).
+bool conv_lds_fits(const ConvArgs& a);
+hipError_t launch_conv_lds(const ConvArgs& a, bool x_f32, bool y_f32, hipStream_t s);
 
 // Weight gradient dW[o][tap][c] = sum_p g[p][o] x[p shifted by tap][c] over
 // N x H x W pixels: g fp32 view (co channels), x bf16 view (ci channels).
@@ -91,8 +92,6 @@ hipError_t launch_upsample_bwd(View src, View dst, int32_t n, int32_t h, int32_t
 hipError_t launch_relu_mask(View g, View act, int64_t pixels, int32_t c, hipStream_t s);
 // Pack fp32 [pixels][cin] into a bf16 view with cpad channels (zeros past cin).
 hipError_t launch_pack_input(const float* x, int32_t cin, View dst, int32_t cpad, int64_t pixels, hipStream_t s);
-// Copy channels [0, c) of an fp32 view into a dense fp32 [pixels][c] array.
-hipError_t launch_unpack_output(View src, int32_t c, float* y, int64_t pixels, hipStream_t s);
 // Mean squared error: grad (fp32 view, c channels) = 2 weight (y - t) / (pixels*c);
 // per-block float64 partial sums of (y - t)^2 into partials[blocks].
 hipError_t launch_mse(View y, const float* t, int32_t c, int64_t pixels, View grad, double* partials, int32_t blocks,

@@ -44,13 +44,11 @@ struct lb_unet {
     lb_unet_config cfg{};
     hipStream_t stream = nullptr;
     int L = 0, out16 = 0;
-    int out_cs = 0;   // channel stride of the inference output: out_channels rounded up to 4
     std::vector<Layer> layers;
     std::vector<Level> lv;
     int64_t np = 0;
     float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
     float *out = nullptr, *g_out = nullptr;
-    float* out_inf = nullptr;   // inference output, out_cs floats per pixel
     float* wpart = nullptr;
     int64_t wpart_n = 0;
     float* bpart = nullptr;
@@ -65,10 +63,8 @@ struct lb_unet {
     float lp_weight = 0.0f;
     std::vector<float*> lp_y, lp_t, lp_g;   // per level 1..lp_levels (index l - 1)
     int32_t last_batch = 0;
-    // inference: the input is copied into xin, then the whole forward pass
-    // (everything between that copy and the output unpacking) is replayed from
-    // a graph captured once per batch size on a private stream
-    float* xin = nullptr;
+    // inference: the layers between the first and the last are replayed from a graph
+    // captured once per batch size on a private stream
     hipStream_t cap_stream = nullptr;
     std::vector<hipGraph_t> fwd_graph;
     std::vector<hipGraphExec_t> fwd_exec;
@@ -183,7 +179,6 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
     n->stream = (hipStream_t)cfg->stream;
     n->L = L;
     n->out16 = 16;
-    n->out_cs = (cfg->out_channels + 3) / 4 * 4;
     n->lv.resize(L);
     for (int l = 0; l < L; ++l) {
         Level& q = n->lv[l];
@@ -254,7 +249,6 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
         const int64_t P0 = B * cfg->height * cfg->width;
         UALLOC(n->out, P0 * n->out16);
         UALLOC(n->g_out, P0 * n->out16);
-        UALLOC(n->out_inf, P0 * n->out_cs);
         int64_t wmax = 0;
         int32_t bmax = 0;
         for (const Layer& y : n->layers) {
@@ -270,7 +264,6 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
         UALLOC(n->bpart, bmax);
         UALLOC(n->mse_part, n->mse_blocks);
         UALLOC(n->loss_dev, 2);
-        UALLOC(n->xin, P0 * cfg->in_channels);
     }
 #undef UALLOC
     e = hipHostMalloc((void**)&n->loss_host, 2 * sizeof(double), hipHostMallocDefault);
@@ -333,7 +326,6 @@ int lb_unet_get_params(lb_unet* n, float* params_host) {
 static int conv_tiled(lb_unet* n, const Layer& y, View x, View out, bool out_f32, int batch, bool relu, View x2,
                       int c_split, View pool, const float* xin, int cin_raw) {
     const Level& q = n->lv[y.level];
-    if (!conv_tiled_fits(q.h, q.w, y.ci_pad)) return 1;
     ConvArgs a{};
     a.x = x;
     a.y = out;
@@ -353,8 +345,8 @@ static int conv_tiled(lb_unet* n, const Layer& y, View x, View out, bool out_f32
     a.pool = pool;
     a.xin = xin;
     a.cin_raw = cin_raw;
-    if (!conv_tiled_offsets_fit(a)) return 1;
-    UHIP(n, launch_conv_tiled(a, out_f32, n->stream));
+    if (!conv_lds_fits(a) || (xin && ((uintptr_t)xin & 15))) return 1;
+    UHIP(n, launch_conv_lds(a, false, out_f32, n->stream));
     return LB_OK;
 }
 
@@ -395,24 +387,10 @@ static int dgrad(lb_unet* n, const Layer& y, View g, View dx, int batch) {
     a.co_pad32 = y.ci_pad32;
     a.relu = 0;
     a.accumulate = 0;
-    // on launches that fill the chip (more than 512 tiles) the LDS-tiled kernel reads a
-    // dense fp32 gradient (channel offset 0, stride = its padded channel count, up to 48)
-    // as its raw input: the same bf16 operands and K order as the plain kernel, so the
-    // same sums; on smaller launches its staging rounds cost more than they save
-    const bool wide = a.w % 32 == 0 && a.h % 8 == 0;
-    const int64_t tiles = (int64_t)batch * (a.h / (wide ? 8 : 16)) * (a.w / (wide ? 32 : 16));
-    if (tiles > 512 && g.co == 0 && g.cs == a.ci_pad && g.cs <= 48 && conv_tiled_fits(a.h, a.w, a.ci_pad)) {
-        ConvArgs t = a;
-        t.x = View{nullptr, 0, 0};
-        t.x2 = View{nullptr, 0, 0};
-        t.c_split = a.ci_pad;
-        t.pool = View{nullptr, 0, 0};
-        t.xin = reinterpret_cast<const float*>(g.base);
-        t.cin_raw = g.cs;
-        if (conv_tiled_offsets_fit(t)) {
-            UHIP(n, launch_conv_tiled(t, true, n->stream));
-            return LB_OK;
-        }
+    a.c_split = a.ci_pad;
+    if (conv_lds_fits(a)) {
+        UHIP(n, launch_conv_lds(a, true, true, n->stream));
+        return LB_OK;
     }
     UHIP(n, launch_conv(a, true, true, n->stream));
     return LB_OK;
@@ -449,77 +427,89 @@ static int check_batch(lb_unet* n, int32_t batch) {
     return LB_OK;
 }
 
-// forward pass into n->out (fp32, out16 channels; for inference n->out_inf, out_cs
-// channels).  Pooling is fused into the
-// second convolution of each encoder level wherever the tiled kernel applies.
-// For inference (train = false) the first convolution also reads the raw input
-// and each decoder convolution reads the coarser level's output at half
-// resolution itself; training materialises the packed input and the
-// concatenated decoder inputs, which the backward pass reads.
-static int forward(lb_unet* n, const float* x, int batch, bool train = true) {
+// A layer's forward convolution where the LDS kernel does not apply.
+static int conv_any(lb_unet* n, const Layer& y, View x, View out, bool out_f32, int batch, bool relu, View pool) {
+    int rc = conv_tiled(n, y, x, out, out_f32, batch, relu, View{nullptr, 0, 0}, 0, pool, nullptr, 0);
+    if (rc != 1) return rc;
+    if ((rc = conv(n, y, x, false, out, out_f32, batch, relu))) return rc;
+    const Level& q = n->lv[y.level];
+    if (pool.base) UHIP(n, launch_avgpool(out, pool, batch, q.h, q.w, y.co, n->stream));
+    return LB_OK;
+}
+
+static int pack_input(lb_unet* n, const float* x, int batch) {
+    UHIP(n, launch_pack_input(x, n->cfg.in_channels, view(n->lv[0].in, 16, 0), 16,
+                              (int64_t)batch * n->cfg.height * n->cfg.width, n->stream));
+    return LB_OK;
+}
+
+// Channel stride of level l's feature buffer.  For inference the decoder convolution reads
+// the coarser level's output at half resolution itself where the LDS kernel applies, so only
+// the level's own channels are stored, densely; training keeps room for the upsampled ones.
+static int cat_stride(const lb_unet* n, int l, int batch, bool train) {
+    const Level& q = n->lv[l];
+    if (train || l == n->L - 1) return q.cat;
+    ConvArgs a{};
+    const Layer& y = n->layers[2 * n->L + (n->L - 2 - l)];
+    a.n = batch;
+    a.h = q.h;
+    a.w = q.w;
+    a.ci_pad = y.ci_pad;
+    a.kpad = y.kpad;
+    return conv_lds_fits(a) ? q.c : q.cat;
+}
+
+// First convolution: for inference from the raw input where the LDS kernel applies,
+// for training from the packed input that the weight gradient reads.
+static int forward_first(lb_unet* n, const float* x, int batch, bool train) {
+    Level& q = n->lv[0];
+    const View none{nullptr, 0, 0}, a1 = view(q.a1, q.c, 0);
+    int rc = 1;
+    if (!train) rc = conv_tiled(n, n->layers[0], none, a1, false, batch, true, none, 0, none, x, n->cfg.in_channels);
+    if (rc != 1) return rc;
+    if ((rc = pack_input(n, x, batch))) return rc;
+    return conv_any(n, n->layers[0], view(q.in, q.cin, 0), a1, false, batch, true, none);
+}
+
+// Everything between the first convolution and the last; pooling is fused into the second
+// convolution of each encoder level.
+static int forward_middle(lb_unet* n, int batch, bool train) {
     const int L = n->L;
-    const int64_t P0 = (int64_t)batch * n->cfg.height * n->cfg.width;
     const View none{nullptr, 0, 0};
     int rc;
-    bool packed = false;
     for (int l = 0; l < L; ++l) {
         Level& q = n->lv[l];
-        const View a1 = view(q.a1, q.c, 0), cat = view(q.cat_buf, q.cat, 0);
-        if (l == 0 && !train) {
-            rc = conv_tiled(n, n->layers[0], none, a1, false, batch, true, none, 0, none, x, n->cfg.in_channels);
-            if (rc < 0) return rc;
-        } else {
-            rc = 1;
-        }
-        if (rc == 1) {
-            if (l == 0 && !packed) {
-                UHIP(n, launch_pack_input(x, n->cfg.in_channels, view(n->lv[0].in, 16, 0), 16, P0, n->stream));
-                packed = true;
-            }
-            rc = conv_tiled(n, n->layers[2 * l], view(q.in, q.cin, 0), a1, false, batch, true, none, 0, none, nullptr, 0);
-            if (rc < 0) return rc;
-            if (rc == 1 && (rc = conv(n, n->layers[2 * l], view(q.in, q.cin, 0), false, a1, false, batch, true)))
-                return rc;
-        }
+        const View a1 = view(q.a1, q.c, 0), cat = view(q.cat_buf, cat_stride(n, l, batch, train), 0);
+        if (l > 0 && (rc = conv_any(n, n->layers[2 * l], view(q.in, q.cin, 0), a1, false, batch, true, none))) return rc;
         const View pool = l < L - 1 ? view(n->lv[l + 1].in, n->lv[l + 1].cin, 0) : none;
-        rc = conv_tiled(n, n->layers[2 * l + 1], a1, cat, false, batch, true, none, 0, pool, nullptr, 0);
-        if (rc < 0) return rc;
-        if (rc == 1) {
-            if ((rc = conv(n, n->layers[2 * l + 1], a1, false, cat, false, batch, true))) return rc;
-            if (l < L - 1) UHIP(n, launch_avgpool(cat, pool, batch, q.h, q.w, q.c, n->stream));
-        }
+        if ((rc = conv_any(n, n->layers[2 * l + 1], a1, cat, false, batch, true, pool))) return rc;
     }
     int li = 2 * L;
     for (int l = L - 2; l >= 0; --l, ++li) {
         Level& q = n->lv[l];
         const Level& r = n->lv[l + 1];
         const View src = l + 1 == L - 1 ? view(r.cat_buf, r.cat, 0) : view(r.d, r.c, 0);
-        const View cat = view(q.cat_buf, q.cat, 0), d = view(q.d, q.c, 0);
+        const View cat = view(q.cat_buf, cat_stride(n, l, batch, train), 0), d = view(q.d, q.c, 0);
         rc = 1;
-        if (!train) {
-            rc = conv_tiled(n, n->layers[li], cat, d, false, batch, true, src, q.c, none, nullptr, 0);
-            if (rc < 0) return rc;
-        }
+        if (!train) rc = conv_tiled(n, n->layers[li], cat, d, false, batch, true, src, q.c, none, nullptr, 0);
         if (rc == 1) {
             UHIP(n, launch_upsample(src, view(q.cat_buf, q.cat, q.c), batch, q.h, q.w, r.c, n->stream));
-            rc = conv_tiled(n, n->layers[li], cat, d, false, batch, true, none, 0, none, nullptr, 0);
-            if (rc < 0) return rc;
-            if (rc == 1 && (rc = conv(n, n->layers[li], cat, false, d, false, batch, true))) return rc;
+            rc = conv_any(n, n->layers[li], cat, d, false, batch, true, none);
         }
+        if (rc) return rc;
     }
-    const Level& q0 = n->lv[0];
-    const View top = L == 1 ? view(q0.cat_buf, q0.cat, 0) : view(q0.d, q0.c, 0);
-    // training keeps 16 channels per pixel (the gradient kernels read 8 at a time); inference
-    // writes out_cs, so that the result leaves as one copy when out_channels is a multiple of 4
-    const View outv = train ? view(n->out, n->out16, 0) : view(n->out_inf, n->out_cs, 0);
-    rc = conv_tiled(n, n->layers[li], top, outv, true, batch, false, none, 0, none, nullptr, 0);
-    if (rc < 0) return rc;
-    if (rc == 1) return conv(n, n->layers[li], top, false, outv, true, batch, false);
     return LB_OK;
 }
 
-// The captured inference pass for `batch` images (reads xin, writes out).
-static int forward_graph(lb_unet* n, int batch, hipGraphExec_t* out) {
+// Last convolution, into `out` (fp32).
+static int forward_last(lb_unet* n, int batch, View out) {
+    const Level& q0 = n->lv[0];
+    const View top = n->L == 1 ? view(q0.cat_buf, q0.cat, 0) : view(q0.d, q0.c, 0);
+    return conv_any(n, n->layers[3 * n->L - 1], top, out, true, batch, false, View{nullptr, 0, 0});
+}
+
+// The captured middle of the inference pass for `batch` images.
+static int middle_graph(lb_unet* n, int batch, hipGraphExec_t* out) {
     if (n->fwd_exec.empty()) {
         n->fwd_exec.assign(n->cfg.max_batch + 1, nullptr);
         n->fwd_graph.assign(n->cfg.max_batch + 1, nullptr);
@@ -532,7 +522,7 @@ static int forward_graph(lb_unet* n, int batch, hipGraphExec_t* out) {
     const hipStream_t own = n->stream;
     UHIP(n, hipStreamBeginCapture(n->cap_stream, hipStreamCaptureModeThreadLocal));
     n->stream = n->cap_stream;
-    const int rc = forward(n, n->xin, batch, false);
+    const int rc = forward_middle(n, batch, false);
     n->stream = own;
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(n->cap_stream, &g);
@@ -551,18 +541,13 @@ int lb_unet_forward(lb_unet* n, const float* x_dev, int32_t batch, float* y_dev)
     int rc = check_batch(n, batch);
     if (rc) return rc;
     UHIP(n, hipSetDevice(n->cfg.device));
-    const int64_t P0 = (int64_t)batch * n->cfg.height * n->cfg.width;
+    // the first and the last layer read and write the caller's arrays, so only the layers
+    // between them, whose buffers do not change, are replayed from a graph
     hipGraphExec_t ge = nullptr;
-    if ((rc = forward_graph(n, batch, &ge))) return rc;
-    UHIP(n, hipMemcpyAsync(n->xin, x_dev, sizeof(float) * P0 * n->cfg.in_channels, hipMemcpyDeviceToDevice,
-                           n->stream));
+    if ((rc = middle_graph(n, batch, &ge))) return rc;
+    if ((rc = forward_first(n, x_dev, batch, false))) return rc;
     UHIP(n, hipGraphLaunch(ge, n->stream));
-    if (n->out_cs == n->cfg.out_channels)
-        UHIP(n, hipMemcpyAsync(y_dev, n->out_inf, sizeof(float) * P0 * n->out_cs, hipMemcpyDeviceToDevice,
-                               n->stream));
-    else
-        UHIP(n, launch_unpack_output(view(n->out_inf, n->out_cs, 0), n->cfg.out_channels, y_dev, P0, n->stream));
-    return LB_OK;
+    return forward_last(n, batch, view(y_dev, n->cfg.out_channels, 0));
 }
 
 static int backward(lb_unet* n, int batch) {
@@ -609,7 +594,10 @@ static int backward(lb_unet* n, int batch) {
 }
 
 static int loss_grad(lb_unet* n, const float* x, const float* target, int batch) {
-    int rc = forward(n, x, batch);
+    int rc = forward_first(n, x, batch, true);
+    if (!rc) rc = forward_middle(n, batch, true);
+    // 16 channels per pixel: the gradient kernels read 8 at a time
+    if (!rc) rc = forward_last(n, batch, view(n->out, n->out16, 0));
     if (rc) return rc;
     const int64_t P0 = (int64_t)batch * n->cfg.height * n->cfg.width;
     const int oc = n->cfg.out_channels;
