@@ -251,34 +251,42 @@ __device__ float block_sum_f32(float v, float* lds) {
     return lds[0];
 }
 
-// Sum over the splits: 64 consecutive (padded) weight entries per workgroup,
-// one per lane; the 4 wavefronts take interleaved splits, each lane with four
-// independent partial sums, then the wavefronts' sums are added in LDS in a
-// fixed order.
-__global__ void __launch_bounds__(256) wgrad_reduce(WgradArgs a) {
-    __shared__ float red[4][64];
+// Sum over the splits: 64 consecutive (padded) entries of the records per
+// workgroup, one per lane; the 16 wavefronts take interleaved splits, each lane
+// with four independent partial sums, then the wavefronts' sums are added in LDS
+// in a fixed order.
+constexpr int kReduceWaves = 16;
+__global__ void __launch_bounds__(64 * kReduceWaves) wgrad_reduce(WgradArgs a) {
+    __shared__ float red[kReduceWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t per_split = (int64_t)a.co_pad16 * 9 * a.ci_pad16;
+    const int64_t weights = (int64_t)a.co_pad16 * 9 * a.ci_pad16;
+    const int64_t record = weights + (a.bias_out ? a.co_pad16 : 0);
     const int64_t e = (int64_t)blockIdx.x * 64 + lane;
     float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    if (e < per_split) {
+    if (e < record) {
         int sp = wave;
-        for (; sp + 12 < a.splits; sp += 16) {
-            s0 += a.partials[(int64_t)sp * per_split + e];
-            s1 += a.partials[(int64_t)(sp + 4) * per_split + e];
-            s2 += a.partials[(int64_t)(sp + 8) * per_split + e];
-            s3 += a.partials[(int64_t)(sp + 12) * per_split + e];
+        for (; sp + 3 * kReduceWaves < a.splits; sp += 4 * kReduceWaves) {
+            s0 += a.partials[(int64_t)sp * record + e];
+            s1 += a.partials[(int64_t)(sp + kReduceWaves) * record + e];
+            s2 += a.partials[(int64_t)(sp + 2 * kReduceWaves) * record + e];
+            s3 += a.partials[(int64_t)(sp + 3 * kReduceWaves) * record + e];
         }
-        for (; sp < a.splits; sp += 4) s0 += a.partials[(int64_t)sp * per_split + e];
+        for (; sp < a.splits; sp += kReduceWaves) s0 += a.partials[(int64_t)sp * record + e];
     }
     red[wave][lane] = (s0 + s1) + (s2 + s3);
     __syncthreads();
-    if (wave == 0 && e < per_split) {
+    if (wave == 0 && e < record) {
+        float s = red[0][lane];
+        for (int w = 1; w < kReduceWaves; ++w) s += red[w][lane];
+        if (e >= weights) {
+            const int o = (int)(e - weights);
+            if (o < a.co) a.bias_out[o] = a.accumulate ? a.bias_out[o] + s : s;
+            return;
+        }
         const int c = (int)(e % a.ci_pad16);
         const int tap = (int)((e / a.ci_pad16) % 9);
         const int o = (int)(e / ((int64_t)9 * a.ci_pad16));
         if (o < a.co && c < a.ci) {
-            const float s = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
             const int64_t i = ((int64_t)o * 9 + tap) * a.ci + c;
             a.out[i] = a.accumulate ? a.out[i] + s : s;
         }
@@ -558,8 +566,13 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
     } else {
         hipLaunchKernelGGL(wgrad_mfma<false>, dim3(tiles, (unsigned)a.splits), dim3(256), 0, s, a);
     }
-    const int64_t entries = (int64_t)a.co_pad16 * 9 * a.ci_pad16;
-    hipLaunchKernelGGL(wgrad_reduce, dim3((unsigned)((entries + 63) / 64)), dim3(256), 0, s, a);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_wgrad_reduce(a, s);
+}
+
+hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t s) {
+    const int64_t entries = (int64_t)a.co_pad16 * 9 * a.ci_pad16 + (a.bias_out ? a.co_pad16 : 0);
+    hipLaunchKernelGGL(wgrad_reduce, dim3((unsigned)((entries + 63) / 64)), dim3(64 * kReduceWaves), 0, s, a);
     return hipGetLastError();
 }
 

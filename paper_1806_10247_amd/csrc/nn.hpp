@@ -67,11 +67,22 @@ struct WgradArgs {
     int32_t splits, chunks_per_wave;  // pixels per wave = 32 * chunks_per_wave
     float* partials;
     float* out;
+    float* bias_out;        // != null: the records end with co_pad16 bias sums, whose totals go here
     int32_t accumulate;
-    FastDiv div_w, div_h;   // set by launch_wgrad
+    FastDiv div_w, div_h;   // set by the launchers
 };
 int32_t wgrad_splits(int64_t pixels, int32_t* chunks_per_wave);
 hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s);
+
+// The same with the pixel tiles transposed in LDS (w a multiple of 16, h of the
+// tile's 8 or 16 rows): partials are [splits] records of [co_pad16][9][ci_pad16]
+// weight sums and [co_pad16] bias sums; launch_wgrad_reduce adds both up.
+// wgrad_lds_splits: workgroups over the pixels, 0 where it does not apply.
+int32_t wgrad_lds_splits(int32_t n, int32_t h, int32_t w, int32_t co_pad16, int32_t ci_pad16);
+bool wgrad_lds_fits(const WgradArgs& a);
+hipError_t launch_wgrad_lds(const WgradArgs& a, hipStream_t s);
+// Ordered sum of the records into out and, with a.bias_out, of their bias sums.
+hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t s);
 
 // Bias gradient db[o] = sum_p g[p][o], o < co; two ordered passes via partials
 // [blocks][co]; `accumulate`: db += sum.

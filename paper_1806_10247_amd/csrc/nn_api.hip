@@ -255,7 +255,10 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
             const int64_t P = B * n->lv[y.level].h * n->lv[y.level].w;
             int32_t cpw = 0;
             const int32_t splits = wgrad_splits(P, &cpw);
-            wmax = std::max(wmax, (int64_t)splits * up_to(y.co, 16) * 9 * up_to(y.ci, 16));
+            const int co = up_to(y.co, 16), ci = up_to(y.ci, 16);
+            wmax = std::max(wmax, (int64_t)splits * co * 9 * ci);
+            wmax = std::max(wmax, wgrad_lds_splits((int32_t)B, n->lv[y.level].h, n->lv[y.level].w, co, ci) *
+                                      ((int64_t)co * 9 * ci + co));
             bmax = std::max(bmax, bias_grad_blocks(P) * (int32_t)y.co);
         }
         n->wpart_n = wmax;
@@ -410,12 +413,20 @@ static int wgrad(lb_unet* n, const Layer& y, View g, View x, int batch) {
     a.ci = y.ci;
     a.co_pad16 = up_to(y.co, 16);
     a.ci_pad16 = up_to(y.ci, 16);
-    a.splits = wgrad_splits(P, &a.chunks_per_wave);
-    if ((int64_t)a.splits * a.co_pad16 * 9 * a.ci_pad16 > n->wpart_n)
-        return ufail(n, LB_EINVAL, "internal: weight-gradient scratch too small");
     a.partials = n->wpart;
     a.out = n->g + y.w_off;
     a.accumulate = 0;
+    a.splits = wgrad_lds_splits(batch, q.h, q.w, a.co_pad16, a.ci_pad16);
+    if (a.splits > 0 && wgrad_lds_fits(a) &&
+        (int64_t)a.splits * ((int64_t)a.co_pad16 * 9 * a.ci_pad16 + a.co_pad16) <= n->wpart_n) {
+        a.bias_out = n->g + y.b_off;
+        UHIP(n, launch_wgrad_lds(a, n->stream));
+        UHIP(n, launch_wgrad_reduce(a, n->stream));
+        return LB_OK;
+    }
+    a.splits = wgrad_splits(P, &a.chunks_per_wave);
+    if ((int64_t)a.splits * a.co_pad16 * 9 * a.ci_pad16 > n->wpart_n)
+        return ufail(n, LB_EINVAL, "internal: weight-gradient scratch too small");
     UHIP(n, launch_wgrad(a, n->stream));
     UHIP(n, launch_bias_grad(g, P, y.co, n->bpart, n->bpart_blocks, n->g + y.b_off, 0, n->stream));
     return LB_OK;
