@@ -251,17 +251,21 @@ __device__ float block_sum_f32(float v, float* lds) {
     return lds[0];
 }
 
-// Sum over the splits: 64 consecutive (padded) entries of the records per
+// Sum over the splits: 64 consecutive (padded) entries of a layer's records per
 // workgroup, one per lane; the 16 wavefronts take interleaved splits, each lane
 // with four independent partial sums, then the wavefronts' sums are added in LDS
-// in a fixed order.
+// in a fixed order.  One launch for all layers: each alone is a few workgroups'
+// latency (18 launches of 4 us).
 constexpr int kReduceWaves = 16;
-__global__ void __launch_bounds__(64 * kReduceWaves) wgrad_reduce(WgradArgs a) {
+__global__ void __launch_bounds__(64 * kReduceWaves) wgrad_reduce(ReduceTable t) {
     __shared__ float red[kReduceWaves][64];
+    int k = 0;
+    while (k + 1 < t.count && (int)blockIdx.x >= t.e[k + 1].first_block) ++k;
+    const ReduceTable::Entry& a = t.e[k];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t weights = (int64_t)a.co_pad16 * 9 * a.ci_pad16;
     const int64_t record = weights + (a.bias_out ? a.co_pad16 : 0);
-    const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t e = (int64_t)((int)blockIdx.x - a.first_block) * 64 + lane;
     float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
     if (e < record) {
         int sp = wave;
@@ -449,18 +453,29 @@ __global__ void pack_input_k(const float* x, int cin, View dst, int cpad, int64_
     }
 }
 
+// One pixel per thread and round; four channels at a time as 16-byte pieces
+// where they are aligned (vec), which a warm start's network has.
 __global__ void __launch_bounds__(256) mse_k(View y, const float* t, int c, int64_t pixels, View grad,
-                                             double* partials, float weight) {
+                                             double* partials, float weight, int vec) {
     __shared__ double red[256];
-    const int64_t total = pixels * c;
-    const float scale = (float)(2.0 * (double)weight / (double)total);
+    const float scale = (float)(2.0 * (double)weight / (double)(pixels * c));
     double s = 0.0;
-    GRID_STRIDE(i, total) {
-        const int ch = (int)(i % c);
-        const int64_t p = i / c;
-        const float d = *at<const float>(y, p, ch) - t[i];
-        *at<float>(grad, p, ch) = scale * d;
-        s += (double)d * (double)d;
+    GRID_STRIDE(p, pixels) {
+        if (vec) {
+            for (int ch = 0; ch < c; ch += 4) {
+                const f32x4 d = *at<const f32x4>(View{y.base, y.cs / 4, 0}, p, ch / 4) -
+                                *reinterpret_cast<const f32x4*>(t + p * c + ch);
+                *at<f32x4>(View{grad.base, grad.cs / 4, 0}, p, ch / 4) = scale * d;
+                s += ((double)d[0] * (double)d[0] + (double)d[1] * (double)d[1]) +
+                     ((double)d[2] * (double)d[2] + (double)d[3] * (double)d[3]);
+            }
+        } else {
+            for (int ch = 0; ch < c; ++ch) {
+                const float d = *at<const float>(y, p, ch) - t[p * c + ch];
+                *at<float>(grad, p, ch) = scale * d;
+                s += (double)d * (double)d;
+            }
+        }
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -496,22 +511,21 @@ __global__ void adam_k(float* p, const float* g, float* m, float* v, int64_t n, 
     }
 }
 
-__global__ void pack_weights_k(const float* w, int co, int ci, bf16_t* fwd, int ci_pad, int kpad, int co_pad32,
-                               bf16_t* bwd, int co_pad16, int kpad_t, int ci_pad32) {
-    const int64_t nf = (int64_t)co_pad32 * kpad, nb = (int64_t)ci_pad32 * kpad_t;
-    GRID_STRIDE(i, nf + nb) {
-        if (i < nf) {
-            const int o = (int)(i / kpad), k = (int)(i % kpad);
-            const int tap = k / ci_pad, c = k % ci_pad;
-            const float val = (o < co && tap < 9 && c < ci) ? w[((int64_t)o * 9 + tap) * ci + c] : 0.0f;
-            fwd[i] = f2bf(val);
-        } else {
-            const int64_t j = i - nf;
-            const int c = (int)(j / kpad_t), k = (int)(j % kpad_t);
-            const int tap = k / co_pad16, o = k % co_pad16;
-            const float val = (c < ci && tap < 9 && o < co) ? w[((int64_t)o * 9 + (8 - tap)) * ci + c] : 0.0f;
-            bwd[j] = f2bf(val);
-        }
+__global__ void __launch_bounds__(256) pack_weights_k(PackTable t) {
+    int k = 0;
+    while (k + 1 < t.count && (int)blockIdx.x >= t.e[k + 1].first_block) ++k;
+    const PackTable::Entry& a = t.e[k];
+    const uint32_t nf = (uint32_t)a.co_pad32 * (uint32_t)a.kpad, nb = (uint32_t)a.ci_pad32 * (uint32_t)a.kpad_t;
+    const uint32_t i = (blockIdx.x - (uint32_t)a.first_block) * 256 + threadIdx.x;
+    if (i < nf) {
+        const int o = (int)(i / (uint32_t)a.kpad), kk = (int)(i % (uint32_t)a.kpad);
+        const int tap = kk / a.ci_pad, c = kk % a.ci_pad;
+        a.fwd[i] = f2bf((o < a.co && tap < 9 && c < a.ci) ? a.w[((int64_t)o * 9 + tap) * a.ci + c] : 0.0f);
+    } else if (i < nf + nb) {
+        const uint32_t j = i - nf;
+        const int c = (int)(j / (uint32_t)a.kpad_t), kk = (int)(j % (uint32_t)a.kpad_t);
+        const int tap = kk / a.co_pad16, o = kk % a.co_pad16;
+        a.bwd[j] = f2bf((c < a.ci && tap < 9 && o < a.co) ? a.w[((int64_t)o * 9 + (8 - tap)) * a.ci + c] : 0.0f);
     }
 }
 
@@ -567,12 +581,25 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
         hipLaunchKernelGGL(wgrad_mfma<false>, dim3(tiles, (unsigned)a.splits), dim3(256), 0, s, a);
     }
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_wgrad_reduce(a, s);
+    if (e != hipSuccess) return e;
+    ReduceTable t{};
+    reduce_entry(&t, a);
+    return launch_wgrad_reduce(t, s);
 }
 
-hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t s) {
-    const int64_t entries = (int64_t)a.co_pad16 * 9 * a.ci_pad16 + (a.bias_out ? a.co_pad16 : 0);
-    hipLaunchKernelGGL(wgrad_reduce, dim3((unsigned)((entries + 63) / 64)), dim3(64 * kReduceWaves), 0, s, a);
+void reduce_entry(ReduceTable* t, const WgradArgs& a) {
+    t->e[t->count++] = {a.partials, a.out, a.bias_out, a.splits, a.co, a.ci, a.co_pad16, a.ci_pad16, a.accumulate, 0};
+}
+
+hipError_t launch_wgrad_reduce(const ReduceTable& table, hipStream_t s) {
+    ReduceTable t = table;
+    int64_t blocks = 0;
+    for (int k = 0; k < t.count; ++k) {
+        t.e[k].first_block = (int32_t)blocks;
+        blocks += ((int64_t)t.e[k].co_pad16 * 9 * t.e[k].ci_pad16 + (t.e[k].bias_out ? t.e[k].co_pad16 : 0) + 63) / 64;
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(wgrad_reduce, dim3((unsigned)blocks), dim3(64 * kReduceWaves), 0, s, t);
     return hipGetLastError();
 }
 
@@ -626,7 +653,8 @@ hipError_t launch_pack_input(const float* x, int32_t cin, View dst, int32_t cpad
 
 hipError_t launch_mse(View y, const float* t, int32_t c, int64_t pixels, View grad, double* partials, int32_t blocks,
                       float weight, hipStream_t s) {
-    hipLaunchKernelGGL(mse_k, dim3((unsigned)blocks), dim3(256), 0, s, y, t, c, pixels, grad, partials, weight);
+    const int vec = c % 4 == 0 && y.cs % 4 == 0 && y.co == 0 && grad.cs % 4 == 0 && grad.co == 0 && ((uintptr_t)t & 15) == 0;
+    hipLaunchKernelGGL(mse_k, dim3((unsigned)blocks), dim3(256), 0, s, y, t, c, pixels, grad, partials, weight, vec);
     return hipGetLastError();
 }
 
@@ -654,12 +682,15 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, 
     return hipGetLastError();
 }
 
-hipError_t launch_pack_weights(const float* w, int32_t co, int32_t ci, bf16_t* fwd, int32_t ci_pad, int32_t kpad,
-                               int32_t co_pad32, bf16_t* bwd, int32_t co_pad16, int32_t kpad_t, int32_t ci_pad32,
-                               hipStream_t s) {
-    const int64_t total = (int64_t)co_pad32 * kpad + (int64_t)ci_pad32 * kpad_t;
-    hipLaunchKernelGGL(pack_weights_k, dim3(grid_for(total)), dim3(256), 0, s, w, co, ci, fwd, ci_pad, kpad, co_pad32,
-                       bwd, co_pad16, kpad_t, ci_pad32);
+hipError_t launch_pack_weights(const PackTable& table, hipStream_t s) {
+    PackTable t = table;
+    int64_t blocks = 0;
+    for (int k = 0; k < t.count; ++k) {
+        const PackTable::Entry& e = t.e[k];
+        t.e[k].first_block = (int32_t)blocks;
+        blocks += ((int64_t)e.co_pad32 * e.kpad + (int64_t)e.ci_pad32 * e.kpad_t + 255) / 256;
+    }
+    hipLaunchKernelGGL(pack_weights_k, dim3((unsigned)blocks), dim3(256), 0, s, t);
     return hipGetLastError();
 }
 

@@ -41,7 +41,14 @@ struct ConvArgs {
     const float* xin;   // != null: the input is this raw fp32 [pixels][cin_raw] array, 16-byte aligned (zeros
                         // past cin_raw <= 16, ci_pad 16)
     int32_t cin_raw;
+    View pack;          // base != null (raw input): the packed bf16 pixels (16 channels) are also written here
     View mask;          // base != null (fp32 output): results where this bf16 view is not > 0 are set to 0
+    View sum;           // base != null (fp32 output): channels from sum_from on are not written to y; their
+    int32_t sum_from;   // 2x2 sums (the adjoint of the upsampling) go here at half resolution, channel 0 for
+    View sum_mask;      // sum_from, set to 0 where this bf16 view is not > 0 (if its base != null)
+    View add;           // base != null (fp32 output): nothing is written to y; a quarter of each result is added
+    View add_mask;      // to its 2x2 pixels here at double resolution (the adjoint of the pooling), and the sum
+                        // set to 0 where this bf16 view is not > 0 (if its base != null)
     // set by the launchers
     int32_t y_vec;      // fp32 output: 16-byte stores are aligned
     FastDiv div_w, div_h, div_raw, div_cin;
@@ -65,6 +72,8 @@ struct WgradArgs {
     int32_t n, h, w;
     int32_t co, ci, co_pad16, ci_pad16;
     int32_t splits, chunks_per_wave;  // pixels per wave = 32 * chunks_per_wave
+    View x2;                // base != null (wgrad_lds): input channels from c_split on come from this view at
+    int32_t c_split;        // half resolution, those before from x; c_split = ci_pad16 without x2
     float* partials;
     float* out;
     float* bias_out;        // != null: the records end with co_pad16 bias sums, whose totals go here
@@ -81,8 +90,20 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s);
 int32_t wgrad_lds_splits(int32_t n, int32_t h, int32_t w, int32_t co_pad16, int32_t ci_pad16);
 bool wgrad_lds_fits(const WgradArgs& a);
 hipError_t launch_wgrad_lds(const WgradArgs& a, hipStream_t s);
-// Ordered sum of the records into out and, with a.bias_out, of their bias sums.
-hipError_t launch_wgrad_reduce(const WgradArgs& a, hipStream_t s);
+// Ordered sums of the records of several layers into their out and bias_out, one launch.
+constexpr int kMaxLayers = 18;
+struct ReduceTable {
+    struct Entry {
+        const float* partials;
+        float* out;
+        float* bias_out;   // null: the records hold no bias sums
+        int32_t splits, co, ci, co_pad16, ci_pad16, accumulate;
+        int32_t first_block;   // set by launch_wgrad_reduce
+    } e[kMaxLayers];
+    int32_t count;
+};
+void reduce_entry(ReduceTable* t, const WgradArgs& a);
+hipError_t launch_wgrad_reduce(const ReduceTable& t, hipStream_t s);
 
 // Bias gradient db[o] = sum_p g[p][o], o < co; two ordered passes via partials
 // [blocks][co]; `accumulate`: db += sum.
@@ -115,12 +136,19 @@ hipError_t launch_unpool_f32(View src, View dst, int32_t n, int32_t h, int32_t w
 // Adam on a flat fp32 vector (bias correction factors given by the host).
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float beta1, float beta2,
                        float eps, float c1, float c2, hipStream_t s);
-// Weight packing from the fp32 parameter layout w[co][3][3][ci]:
+// Weight packing of every layer from the fp32 parameter layout w[co][3][3][ci]:
 // forward layout (see ConvArgs) and the input-gradient layout
 // wt_t[c][k'] with k' = tap'*co_pad16 + o holding w[o][8 - tap'][c].
-hipError_t launch_pack_weights(const float* w, int32_t co, int32_t ci, bf16_t* fwd, int32_t ci_pad, int32_t kpad,
-                               int32_t co_pad32, bf16_t* bwd, int32_t co_pad16, int32_t kpad_t, int32_t ci_pad32,
-                               hipStream_t s);
+struct PackTable {
+    struct Entry {
+        const float* w;
+        bf16_t *fwd, *bwd;
+        int32_t co, ci, ci_pad, kpad, co_pad32, co_pad16, kpad_t, ci_pad32;
+        int32_t first_block;   // set by launch_pack_weights
+    } e[kMaxLayers];
+    int32_t count;
+};
+hipError_t launch_pack_weights(const PackTable& t, hipStream_t s);
 // Ordered sum of doubles (single block).
 hipError_t launch_sum(const double* in, int32_t n, double* out, hipStream_t s);
 

@@ -44,19 +44,23 @@ struct lb_unet {
     lb_unet_config cfg{};
     hipStream_t stream = nullptr;
     int L = 0, out16 = 0;
+    int out_cs = 0;   // channel stride of the training output: out_channels rounded up to 4
     std::vector<Layer> layers;
     std::vector<Level> lv;
     int64_t np = 0;
     float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
     float *out = nullptr, *g_out = nullptr;
-    float* wpart = nullptr;
+    float* wpart = nullptr;                  // weight-gradient partial sums of one layer (wgrad_mfma)
     int64_t wpart_n = 0;
+    std::vector<float*> lpart;               // per layer (wgrad_lds), summed together at the end
+    std::vector<int64_t> lpart_n;
+    ReduceTable reduce{};
     float* bpart = nullptr;
     int32_t bpart_blocks = 0;
     double* mse_part = nullptr;
     double* loss_dev = nullptr;
     double* loss_host = nullptr;
-    int32_t mse_blocks = 512;
+    int32_t mse_blocks = 2048;
     int64_t t = 0;  // Adam steps taken
     // low-pass loss term: weight * MSE of the (2^lp x 2^lp)-block means
     int32_t lp_levels = 0;
@@ -147,9 +151,10 @@ double lb_unet_macs_per_image(const lb_unet* n) {
 }
 
 static int pack_all(lb_unet* n) {
+    PackTable t{};
     for (const Layer& l : n->layers)
-        UHIP(n, launch_pack_weights(n->p + l.w_off, l.co, l.ci, l.wf, l.ci_pad, l.kpad, l.co_pad32, l.wb, l.co_pad16,
-                                    l.kpad_t, l.ci_pad32, n->stream));
+        t.e[t.count++] = {n->p + l.w_off, l.wf, l.wb, l.co, l.ci, l.ci_pad, l.kpad, l.co_pad32, l.co_pad16, l.kpad_t, l.ci_pad32, 0};
+    UHIP(n, launch_pack_weights(t, n->stream));
     return LB_OK;
 }
 
@@ -179,6 +184,7 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
     n->stream = (hipStream_t)cfg->stream;
     n->L = L;
     n->out16 = 16;
+    n->out_cs = (cfg->out_channels + 3) / 4 * 4;
     n->lv.resize(L);
     for (int l = 0; l < L; ++l) {
         Level& q = n->lv[l];
@@ -247,7 +253,7 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
     }
     {
         const int64_t P0 = B * cfg->height * cfg->width;
-        UALLOC(n->out, P0 * n->out16);
+        UALLOC(n->out, P0 * n->out_cs);
         UALLOC(n->g_out, P0 * n->out16);
         int64_t wmax = 0;
         int32_t bmax = 0;
@@ -256,11 +262,15 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
             int32_t cpw = 0;
             const int32_t splits = wgrad_splits(P, &cpw);
             const int co = up_to(y.co, 16), ci = up_to(y.ci, 16);
-            wmax = std::max(wmax, (int64_t)splits * co * 9 * ci);
-            wmax = std::max(wmax, wgrad_lds_splits((int32_t)B, n->lv[y.level].h, n->lv[y.level].w, co, ci) *
-                                      ((int64_t)co * 9 * ci + co));
+            const int64_t ls = wgrad_lds_splits((int32_t)B, n->lv[y.level].h, n->lv[y.level].w, co, ci);
+            // the general path's scratch only where the LDS path may not apply (its offsets are 32-bit)
+            if (ls == 0 || P * (int64_t)(512 * 4) >= ((int64_t)1 << 32)) wmax = std::max(wmax, (int64_t)splits * co * 9 * ci);
+            n->lpart.push_back(nullptr);
+            n->lpart_n.push_back(ls * ((int64_t)co * 9 * ci + co));
             bmax = std::max(bmax, bias_grad_blocks(P) * (int32_t)y.co);
         }
+        for (size_t k = 0; k < n->lpart.size(); ++k)
+            if (n->lpart_n[k]) UALLOC(n->lpart[k], n->lpart_n[k]);
         n->wpart_n = wmax;
         UALLOC(n->wpart, wmax);
         n->bpart_blocks = 4096;
@@ -327,7 +337,7 @@ int lb_unet_get_params(lb_unet* n, float* params_host) {
 // c_split on, pool = 2 x 2 means of the output, xin = raw fp32 input with
 // cin_raw channels); returns 1 without launching when it does not apply.
 static int conv_tiled(lb_unet* n, const Layer& y, View x, View out, bool out_f32, int batch, bool relu, View x2,
-                      int c_split, View pool, const float* xin, int cin_raw) {
+                      int c_split, View pool, const float* xin, int cin_raw, View pack = View{nullptr, 0, 0}) {
     const Level& q = n->lv[y.level];
     ConvArgs a{};
     a.x = x;
@@ -348,6 +358,7 @@ static int conv_tiled(lb_unet* n, const Layer& y, View x, View out, bool out_f32
     a.pool = pool;
     a.xin = xin;
     a.cin_raw = cin_raw;
+    a.pack = pack;
     if (!conv_lds_fits(a) || (xin && ((uintptr_t)xin & 15))) return 1;
     UHIP(n, launch_conv_lds(a, false, out_f32, n->stream));
     return LB_OK;
@@ -373,14 +384,13 @@ static int conv(lb_unet* n, const Layer& y, View x, bool x_f32, View out, bool o
     return LB_OK;
 }
 
-// input gradient of layer y: dx (fp32 view, y.ci channels) = conv(g, flipped W^T)
-static int dgrad(lb_unet* n, const Layer& y, View g, View dx, int batch) {
+// Arguments of layer y's input gradient: dx (fp32 view, y.ci channels) = conv(g, flipped W^T)
+static ConvArgs dgrad_args(lb_unet* n, const Layer& y, View g, View dx, int batch) {
     const Level& q = n->lv[y.level];
     ConvArgs a{};
     a.x = g;
     a.y = dx;
     a.wt = y.wb;
-    a.bias = nullptr;
     a.n = batch;
     a.h = q.h;
     a.w = q.w;
@@ -388,21 +398,26 @@ static int dgrad(lb_unet* n, const Layer& y, View g, View dx, int batch) {
     a.kpad = y.kpad_t;
     a.co = y.ci;
     a.co_pad32 = y.ci_pad32;
-    a.relu = 0;
-    a.accumulate = 0;
     a.c_split = a.ci_pad;
+    return a;
+}
+
+// input gradient of layer y into dx, set to 0 where the activation `act` of that input is not > 0
+static int dgrad(lb_unet* n, const Layer& y, View g, View dx, View act, int batch) {
+    ConvArgs a = dgrad_args(n, y, g, dx, batch);
+    a.mask = act;
     if (conv_lds_fits(a)) {
         UHIP(n, launch_conv_lds(a, true, true, n->stream));
         return LB_OK;
     }
     UHIP(n, launch_conv(a, true, true, n->stream));
+    if (act.base) UHIP(n, launch_relu_mask(dx, act, (int64_t)batch * a.h * a.w, y.ci, n->stream));
     return LB_OK;
 }
 
-// weight and bias gradients of layer y from its output gradient g (fp32) and input x (bf16)
-static int wgrad(lb_unet* n, const Layer& y, View g, View x, int batch) {
+static WgradArgs wgrad_args(lb_unet* n, int layer, View g, View x, View x2, int c_split, int batch) {
+    const Layer& y = n->layers[layer];
     const Level& q = n->lv[y.level];
-    const int64_t P = (int64_t)batch * q.h * q.w;
     WgradArgs a{};
     a.g = g;
     a.x = x;
@@ -413,20 +428,36 @@ static int wgrad(lb_unet* n, const Layer& y, View g, View x, int batch) {
     a.ci = y.ci;
     a.co_pad16 = up_to(y.co, 16);
     a.ci_pad16 = up_to(y.ci, 16);
-    a.partials = n->wpart;
+    a.x2 = x2;
+    a.c_split = x2.base ? c_split : a.ci_pad16;
     a.out = n->g + y.w_off;
-    a.accumulate = 0;
+    a.bias_out = n->g + y.b_off;
+    a.partials = n->lpart[layer];
     a.splits = wgrad_lds_splits(batch, q.h, q.w, a.co_pad16, a.ci_pad16);
-    if (a.splits > 0 && wgrad_lds_fits(a) &&
-        (int64_t)a.splits * ((int64_t)a.co_pad16 * 9 * a.ci_pad16 + a.co_pad16) <= n->wpart_n) {
-        a.bias_out = n->g + y.b_off;
+    return a;
+}
+
+static bool wgrad_lds_applies(const lb_unet* n, int layer, const WgradArgs& a) {
+    return a.splits > 0 && wgrad_lds_fits(a) &&
+           (int64_t)a.splits * ((int64_t)a.co_pad16 * 9 * a.ci_pad16 + a.co_pad16) <= n->lpart_n[layer];
+}
+
+// weight and bias gradients of a layer from its output gradient g (fp32) and input x (bf16;
+// channels from c_split on from x2 at half resolution, if given: the LDS kernel only)
+static int wgrad(lb_unet* n, int layer, View g, View x, int batch, View x2 = View{nullptr, 0, 0}, int c_split = 0) {
+    const Layer& y = n->layers[layer];
+    WgradArgs a = wgrad_args(n, layer, g, x, x2, c_split, batch);
+    if (wgrad_lds_applies(n, layer, a)) {
         UHIP(n, launch_wgrad_lds(a, n->stream));
-        UHIP(n, launch_wgrad_reduce(a, n->stream));
+        reduce_entry(&n->reduce, a);
         return LB_OK;
     }
+    const int64_t P = (int64_t)batch * a.h * a.w;
+    a.bias_out = nullptr;
     a.splits = wgrad_splits(P, &a.chunks_per_wave);
-    if ((int64_t)a.splits * a.co_pad16 * 9 * a.ci_pad16 > n->wpart_n)
+    if (x2.base || (int64_t)a.splits * a.co_pad16 * 9 * a.ci_pad16 > n->wpart_n)
         return ufail(n, LB_EINVAL, "internal: weight-gradient scratch too small");
+    a.partials = n->wpart;
     UHIP(n, launch_wgrad(a, n->stream));
     UHIP(n, launch_bias_grad(g, P, y.co, n->bpart, n->bpart_blocks, n->g + y.b_off, 0, n->stream));
     return LB_OK;
@@ -454,29 +485,39 @@ static int pack_input(lb_unet* n, const float* x, int batch) {
     return LB_OK;
 }
 
-// Channel stride of level l's feature buffer.  For inference the decoder convolution reads
-// the coarser level's output at half resolution itself where the LDS kernel applies, so only
-// the level's own channels are stored, densely; training keeps room for the upsampled ones.
-static int cat_stride(const lb_unet* n, int l, int batch, bool train) {
-    const Level& q = n->lv[l];
-    if (train || l == n->L - 1) return q.cat;
+static Layer& decoder_layer(lb_unet* n, int l) { return n->layers[2 * n->L + (n->L - 2 - l)]; }
+
+// Whether level l's decoder convolution reads the coarser level's output at half resolution
+// itself, and (training) its gradients are taken the same way: then only the level's own
+// channels are stored, densely.  Otherwise the upsampled channels are stored beside them.
+static bool half_res(lb_unet* n, int l, int batch, bool train) {
+    if (l == n->L - 1) return false;
+    const Level &q = n->lv[l], &r = n->lv[l + 1];
+    const Layer& y = decoder_layer(n, l);
     ConvArgs a{};
-    const Layer& y = n->layers[2 * n->L + (n->L - 2 - l)];
     a.n = batch;
     a.h = q.h;
     a.w = q.w;
     a.ci_pad = y.ci_pad;
     a.kpad = y.kpad;
-    return conv_lds_fits(a) ? q.c : q.cat;
+    if (!conv_lds_fits(a)) return false;
+    if (!train) return true;
+    const int layer = (int)(&y - n->layers.data());
+    return conv_lds_fits(dgrad_args(n, y, view(nullptr, q.c, 0), view(nullptr, q.c, 0), batch)) &&
+           wgrad_lds_applies(n, layer, wgrad_args(n, layer, view(nullptr, q.c, 0), view(nullptr, q.c, 0),
+                                                  view(q.in, r.c, 0), q.c, batch));
+}
+static int cat_stride(lb_unet* n, int l, int batch, bool train) {
+    return half_res(n, l, batch, train) ? n->lv[l].c : n->lv[l].cat;
 }
 
-// First convolution: for inference from the raw input where the LDS kernel applies,
-// for training from the packed input that the weight gradient reads.
+// First convolution, from the raw input where the LDS kernel applies; training also keeps
+// the packed input, which the weight gradient reads.
 static int forward_first(lb_unet* n, const float* x, int batch, bool train) {
     Level& q = n->lv[0];
     const View none{nullptr, 0, 0}, a1 = view(q.a1, q.c, 0);
-    int rc = 1;
-    if (!train) rc = conv_tiled(n, n->layers[0], none, a1, false, batch, true, none, 0, none, x, n->cfg.in_channels);
+    int rc = conv_tiled(n, n->layers[0], none, a1, false, batch, true, none, 0, none, x, n->cfg.in_channels,
+                        train ? view(q.in, q.cin, 0) : none);
     if (rc != 1) return rc;
     if ((rc = pack_input(n, x, batch))) return rc;
     return conv_any(n, n->layers[0], view(q.in, q.cin, 0), a1, false, batch, true, none);
@@ -501,9 +542,9 @@ static int forward_middle(lb_unet* n, int batch, bool train) {
         const Level& r = n->lv[l + 1];
         const View src = l + 1 == L - 1 ? view(r.cat_buf, r.cat, 0) : view(r.d, r.c, 0);
         const View cat = view(q.cat_buf, cat_stride(n, l, batch, train), 0), d = view(q.d, q.c, 0);
-        rc = 1;
-        if (!train) rc = conv_tiled(n, n->layers[li], cat, d, false, batch, true, src, q.c, none, nullptr, 0);
-        if (rc == 1) {
+        if (half_res(n, l, batch, train)) {
+            rc = conv_tiled(n, n->layers[li], cat, d, false, batch, true, src, q.c, none, nullptr, 0);
+        } else {
             UHIP(n, launch_upsample(src, view(q.cat_buf, q.cat, q.c), batch, q.h, q.w, r.c, n->stream));
             rc = conv_any(n, n->layers[li], cat, d, false, batch, true, none);
         }
@@ -561,64 +602,85 @@ int lb_unet_forward(lb_unet* n, const float* x_dev, int32_t batch, float* y_dev)
     return forward_last(n, batch, view(y_dev, n->cfg.out_channels, 0));
 }
 
+// Gradients of every parameter from the output gradient.  Each input gradient is masked by
+// the activation it belongs to as it is written.
 static int backward(lb_unet* n, int batch) {
     const int L = n->L;
+    const View none{nullptr, 0, 0};
     int rc;
+    n->reduce.count = 0;
     // output layer
-    const Layer& last = n->layers[3 * L - 1];
     Level& q0 = n->lv[0];
     const View top = L == 1 ? view(q0.cat_buf, q0.cat, 0) : view(q0.d, q0.c, 0);
     const View gtop = L == 1 ? view(q0.g_cat, q0.cat, 0) : view(q0.g_d, q0.c, 0);
     const View gout = view(n->g_out, n->out16, 0);
-    if ((rc = wgrad(n, last, gout, top, batch))) return rc;
-    if ((rc = dgrad(n, last, gout, gtop, batch))) return rc;
+    if ((rc = wgrad(n, 3 * L - 1, gout, top, batch))) return rc;
+    if ((rc = dgrad(n, n->layers[3 * L - 1], gout, gtop, top, batch))) return rc;
     // decoder, level 0 upwards (reverse of the forward order)
     for (int l = 0; l <= L - 2; ++l) {
         Level& q = n->lv[l];
         const Level& r = n->lv[l + 1];
-        const Layer& y = n->layers[2 * L + (L - 2 - l)];
-        const int64_t P = (int64_t)batch * q.h * q.w;
-        UHIP(n, launch_relu_mask(view(q.g_d, q.c, 0), view(q.d, q.c, 0), P, q.c, n->stream));
-        if ((rc = wgrad(n, y, view(q.g_d, q.c, 0), view(q.cat_buf, q.cat, 0), batch))) return rc;
-        if ((rc = dgrad(n, y, view(q.g_d, q.c, 0), view(q.g_cat, q.cat, 0), batch))) return rc;
+        const int layer = 2 * L + (L - 2 - l);
+        const int cs = cat_stride(n, l, batch, true);
+        const View cat = view(q.cat_buf, cs, 0), gcat = view(q.g_cat, cs, 0), gd = view(q.g_d, q.c, 0);
+        const View src = l + 1 == L - 1 ? view(r.cat_buf, r.cat, 0) : view(r.d, r.c, 0);
         const View dst = l + 1 == L - 1 ? view(r.g_cat, r.cat, 0) : view(r.g_d, r.c, 0);
-        UHIP(n, launch_upsample_bwd(view(q.g_cat, q.cat, q.c), dst, batch, q.h, q.w, r.c, n->stream));
+        if (half_res(n, l, batch, true)) {
+            if ((rc = wgrad(n, layer, gd, cat, batch, src, q.c))) return rc;
+            ConvArgs a = dgrad_args(n, n->layers[layer], gd, gcat, batch);
+            a.sum = dst;
+            a.sum_from = q.c;
+            a.sum_mask = src;
+            UHIP(n, launch_conv_lds(a, true, true, n->stream));
+        } else {
+            if ((rc = wgrad(n, layer, gd, cat, batch))) return rc;
+            if ((rc = dgrad(n, n->layers[layer], gd, gcat, none, batch))) return rc;
+            UHIP(n, launch_upsample_bwd(view(q.g_cat, q.cat, q.c), dst, batch, q.h, q.w, r.c, n->stream));
+            UHIP(n, launch_relu_mask(dst, src, (int64_t)batch * r.h * r.w, r.c, n->stream));
+        }
     }
     // encoder, bottom level first
     for (int l = L - 1; l >= 0; --l) {
         Level& q = n->lv[l];
-        const int64_t P = (int64_t)batch * q.h * q.w;
-        const View g2 = view(q.g_cat, q.cat, 0);
-        UHIP(n, launch_relu_mask(g2, view(q.cat_buf, q.cat, 0), P, q.c, n->stream));
-        if ((rc = wgrad(n, n->layers[2 * l + 1], g2, view(q.a1, q.c, 0), batch))) return rc;
-        if ((rc = dgrad(n, n->layers[2 * l + 1], g2, view(q.g_a1, q.c, 0), batch))) return rc;
-        UHIP(n, launch_relu_mask(view(q.g_a1, q.c, 0), view(q.a1, q.c, 0), P, q.c, n->stream));
-        if ((rc = wgrad(n, n->layers[2 * l], view(q.g_a1, q.c, 0), view(q.in, q.cin, 0), batch))) return rc;
+        const View g2 = view(q.g_cat, cat_stride(n, l, batch, true), 0), a1 = view(q.a1, q.c, 0), ga1 = view(q.g_a1, q.c, 0);
+        if ((rc = wgrad(n, 2 * l + 1, g2, a1, batch))) return rc;
+        if ((rc = dgrad(n, n->layers[2 * l + 1], g2, ga1, a1, batch))) return rc;
+        if ((rc = wgrad(n, 2 * l, ga1, view(q.in, q.cin, 0), batch))) return rc;
         if (l > 0) {
+            // through the pooling into the finer level's features, whose gradient is then complete
             Level& u = n->lv[l - 1];
-            if ((rc = dgrad(n, n->layers[2 * l], view(q.g_a1, q.c, 0), view(q.g_in, q.cin, 0), batch))) return rc;
-            UHIP(n, launch_avgpool_bwd(view(q.g_in, q.cin, 0), view(u.g_cat, u.cat, 0), batch, u.h, u.w, u.c,
-                                       n->stream));
+            const int cs = cat_stride(n, l - 1, batch, true);
+            const View gfine = view(u.g_cat, cs, 0), fine = view(u.cat_buf, cs, 0);
+            ConvArgs a = dgrad_args(n, n->layers[2 * l], ga1, view(q.g_in, q.cin, 0), batch);
+            if (conv_lds_fits(a)) {
+                a.add = gfine;
+                a.add_mask = fine;
+                UHIP(n, launch_conv_lds(a, true, true, n->stream));
+            } else {
+                UHIP(n, launch_conv(a, true, true, n->stream));
+                UHIP(n, launch_avgpool_bwd(a.y, gfine, batch, u.h, u.w, u.c, n->stream));
+                UHIP(n, launch_relu_mask(gfine, fine, (int64_t)batch * u.h * u.w, u.c, n->stream));
+            }
         }
     }
+    UHIP(n, launch_wgrad_reduce(n->reduce, n->stream));
     return LB_OK;
 }
 
 static int loss_grad(lb_unet* n, const float* x, const float* target, int batch) {
     int rc = forward_first(n, x, batch, true);
     if (!rc) rc = forward_middle(n, batch, true);
-    // 16 channels per pixel: the gradient kernels read 8 at a time
-    if (!rc) rc = forward_last(n, batch, view(n->out, n->out16, 0));
+    if (!rc) rc = forward_last(n, batch, view(n->out, n->out_cs, 0));
     if (rc) return rc;
     const int64_t P0 = (int64_t)batch * n->cfg.height * n->cfg.width;
     const int oc = n->cfg.out_channels;
-    UHIP(n, launch_mse(view(n->out, n->out16, 0), target, oc, P0, view(n->g_out, n->out16, 0), n->mse_part,
+    UHIP(n, launch_mse(view(n->out, n->out_cs, 0), target, oc, P0, view(n->g_out, n->out16, 0), n->mse_part,
                        n->mse_blocks, 1.0f, n->stream));
     UHIP(n, launch_sum(n->mse_part, n->mse_blocks, n->loss_dev, n->stream));
     if (n->lp_levels > 0 && n->lp_weight > 0.0f) {
         // block means of output and target, their weighted MSE, and its gradient
         // carried back to the full grid and added to the output gradient
-        View ys = view(n->out, n->out16, 0), ts = view((void*)target, oc, 0);
+        View ys = view(n->out, n->out_cs, 0), ts = view((void*)target, oc, 0);
         for (int l = 1; l <= n->lp_levels; ++l) {
             const int h = n->cfg.height >> (l - 1), w = n->cfg.width >> (l - 1);
             const View yd = view(n->lp_y[l - 1], n->out16, 0), td = view(n->lp_t[l - 1], oc, 0);

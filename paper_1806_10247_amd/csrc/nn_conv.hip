@@ -7,8 +7,10 @@
 // pixels hit distinct banks).  A wavefront owns T matrix-core tiles of 16
 // consecutive pixels.  The products are D = W X: the rows of D are output
 // channels, its columns pixels, so that a lane ends with four consecutive
-// channels of one pixel and the epilogue (bias, ReLU, 2 x 2 mean, or the ReLU
-// mask of the gradient) works on them as one 8- or 16-byte piece.
+// channels of one pixel and the epilogue works on them as one 8- or 16-byte
+// piece: bias, ReLU and the 2 x 2 means forward; the ReLU mask of the next
+// gradient and the adjoints of the upsampling (2 x 2 sums) and of the pooling (a
+// quarter added to four pixels) backward.
 //
 // Everything but the tensors' sizes is a template argument (channels CI, tile,
 // input and output kind), so that the K loop is straight code: K runs over
@@ -54,6 +56,18 @@ __device__ __forceinline__ int wrap(int v, int n) { return v < 0 ? v + n : (v >=
 
 __device__ __forceinline__ float shuffle_x1(float v) {   // the value of lane ^ 1
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));
+}
+
+// v with 0 where channels c .. c + 3 of pixel px of the bf16 view m are not > 0.
+__device__ __forceinline__ f32x4 masked(f32x4 v, const View& m, size_t px, int c) {
+    if (m.base) {
+        const bf16x4 a = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const bf16_t*>(m.base) +
+                                                          px * (uint32_t)m.cs + (uint32_t)(m.co + c));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (!((float)a[j] > 0.0f)) v[j] = 0.0f;
+    }
+    return v;
 }
 
 enum Input { kBf16 = 0, kF32 = 1, kRaw = 2 };
@@ -120,7 +134,7 @@ struct Staged {
             }
         }
     }
-    __device__ __forceinline__ void store(const ConvArgs&, bf16_t* tile) {
+    __device__ __forceinline__ void store(const ConvArgs&, bf16_t* tile, uint32_t, int, int) {
 #pragma unroll
         for (int r = 0; r < N; ++r) {
             const uint32_t e = r * 256 + threadIdx.x;
@@ -174,7 +188,7 @@ struct Staged<16, TW, T, kRaw> {
             }
         }
     }
-    __device__ __forceinline__ void store(const ConvArgs& a, bf16_t* tile) {
+    __device__ __forceinline__ void store(const ConvArgs& a, bf16_t* tile, uint32_t img_row, int y0, int x0) {
         const uint32_t cr = (uint32_t)a.cin_raw, inner_n = G::HH * (TW / 4) * cr;
         float* inner = reinterpret_cast<float*>(tile + G::NP * G::PS);   // [HH][TW * cr]
         float* edge = inner + G::HH * TW * cr;                           // [HH][2][cr]
@@ -201,6 +215,12 @@ struct Staged<16, TW, T, kRaw> {
             }
             *reinterpret_cast<bf16x8*>(tile + q * G::PS) = lo;
             *reinterpret_cast<bf16x8*>(tile + q * G::PS + 8) = hi;
+            if (a.pack.base && blockIdx.y == 0 && qx >= 1 && qx <= (uint32_t)TW && qy >= 1 && qy <= (uint32_t)G::TH) {
+                const size_t px = (size_t)(img_row + (uint32_t)y0 + qy - 1) * (uint32_t)a.w + (uint32_t)x0 + qx - 1;
+                bf16_t* to = reinterpret_cast<bf16_t*>(a.pack.base) + px * (uint32_t)a.pack.cs + (uint32_t)a.pack.co;
+                *reinterpret_cast<bf16x8*>(to) = lo;
+                *reinterpret_cast<bf16x8*>(to + 8) = hi;
+            }
         }
     }
 };
@@ -208,7 +228,7 @@ struct Staged<16, TW, T, kRaw> {
 template <int CI, int TW, int T, int XM, bool YF32, int NU, int PF>
 __global__ void __launch_bounds__(256) conv3x3_lds(ConvArgs a) {
     using G = Tile<CI, TW, T>;
-    static_assert(T % G::TPR == 0, "whole pixel rows per wavefront");
+    static_assert(T % G::TPR == 0 && G::R % 2 == 0, "whole pairs of pixel rows per wavefront");
     extern __shared__ __align__(16) unsigned char lds_raw[];
     bf16_t* tile = reinterpret_cast<bf16_t*>(lds_raw);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, col = lane & 15;
@@ -232,7 +252,7 @@ __global__ void __launch_bounds__(256) conv3x3_lds(ConvArgs a) {
     Staged<CI, TW, T, XM> staged;
     staged.load(a, img_row, y0, x0);
     unrolled<(PF < G::S ? PF : G::S)>(load_weights);
-    staged.store(a, tile);
+    staged.store(a, tile, img_row, y0, x0);
     __syncthreads();
 
     // ---- products
@@ -286,20 +306,26 @@ __global__ void __launch_bounds__(256) conv3x3_lds(ConvArgs a) {
                 if (a.relu) v[t][j] = fmaxf(v[t][j], 0.0f);
             }
             if constexpr (YF32) {
-                if (a.mask.base) {
-                    const bf16x4 m = *reinterpret_cast<const bf16x4*>(
-                        reinterpret_cast<const bf16_t*>(a.mask.base) + px * (uint32_t)a.mask.cs + (uint32_t)(a.mask.co + o));
+                if (a.add.base) {
+                    const uint32_t fw = 2 * (uint32_t)a.w;   // the finer level's width
+                    const size_t fine = (size_t)(2 * row) * fw + 2 * (uint32_t)(x0 + 16 * (t % G::TPR) + col);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (!((float)m[j] > 0.0f)) v[t][j] = 0.0f;
-                }
-                float* d = reinterpret_cast<float*>(a.y.base) + px * (uint32_t)a.y.cs + (uint32_t)(a.y.co + o);
-                if (o + 4 <= a.co && a.y_vec) {
-                    *reinterpret_cast<f32x4*>(d) = v[t];
-                } else {
+                    for (int k = 0; k < 4; ++k) {
+                        const size_t q = fine + (k >> 1) * fw + (k & 1);
+                        float* d = reinterpret_cast<float*>(a.add.base) + q * (uint32_t)a.add.cs + (uint32_t)(a.add.co + o);
+                        const f32x4 sum = *reinterpret_cast<const f32x4*>(d) + 0.25f * v[t];
+                        *reinterpret_cast<f32x4*>(d) = masked(sum, a.add_mask, q, o);
+                    }
+                } else if (!(a.sum.base && o >= a.sum_from)) {
+                    v[t] = masked(v[t], a.mask, px, o);
+                    float* d = reinterpret_cast<float*>(a.y.base) + px * (uint32_t)a.y.cs + (uint32_t)(a.y.co + o);
+                    if (o + 4 <= a.co && a.y_vec) {
+                        *reinterpret_cast<f32x4*>(d) = v[t];
+                    } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (o + j < a.co) d[j] = v[t][j];
+                        for (int j = 0; j < 4; ++j)
+                            if (o + j < a.co) d[j] = v[t][j];
+                    }
                 }
             } else {
                 bf16x4 h;
@@ -312,7 +338,25 @@ __global__ void __launch_bounds__(256) conv3x3_lds(ConvArgs a) {
                                            (uint32_t)(a.y.co + o)) = h;
             }
         }
-        if constexpr (!YF32 && G::R % 2 == 0) {
+        if constexpr (YF32) {
+            if (a.sum.base && o >= a.sum_from) {   // 2 x 2 sums, in the order of upsample_bwd_k
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    if ((t / G::TPR) % 2) continue;   // the upper row of each pair
+                    f32x4 sum;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        sum[j] = (v[t][j] + shuffle_x1(v[t][j])) + (v[t + G::TPR][j] + shuffle_x1(v[t + G::TPR][j]));
+                    if ((col & 1) == 0) {
+                        const uint32_t row = (img_row >> 1) + (uint32_t)((y0 + wave * G::R + t / G::TPR) >> 1);
+                        const size_t px = row * (uint32_t)(a.w >> 1) + (uint32_t)((x0 + 16 * (t % G::TPR) + col) >> 1);
+                        const int c = o - a.sum_from;
+                        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.sum.base) + px * (uint32_t)a.sum.cs +
+                                                  (uint32_t)(a.sum.co + c)) = masked(sum, a.sum_mask, px, c);
+                    }
+                }
+            }
+        } else {
             if (a.pool.base) {   // 2 x 2 means of the bf16 outputs, in the order of avgpool_k
 #pragma unroll
                 for (int t = 0; t < T; ++t) {

@@ -66,6 +66,7 @@ __global__ void __launch_bounds__(256, 2) wgrad_lds(WgradArgs a) {
     const uint32_t tiles = (uint32_t)a.n * tiles_x * tiles_y;
     const char* gbase = reinterpret_cast<const char*>(a.g.base);
     const char* xbase = reinterpret_cast<const char*>(a.x.base);
+    const char* x2base = reinterpret_cast<const char*>(a.x2.base);
     const int ct_n = a.ci_pad16 / 16 - cg * CT < CT ? a.ci_pad16 / 16 - cg * CT : CT;   // channel tiles of this group
 
     f32x4 gl[2][2];    // [round][pixel of the pair]: 4 channels
@@ -93,9 +94,17 @@ __global__ void __launch_bounds__(256, 2) wgrad_lds(WgradArgs a) {
                 const int xa = x0 - 2 + 2 * (int)k;   // the pair's pixels xa, xa + 1 (the outermost two are not used)
                 const uint32_t pa = (img_row + yy) * (uint32_t)a.w + (uint32_t)wrap(xa, a.w);
                 const uint32_t pb = (img_row + yy) * (uint32_t)a.w + (uint32_t)wrap(xa + 1, a.w);
-                const uint32_t c = (uint32_t)(a.x.co + cg * CT * 16) + 8 * piece;
-                xl[r][0] = *reinterpret_cast<const u32x4*>(xbase + (pa * (uint32_t)a.x.cs + c) * 2u);
-                xl[r][1] = *reinterpret_cast<const u32x4*>(xbase + (pb * (uint32_t)a.x.cs + c) * 2u);
+                const uint32_t c = (uint32_t)(cg * CT * 16) + 8 * piece;
+                if ((int)c < a.c_split) {
+                    const uint32_t co = (uint32_t)a.x.co + c;
+                    xl[r][0] = *reinterpret_cast<const u32x4*>(xbase + (pa * (uint32_t)a.x.cs + co) * 2u);
+                    xl[r][1] = *reinterpret_cast<const u32x4*>(xbase + (pb * (uint32_t)a.x.cs + co) * 2u);
+                } else {
+                    const uint32_t half = ((img_row >> 1) + (yy >> 1)) * (uint32_t)(a.w >> 1), co = (uint32_t)a.x2.co + c - (uint32_t)a.c_split;
+                    const uint32_t qa = half + ((uint32_t)wrap(xa, a.w) >> 1), qb = half + ((uint32_t)wrap(xa + 1, a.w) >> 1);
+                    xl[r][0] = *reinterpret_cast<const u32x4*>(x2base + (qa * (uint32_t)a.x2.cs + co) * 2u);
+                    xl[r][1] = *reinterpret_cast<const u32x4*>(x2base + (qb * (uint32_t)a.x2.cs + co) * 2u);
+                }
             }
         }
     };
@@ -260,7 +269,9 @@ bool wgrad_lds_fits(const WgradArgs& a) {
     const int64_t px = (int64_t)a.n * a.h * a.w;
     return px * a.g.cs * 4 < ((int64_t)1 << 32) && px * a.x.cs * 2 < ((int64_t)1 << 32) &&
            a.g.co % 4 == 0 && a.g.cs % 4 == 0 && a.x.co % 8 == 0 && a.x.cs % 8 == 0 &&
-           a.g.co + a.co_pad16 <= a.g.cs && a.x.co + a.ci_pad16 <= a.x.cs;
+           a.g.co + a.co_pad16 <= a.g.cs && a.c_split % 16 == 0 && a.x.co + a.c_split <= a.x.cs &&
+           (a.c_split == a.ci_pad16 || (a.x2.co % 8 == 0 && a.x2.cs % 8 == 0 && px / 4 * a.x2.cs * 2 < ((int64_t)1 << 32) &&
+                                        a.x2.co + a.ci_pad16 - a.c_split <= a.x2.cs));
 }
 
 }  // namespace nn
