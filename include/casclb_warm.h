@@ -50,6 +50,18 @@ int lb_warm_restrict(const double* src, int32_t planes, int32_t L, double scale,
  * lies 3/4 past X - 1; separable, 4 x 4 taps.  Preserves the plane mean. */
 int lb_warm_prolong(const double* src, int32_t planes, int32_t Lc, double scale, double* dst, void* stream);
 
+/* lb_warm_prolong of the four fields of `batch` problems in one launch: planes
+ * in the order density [batch], velocity [2][batch], scalar [batch], with
+ * scales[0], [1], [2] (host array) for the density, velocity and scalar ones. */
+int lb_warm_prolong_fields(const double* src, int32_t batch, int32_t Lc, const double scales[3], double* dst,
+                           void* stream);
+
+/* out = a x + b y + c z over fields laid out the same way, n nodes a plane, with
+ * a, b, c (host arrays) per density, velocity and scalar; z and c may be NULL
+ * (no third term).  out may not alias x, y or z. */
+int lb_warm_combine_fields(int32_t batch, int64_t n, const double a[3], const double* x, const double b[3],
+                           const double* y, const double c[3], const double* z, double* out, void* stream);
+
 /* out[i] = a x[i] + b y[i], i < n (out may alias x or y). */
 int lb_warm_axpby(int64_t n, double a, const double* x, double b, const double* y, double* out, void* stream);
 
@@ -94,7 +106,7 @@ int lb_warm_unpack(const float* y, const lb_warm_channel* channels, int32_t ncha
  *     keeps the total half-forced momentum at zero under zero-mean forcing);
  *   u_out = u - F / (2 rho), phi_out = phi - S / 2 (eq. 25 and 43 read
  *     backwards: the initial state's own half-forced moments are the estimate).
- * One workgroup per problem; sums in a fixed order (deterministic). */
+ * Sums in a fixed order (deterministic). */
 int lb_warm_initial_state(const double* drho, const double* u, const double* phi, const double* F, const double* S,
                           int32_t batch, int64_t n, double rho0, int32_t zero_momentum, double* rho_out,
                           double* u_out, double* phi_out, void* stream);

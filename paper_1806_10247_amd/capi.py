@@ -207,6 +207,9 @@ SIGNATURES = {
     "lb_read_moments_device": (ctypes.c_int, [_P, _I32, _P, _P, _P]),
     "lb_warm_restrict": (ctypes.c_int, [_P, _I32, _I32, _D, _P, _P]),
     "lb_warm_prolong": (ctypes.c_int, [_P, _I32, _I32, _D, _P, _P]),
+    "lb_warm_prolong_fields": (ctypes.c_int, [_P, _I32, _I32, ctypes.POINTER(_D), _P, _P]),
+    "lb_warm_combine_fields": (ctypes.c_int, [_I32, _I64, ctypes.POINTER(_D), _P, ctypes.POINTER(_D), _P,
+                                              ctypes.POINTER(_D), _P, _P, _P]),
     "lb_warm_axpby": (ctypes.c_int, [_I64, _D, _P, _D, _P, _P, _P]),
     "lb_warm_project": (ctypes.c_int, [_P, _I32, _I32, _I32, _P]),
     "lb_warm_pack": (ctypes.c_int, [ctypes.POINTER(lb_warm_channel), _I32, _I32, _I64, _P, _P]),
@@ -631,6 +634,19 @@ def lb_warm_restrict(src, planes, L, scale, dst, stream=None):
 
 def lb_warm_prolong(src, planes, Lc, scale, dst, stream=None):
     _wcheck(lib().lb_warm_prolong(src, int(planes), int(Lc), float(scale), dst, stream), "lb_warm_prolong")
+
+
+def lb_warm_prolong_fields(src, batch, Lc, scales, dst, stream=None):
+    """scales: density, velocity, scalar."""
+    _wcheck(lib().lb_warm_prolong_fields(src, int(batch), int(Lc), (_D * 3)(*scales), dst, stream),
+            "lb_warm_prolong_fields")
+
+
+def lb_warm_combine_fields(batch, n, a, x, b, y, c, z, out, stream=None):
+    """a, b, c: density, velocity, scalar (c and z may be None)."""
+    _wcheck(lib().lb_warm_combine_fields(int(batch), int(n), (_D * 3)(*a), x, (_D * 3)(*b), y,
+                                         (_D * 3)(*c) if z is not None else None, z, out, stream),
+            "lb_warm_combine_fields")
 
 
 def lb_warm_axpby(n, a, x, b, y, out, stream=None):

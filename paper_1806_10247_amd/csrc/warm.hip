@@ -7,6 +7,7 @@
 // results do not depend on timing.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "casclb_warm.h"
@@ -48,27 +49,48 @@ __global__ void __launch_bounds__(kBlock) restrict_k(const double* __restrict__ 
 __constant__ double kW[2][4] = {{-0.0234375, 0.2265625, 0.8671875, -0.0703125},
                                 {-0.0703125, 0.8671875, 0.2265625, -0.0234375}};
 
-__global__ void __launch_bounds__(kBlock) prolong_k(const double* __restrict__ src, int64_t planes, int Lc,
-                                                    double scale, double* __restrict__ dst) {
-    const int L = 2 * Lc;
-    const int64_t total = planes * (int64_t)L * L;
-    for (int64_t k = blockIdx.x * (int64_t)kBlock + threadIdx.x; k < total; k += (int64_t)gridDim.x * kBlock) {
-        const int64_t p = k / ((int64_t)L * L);
-        const int r = (int)(k - p * (int64_t)L * L);
-        const int y = r / L, x = r - y * L;
-        // first tap and weight row per axis
-        const int ox = x & 1, oy = y & 1;
-        const int x0 = (x >> 1) - 2 + ox, y0 = (y >> 1) - 2 + oy;
-        const double* a = src + p * (int64_t)Lc * Lc;
-        double acc = 0.0;
-        for (int j = 0; j < 4; ++j) {
-            const double* row = a + (int64_t)wrap(y0 + j, Lc) * Lc;
-            double s = 0.0;
-            for (int i = 0; i < 4; ++i) s += kW[ox][i] * row[wrap(x0 + i, Lc)];
-            acc += kW[oy][j] * s;
-        }
-        dst[k] = scale * acc;
+// Scale of a plane: that of its field when the planes are density, velocity (two
+// components) and scalar of `batch` problems.
+struct PlaneScales {
+    double s[3];
+    int batch;   // 0: every plane has scale s[0]
+};
+__device__ __forceinline__ double plane_scale(const PlaneScales& f, int plane) {
+    if (f.batch == 0) return f.s[0];
+    return plane < f.batch ? f.s[0] : (plane < 3 * f.batch ? f.s[1] : f.s[2]);
+}
+
+__global__ void __launch_bounds__(kBlock) prolong_k(const double* __restrict__ src, int plane0, int Lc,
+                                                    PlaneScales scales, double* __restrict__ dst) {
+    const int L = 2 * Lc, plane = plane0 + (int)blockIdx.y;
+    const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
+    if (r >= (uint32_t)L * (uint32_t)L) return;
+    const int y = (int)(r / (uint32_t)L), x = (int)(r - (uint32_t)y * (uint32_t)L);
+    // first tap and weight row per axis
+    const int ox = x & 1, oy = y & 1;
+    const int x0 = (x >> 1) - 2 + ox, y0 = (y >> 1) - 2 + oy;
+    const double* a = src + (int64_t)plane * Lc * Lc;
+    double acc = 0.0;
+    for (int j = 0; j < 4; ++j) {
+        const double* row = a + wrap(y0 + j, Lc) * Lc;
+        double s = 0.0;
+        for (int i = 0; i < 4; ++i) s += kW[ox][i] * row[wrap(x0 + i, Lc)];
+        acc += kW[oy][j] * s;
     }
+    dst[(int64_t)plane * L * L + r] = plane_scale(scales, plane) * acc;
+}
+
+// out = a x + b y + c z over the planes of the fields, a, b, c per field
+__global__ void __launch_bounds__(kBlock) combine_k(int64_t n, int plane0, PlaneScales a, const double* __restrict__ x, PlaneScales b,
+                                                    const double* __restrict__ y, PlaneScales c,
+                                                    const double* __restrict__ z, double* __restrict__ out) {
+    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (r >= n) return;
+    const int plane = plane0 + (int)blockIdx.y;
+    const int64_t i = (int64_t)plane * n + r;
+    double v = plane_scale(a, plane) * x[i] + plane_scale(b, plane) * y[i];
+    if (z) v = v + plane_scale(c, plane) * z[i];
+    out[i] = v;
 }
 
 __global__ void __launch_bounds__(kBlock) axpby_k(int64_t n, double a, const double* x, double b, const double* y,
@@ -87,21 +109,24 @@ __global__ void __launch_bounds__(kBlock) axpby_k(int64_t n, double a, const dou
 // orthogonal to both lines and to each other, so every coefficient comes from
 // the original plane and one second pass subtracts them all.
 //
-// Pass 1: wave w takes rows w, w + 16, ...; lane l the columns l + 64 j.  Each
-// row's sums over x (the (-1)^x sum, the plain sum and, with low modes, the
-// sums against cos / sin (kx x 2 pi / L), kx = 1, 2) are reduced across the
-// wave by a butterfly and kept in LDS; each lane keeps its columns' (-1)^y
-// sums in registers.  Then the plane sums (total, (pi, pi) and the low-mode
-// coefficients, whose y factor exp(i ky y 2 pi / L) multiplies the row sums:
-// the modes are separable) are formed one per wave from the row sums, and the
-// column sums are added in wave order through LDS.  Pass 2 subtracts, per row,
-// R[y], the column terms and the low modes regrouped as a_kx(y) cos(kx x ..) +
-// b_kx(y) sin(kx x ..).  Every sum has a fixed order: results do not depend on
-// timing.
+// Both passes take the columns in groups of 64 J (J per lane) and the rows
+// two or four at a time, their loads in flight together; wave w takes rows w, w +
+// 16, ...  Pass 1: a row's (-1)^x sum is reduced across the wave by a butterfly
+// and kept in LDS; everything else is summed along the columns in registers: the
+// (-1)^y sums and, for the low modes, the sums against 1, cos / sin(ky y 2 pi /
+// L), ky = 1, 2, whose factors are the same for every lane.  The waves' column
+// sums are added in wave order through LDS, and the low-mode coefficients (the
+// modes are separable) are formed one per wave from them.  Pass 2 subtracts, per
+// row, R[y], the column terms and the low modes regrouped as a_kx(y) cos(kx x ..)
+// + b_kx(y) sin(kx x ..), one row's coefficients per thread beforehand.  Every sum
+// has a fixed order: results do not depend on timing.  Bound by one CU's memory
+// latency: four planes of 256^2 take 32 us without and 53 us with the low
+// modes (40 and 140 with six row sums by butterflies and one row's loads at a time).
 constexpr int kProjBlock = 1024;
 constexpr int kProjWaves = kProjBlock / 64;
 constexpr int kMaxLowModes = 12;   // half-plane modes with kx^2 + ky^2 <= 8
 constexpr int kProjSums = 2 + 2 * kMaxLowModes;
+constexpr int kProjRows = 4;
 
 __device__ __forceinline__ double wave_sum(double v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -110,34 +135,38 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // index of the twiddle for wave number k at position i (|k| <= 2, 0 <= i < L)
 __device__ __forceinline__ int twiddle_index(int k, int i, int L) {
-    int m = (k * i) % L;
-    return m < 0 ? m + L : m;
+    int m = k * i;
+    m = m < 0 ? m + 2 * L : m;   // -2 L < k i < 2 L
+    m = m >= L ? m - L : m;
+    return m >= L ? m - L : m;
 }
+
+// columns per lane: the largest lattices keep the LDS for their row and column sums,
+// and six column sums of four columns do not fit the 128 registers of a lane
+int project_columns(int L, int nmodes) { return L <= 64 || L > 1024 ? 1 : (L <= 128 || nmodes > 0 ? 2 : 4); }
 
 size_t project_lds_bytes(int L, int nmodes) {
-    return (size_t)((nmodes > 0 ? 9 : 3) * L + kProjWaves * 64 + kProjSums) * sizeof(double);
+    return (size_t)((nmodes > 0 ? 9 : 2) * L + project_columns(L, nmodes) * kProjWaves * 64 + kProjWaves + kProjSums) *
+           sizeof(double);
 }
 
-template <int J>
+template <int J, bool LOW>
 __global__ void __launch_bounds__(kProjBlock) project_k(double* data, int L, int nmodes, int4 modes_a, int4 modes_b,
                                                         int4 modes_c, int4 modes_d, int4 modes_e, int4 modes_f) {
+    constexpr int KR = LOW && J > 1 ? 2 : kProjRows, NC = LOW ? 6 : 1;   // column sums: (-1)^y, then 1, cos y, sin y, cos 2y, sin 2y
     extern __shared__ double lds[];
-    double* red = lds;                          // [kProjWaves][64] wave partials
-    double* fin = red + kProjWaves * 64;        // [kProjSums] plane sums
-    double* rowR = fin + kProjSums;             // R[y]
-    double* rowT = rowR + L;                    // row sums
-    double* col = rowT + L;                     // C[x] - (-1)^x c
-    double* ct = col + L;                       // with low modes: cos(2 pi m / L)
-    double* st = ct + L;                        //   sin(2 pi m / L)
-    double* rc1 = st + L;                       //   row sums against cos / sin(kx x 2 pi / L), kx = 1, 2
-    double* rs1 = rc1 + L;
-    double* rc2 = rs1 + L;
-    double* rs2 = rc2 + L;
+    double* red = lds;                              // [J][kProjWaves][64] wave partials
+    double* totals = red + J * kProjWaves * 64;     // [kProjWaves]
+    double* fin = totals + kProjWaves;              // [kProjSums] plane sums
+    double* rowR = fin + kProjSums;                 // R[y]
+    double* cols = rowR + L;                        // [NC][L] column sums; [1..5] later the low modes' row coefficients
+    double* ct = cols + NC * L;                     // with low modes: cos(2 pi m / L)
+    double* st = ct + L;                            //   sin(2 pi m / L)
     double* A = data + (int64_t)blockIdx.x * L * L;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const double inv = 1.0 / (double)L;
     __shared__ int mkx[kMaxLowModes], mky[kMaxLowModes];   // wave numbers of the low modes
-    if (nmodes > 0) {
+    if constexpr (LOW) {
         if (threadIdx.x == 0) {
             const int4 packed[6] = {modes_a, modes_b, modes_c, modes_d, modes_e, modes_f};
 #pragma unroll
@@ -151,117 +180,159 @@ __global__ void __launch_bounds__(kProjBlock) project_k(double* data, int L, int
         for (int m = threadIdx.x; m < L; m += kProjBlock) sincospi(2.0 * (double)m / (double)L, &st[m], &ct[m]);
         __syncthreads();
     }
-    // ---- pass 1: row sums to LDS, column sums in registers
-    double colacc[J];
+    const double sx0 = (lane & 1) ? -1.0 : 1.0;   // x is even exactly when lane is
+    auto load_rows = [&](int y0, int g, double (&v)[KR][J]) {
 #pragma unroll
-    for (int j = 0; j < J; ++j) colacc[j] = 0.0;
-    for (int y = wave; y < L; y += kProjWaves) {
-        const double* row = A + (int64_t)y * L;
-        const double sy = (y & 1) ? -1.0 : 1.0;
-        double alt = 0.0, tot = 0.0, c1 = 0.0, s1 = 0.0, c2 = 0.0, s2 = 0.0;
+        for (int i = 0; i < KR; ++i)
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int x = lane + 64 * j;   // x is even exactly when lane is
-            if (x < L) {
-                const double v = row[x];
-                alt += (lane & 1) ? -v : v;
-                tot += v;
-                colacc[j] += sy * v;
-                if (nmodes > 0) {
-                    const int x2 = twiddle_index(2, x, L);
-                    c1 += v * ct[x];
-                    s1 += v * st[x];
-                    c2 += v * ct[x2];
-                    s2 += v * st[x2];
-                }
+            for (int j = 0; j < J; ++j) {
+                const int y = y0 + i * kProjWaves, x = g + lane + 64 * j;
+                v[i][j] = y < L && x < L ? A[(int64_t)y * L + x] : 0.0;
             }
+    };
+    // ---- pass 1
+    double total = 0.0;
+    for (int g = 0; g < L; g += 64 * J) {
+        double acc[NC][J];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int j = 0; j < J; ++j) acc[c][j] = 0.0;
+        for (int y0 = wave; y0 < L; y0 += KR * kProjWaves) {
+            double v[KR][J], alt[KR];
+            load_rows(y0, g, v);
+#pragma unroll
+            for (int i = 0; i < KR; ++i) {
+                const int y = y0 + i * kProjWaves;
+                const double sy = (y & 1) ? -1.0 : 1.0;
+                alt[i] = 0.0;
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    alt[i] += v[i][j];
+                    acc[0][j] += sy * v[i][j];
+                }
+                if constexpr (LOW) {
+                    const int yc = y < L ? y : 0, y2 = twiddle_index(2, yc, L);   // (rows past the end are zeros)
+                    const double c1 = ct[yc], s1 = st[yc], c2 = ct[y2], s2 = st[y2];
+#pragma unroll
+                    for (int j = 0; j < J; ++j) {
+                        acc[1][j] += v[i][j];
+                        acc[2][j] += v[i][j] * c1;
+                        acc[3][j] += v[i][j] * s1;
+                        acc[4][j] += v[i][j] * c2;
+                        acc[5][j] += v[i][j] * s2;
+                    }
+                }
+                total += alt[i];
+                alt[i] *= sx0;
+            }
+#pragma unroll
+            for (int i = 0; i < KR; ++i) alt[i] = wave_sum(alt[i]);
+            if (lane == 0)
+#pragma unroll
+                for (int i = 0; i < KR; ++i) {
+                    const int y = y0 + i * kProjWaves;
+                    if (y < L) rowR[y] = (g == 0 ? 0.0 : rowR[y]) + alt[i] * inv;
+                }
         }
-        alt = wave_sum(alt);
-        tot = wave_sum(tot);
-        if (nmodes > 0) {   // uniform: every lane of the block takes the same branch
-            c1 = wave_sum(c1);
-            s1 = wave_sum(s1);
-            c2 = wave_sum(c2);
-            s2 = wave_sum(s2);
-        }
-        if (lane == 0) {
-            rowR[y] = alt * inv;
-            rowT[y] = tot;
-            if (nmodes > 0) {
-                rc1[y] = c1;
-                rs1[y] = s1;
-                rc2[y] = c2;
-                rs2[y] = s2;
+        // the waves' column sums, added in wave order
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < J; ++j) red[(j * kProjWaves + wave) * 64 + lane] = acc[c][j];
+            __syncthreads();
+            const int x = g + (int)threadIdx.x;
+            if (threadIdx.x < 64 * J && x < L) {
+                double s = 0.0;
+                for (int w = 0; w < kProjWaves; ++w) s += red[(wave * kProjWaves + w) * 64 + lane];
+                cols[c * L + x] = s;
             }
         }
     }
+    total = wave_sum(total);
+    if (lane == 0) totals[wave] = total;
     __syncthreads();
-    // ---- plane sums, one per wave: q = 0 total, 1 (-1)^y R[y], 2 + 2 i and 3 + 2 i the
+    // ---- plane sums, one per wave: q = 0 mean, 1 (-1)^y R[y], 2 + 2 i and 3 + 2 i the
     // cos and sin coefficients of low mode i
     for (int q = wave; q < 2 + 2 * nmodes; q += kProjWaves) {
-        const int kx = q >= 2 ? mkx[(q - 2) >> 1] : 0, ky = q >= 2 ? mky[(q - 2) >> 1] : 0;
         double s = 0.0;
-        for (int y = lane; y < L; y += 64) {
-            if (q == 0) {
-                s += rowT[y];
-            } else if (q == 1) {
-                s += (y & 1) ? -rowR[y] : rowR[y];
-            } else {
-                const double pc = kx == 0 ? rowT[y] : (kx == 1 ? rc1[y] : rc2[y]);
-                const double ps = kx == 0 ? 0.0 : (kx == 1 ? rs1[y] : rs2[y]);
-                const int t = twiddle_index(ky, y, L);
-                s += (q & 1) ? ps * ct[t] + pc * st[t] : pc * ct[t] - ps * st[t];
+        if (q == 0) {
+            for (int w = 0; w < kProjWaves; ++w) s += totals[w];
+        } else if (q == 1) {
+            for (int y = lane; y < L; y += 64) s += (y & 1) ? -rowR[y] : rowR[y];
+            s = wave_sum(s);
+        } else if constexpr (LOW) {
+            const int kx = mkx[(q - 2) >> 1], ky = mky[(q - 2) >> 1], k = ky < 0 ? -ky : ky;
+            const double sgn = ky < 0 ? -1.0 : 1.0;
+            const double* cy = cols + (k == 0 ? 1 : 2 * k) * L;   // sums against cos(k y ..), sin(k y ..)
+            const double* sn = cols + (2 * k + 1) * L;
+            for (int x = lane; x < L; x += 64) {
+                const int t = twiddle_index(kx, x, L);
+                const double pc = cy[x], ps = k == 0 ? 0.0 : sgn * sn[x];
+                s += (q & 1) ? pc * st[t] + ps * ct[t] : pc * ct[t] - ps * st[t];
             }
+            s = wave_sum(s);
         }
-        s = wave_sum(s);
         if (lane == 0) fin[q] = q == 0 ? s * inv * inv : (q == 1 ? s * inv : 2.0 * s * inv * inv);
     }
     __syncthreads();
     const double mean = fin[0], cnn = fin[1];
-    // ---- column sums, 64 columns at a time, added in wave order
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        red[wave * 64 + lane] = colacc[j];
-        __syncthreads();
-        const int x = 64 * j + (int)threadIdx.x;
-        if (threadIdx.x < 64 && x < L) {
-            double s = 0.0;
-            for (int w = 0; w < kProjWaves; ++w) s += red[w * 64 + threadIdx.x];
-            col[x] = s * inv - ((x & 1) ? -cnn : cnn);
+    if constexpr (LOW) {
+        // row coefficients a0 (with the mean), a1, b1, a2, b2 over the sums no longer needed
+        for (int y = threadIdx.x; y < L; y += kProjBlock) {
+            double a0 = mean, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0;
+            for (int m = 0; m < nmodes; ++m) {
+                const int kx = mkx[m], t = twiddle_index(mky[m], y, L);
+                const double mc = fin[2 + 2 * m], ms = fin[3 + 2 * m];
+                const double a = mc * ct[t] + ms * st[t], b = ms * ct[t] - mc * st[t];
+                if (kx == 0) {
+                    a0 += a;
+                } else if (kx == 1) {
+                    a1 += a;
+                    b1 += b;
+                } else {
+                    a2 += a;
+                    b2 += b;
+                }
+            }
+            cols[1 * L + y] = a0;
+            cols[2 * L + y] = a1;
+            cols[3 * L + y] = b1;
+            cols[4 * L + y] = a2;
+            cols[5 * L + y] = b2;
         }
         __syncthreads();
     }
     // ---- pass 2
-    for (int y = wave; y < L; y += kProjWaves) {
-        double* row = A + (int64_t)y * L;
-        const double sy = (y & 1) ? -1.0 : 1.0;
-        const double ry = rowR[y];
-        double a0 = mean, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0;
-        for (int i = 0; i < nmodes; ++i) {
-            const int kx = mkx[i], t = twiddle_index(mky[i], y, L);
-            const double mc = fin[2 + 2 * i], ms = fin[3 + 2 * i];
-            const double a = mc * ct[t] + ms * st[t], b = ms * ct[t] - mc * st[t];
-            if (kx == 0) {
-                a0 += a;
-            } else if (kx == 1) {
-                a1 += a;
-                b1 += b;
-            } else {
-                a2 += a;
-                b2 += b;
-            }
-        }
-        const double sx0 = (lane & 1) ? -1.0 : 1.0;
+    for (int g = 0; g < L; g += 64 * J) {
+        double col[J];   // C[x] - (-1)^x c of this lane's columns
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            const int x = lane + 64 * j;
-            if (x < L) {
-                double low = a0;
-                if (nmodes > 0) {
-                    const int x2 = twiddle_index(2, x, L);
-                    low += a1 * ct[x] + b1 * st[x] + a2 * ct[x2] + b2 * st[x2];
+            const int x = g + lane + 64 * j;
+            col[j] = x < L ? cols[x] * inv - sx0 * cnn : 0.0;
+        }
+        for (int y0 = wave; y0 < L; y0 += KR * kProjWaves) {
+            double v[KR][J];
+            load_rows(y0, g, v);
+#pragma unroll
+            for (int i = 0; i < KR; ++i) {
+                const int y = y0 + i * kProjWaves;
+                if (y >= L) break;
+                const double sy = (y & 1) ? -1.0 : 1.0, ry = rowR[y];
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int x = g + lane + 64 * j;
+                    if (x < L) {
+                        double low = mean;
+                        if constexpr (LOW) {
+                            const int x2 = twiddle_index(2, x, L);
+                            low = cols[1 * L + y] + cols[2 * L + y] * ct[x] + cols[3 * L + y] * st[x] +
+                                  cols[4 * L + y] * ct[x2] + cols[5 * L + y] * st[x2];
+                        }
+                        A[(int64_t)y * L + x] = v[i][j] - sx0 * ry - sy * col[j] - low;
+                    }
                 }
-                row[x] = row[x] - sx0 * ry - sy * col[x] - low;
             }
         }
     }
@@ -342,12 +413,93 @@ __global__ void __launch_bounds__(kProjBlock) initial_state_k(const double* drho
     }
 }
 
+// The same in three launches that use the whole chip, for problems of many nodes
+// and outputs apart from the inputs: partial sums (kInitParts workgroups per
+// problem, left in the first kInitParts nodes of the outputs), every other node,
+// then those first nodes.  One problem of 64^2: 9.7 us in one launch, 9.9 in
+// three; 90^2: 18 and 10; 256^2: 109 and 10 (launch-bound: the kernels take 4 + 4 + 2).
+constexpr int kInitParts = 64;
+struct InitArgs {
+    const double *drho, *u, *phi, *F, *S;
+    int64_t n, comp;   // nodes per problem, stride between the components
+    double rho0;
+    double *rho_out, *u_out, *phi_out;
+};
+
+__device__ __forceinline__ void initial_node(const InitArgs& a, int64_t i, double shift_x, double shift_y) {
+    const double r = a.rho0 + a.drho[i];
+    a.rho_out[i] = r;
+    a.u_out[i] = (a.u[i] - shift_x) - a.F[i] / (2.0 * r);
+    a.u_out[a.comp + i] = (a.u[a.comp + i] - shift_y) - a.F[a.comp + i] / (2.0 * r);
+    if (a.phi_out) a.phi_out[i] = a.phi[i] - (a.S ? 0.5 * a.S[i] : 0.0);
+}
+
+__global__ void __launch_bounds__(kBlock) initial_sums_k(InitArgs a) {
+    __shared__ double lds[kBlock];
+    const int64_t o = (int64_t)blockIdx.y * a.n;
+    double sr = 0.0, sx = 0.0, sy = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < a.n; i += kInitParts * kBlock) {
+        const double r = a.rho0 + a.drho[o + i];
+        sr += r;
+        sx += r * a.u[o + i];
+        sy += r * a.u[a.comp + o + i];
+    }
+    sr = block_sum(sr, lds);
+    sx = block_sum(sx, lds);
+    sy = block_sum(sy, lds);
+    if (threadIdx.x == 0) {
+        a.rho_out[o + blockIdx.x] = sr;
+        a.u_out[o + blockIdx.x] = sx;
+        a.u_out[a.comp + o + blockIdx.x] = sy;
+    }
+}
+
+// u's shift of problem o / n from the partial sums (every wavefront adds them in the same order)
+__device__ __forceinline__ void initial_shift(const InitArgs& a, int64_t o, double& shift_x, double& shift_y) {
+    static_assert(kInitParts == 64, "one partial sum per lane");
+    const int lane = threadIdx.x & 63;
+    const double tr = wave_sum(a.rho_out[o + lane]), tx = wave_sum(a.u_out[o + lane]),
+                 ty = wave_sum(a.u_out[a.comp + o + lane]);
+    shift_x = tx / tr;
+    shift_y = ty / tr;
+}
+
+__global__ void __launch_bounds__(kBlock) initial_rest_k(InitArgs a) {
+    const int64_t o = (int64_t)blockIdx.y * a.n;
+    double shift_x, shift_y;
+    initial_shift(a, o, shift_x, shift_y);
+    const int64_t i = kInitParts + (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < a.n) initial_node(a, o + i, shift_x, shift_y);
+}
+
+__global__ void __launch_bounds__(kInitParts) initial_first_k(InitArgs a) {
+    const int64_t o = (int64_t)blockIdx.x * a.n;
+    double shift_x, shift_y;
+    initial_shift(a, o, shift_x, shift_y);   // one wavefront: read before any of it is overwritten
+    initial_node(a, o + threadIdx.x, shift_x, shift_y);
+}
+
 int grid_for(int64_t total) {
     const int64_t blocks = (total + kBlock - 1) / kBlock;
     return (int)(blocks < 65536 ? (blocks > 0 ? blocks : 1) : 65536);
 }
 
+constexpr int kMaxPlanes = 65535;   // of one launch (grid.y)
+
 int done(hipError_t e) { return e == hipSuccess ? LB_OK : LB_EHIP; }
+
+int launch_prolong(const double* src, int planes, int Lc, const PlaneScales& scales, double* dst, hipStream_t s) {
+    const unsigned blocks = ((unsigned)(2 * Lc) * (unsigned)(2 * Lc) + kBlock - 1) / kBlock;
+    for (int p0 = 0; p0 < planes; p0 += kMaxPlanes)
+        hipLaunchKernelGGL(prolong_k, dim3(blocks, (unsigned)std::min(kMaxPlanes, planes - p0)), dim3(kBlock), 0, s, src, p0,
+                           Lc, scales, dst);
+    return done(hipGetLastError());
+}
+
+// Whether [a, a + n) and [b, b + m) share an element.
+bool overlap(const double* a, int64_t n, const double* b, int64_t m) {
+    return a && b && (uintptr_t)a < (uintptr_t)(b + m) && (uintptr_t)b < (uintptr_t)(a + n);
+}
 
 }  // namespace casclb_warm
 
@@ -365,9 +517,26 @@ int lb_warm_restrict(const double* src, int32_t planes, int32_t L, double scale,
 
 int lb_warm_prolong(const double* src, int32_t planes, int32_t Lc, double scale, double* dst, void* stream) {
     if (!src || !dst || planes < 1 || Lc < 2 || 2 * Lc > LB_WARM_MAX_L) return LB_EINVAL;
-    const int64_t total = (int64_t)planes * (2 * Lc) * (2 * Lc);
-    hipLaunchKernelGGL(prolong_k, dim3(grid_for(total)), dim3(kBlock), 0, (hipStream_t)stream, src, (int64_t)planes,
-                       (int)Lc, scale, dst);
+    return launch_prolong(src, planes, Lc, PlaneScales{{scale, scale, scale}, 0}, dst, (hipStream_t)stream);
+}
+
+int lb_warm_prolong_fields(const double* src, int32_t batch, int32_t Lc, const double scales[3], double* dst,
+                           void* stream) {
+    if (!src || !dst || !scales || batch < 1 || batch > (1 << 28) || Lc < 2 || 2 * Lc > LB_WARM_MAX_L) return LB_EINVAL;
+    return launch_prolong(src, 4 * batch, Lc, PlaneScales{{scales[0], scales[1], scales[2]}, batch}, dst, (hipStream_t)stream);
+}
+
+int lb_warm_combine_fields(int32_t batch, int64_t n, const double a[3], const double* x, const double b[3],
+                           const double* y, const double c[3], const double* z, double* out, void* stream) {
+    if (batch < 1 || batch > (1 << 28) || n < 1 || n > (int64_t)LB_WARM_MAX_L * LB_WARM_MAX_L || !a || !x || !b || !y ||
+        (z && !c) || !out)
+        return LB_EINVAL;
+    const PlaneScales pa{{a[0], a[1], a[2]}, batch}, pb{{b[0], b[1], b[2]}, batch};
+    PlaneScales pc{{0.0, 0.0, 0.0}, batch};
+    if (z) pc = PlaneScales{{c[0], c[1], c[2]}, batch};
+    for (int p0 = 0; p0 < 4 * batch; p0 += kMaxPlanes)
+        hipLaunchKernelGGL(combine_k, dim3((unsigned)((n + kBlock - 1) / kBlock), (unsigned)std::min(kMaxPlanes, 4 * batch - p0)),
+                           dim3(kBlock), 0, (hipStream_t)stream, n, p0, pa, x, pb, y, pc, z, out);
     return done(hipGetLastError());
 }
 
@@ -397,10 +566,10 @@ int lb_warm_project(double* data, int32_t planes, int32_t L, int32_t k2max, void
     const int4 ma = make_int4(m[0], m[1], m[2], m[3]), mb = make_int4(m[4], m[5], m[6], m[7]),
                mc = make_int4(m[8], m[9], m[10], m[11]), md = make_int4(m[12], m[13], m[14], m[15]),
                me = make_int4(m[16], m[17], m[18], m[19]), mf = make_int4(m[20], m[21], m[22], m[23]);
-    // columns per lane, rounded up to a power of two
-    const int cols = (L + 63) / 64;
-    auto kernel = cols <= 1 ? project_k<1> : cols <= 2 ? project_k<2> : cols <= 4 ? project_k<4>
-                : cols <= 8 ? project_k<8> : cols <= 16 ? project_k<16> : project_k<32>;
+    const int J = project_columns(L, n);
+    auto plain = J == 1 ? project_k<1, false> : J == 2 ? project_k<2, false> : project_k<4, false>;
+    auto low = J == 1 ? project_k<1, true> : project_k<2, true>;
+    auto kernel = n > 0 ? low : plain;
     if (lds > 65536) {   // the largest lattices need more than the default dynamic LDS limit
         const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return LB_EHIP;
@@ -444,6 +613,22 @@ int lb_warm_initial_state(const double* drho, const double* u, const double* phi
                           double* u_out, double* phi_out, void* stream) {
     if (!drho || !u || !F || !rho_out || !u_out || batch < 1 || n < 1) return LB_EINVAL;
     if ((phi == nullptr) != (phi_out == nullptr)) return LB_EINVAL;
+    const int64_t all = (int64_t)batch * n;
+    const InitArgs a{drho, u, phi, F, S, n, all, rho0, rho_out, u_out, phi_out};
+    // outputs that share memory with an input are written only after every sum: one workgroup each
+    bool apart = true;
+    for (const double* in : {drho, phi, S})
+        apart = apart && !overlap(in, all, rho_out, all) && !overlap(in, all, u_out, 2 * all) && !overlap(in, all, phi_out, all);
+    for (const double* in : {u, F})
+        apart = apart && !overlap(in, 2 * all, rho_out, all) && !overlap(in, 2 * all, u_out, 2 * all) && !overlap(in, 2 * all, phi_out, all);
+    // from where three launches cost less than one: 64^2 nodes
+    if (zero_momentum && apart && n >= 4096 && batch <= kMaxPlanes) {
+        hipLaunchKernelGGL(initial_sums_k, dim3(kInitParts, (unsigned)batch), dim3(kBlock), 0, (hipStream_t)stream, a);
+        hipLaunchKernelGGL(initial_rest_k, dim3((unsigned)((n - kInitParts + kBlock - 1) / kBlock), (unsigned)batch),
+                           dim3(kBlock), 0, (hipStream_t)stream, a);
+        hipLaunchKernelGGL(initial_first_k, dim3((unsigned)batch), dim3(kInitParts), 0, (hipStream_t)stream, a);
+        return done(hipGetLastError());
+    }
     hipLaunchKernelGGL(initial_state_k, dim3(batch), dim3(kProjBlock), 0, (hipStream_t)stream, drho, u, phi, F, S,
                        (int)batch, n, rho0, (int)(zero_momentum != 0), rho_out, u_out, phi_out);
     return done(hipGetLastError());

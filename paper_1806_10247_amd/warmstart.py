@@ -155,6 +155,15 @@ class Fields:
         run over all 4 B planes for Fields that own one allocation."""
         return ((self.buf, 4 * self.B),) if self.buf is not None else self.planes()
 
+    def whole(self):
+        """The one allocation, if rho, u and phi are (still) its parts, else None."""
+        n = self.B * self.L * self.L
+        if self.buf is None:
+            return None
+        base = self.buf.data_ptr()
+        parts = (self.rho.data_ptr(), self.u.data_ptr(), self.phi.data_ptr())
+        return self.buf if parts == (base, base + 8 * n, base + 24 * n) else None
+
     def project(self, k2max=0):
         """Means and Nyquist lines (and the modes 0 < |k|^2 <= k2max) removed from
         every plane, in place."""
@@ -182,6 +191,9 @@ _LEVEL_SCALE = (0.25, 0.5, 1.0)
 def prolong(f):
     """Fields on the 2L lattice from those on L, rescaled (u/2, (rho - .)/4)."""
     g = Fields(2 * f.L, f.B)
+    if f.whole() is not None:
+        C.lb_warm_prolong_fields(_ptr(f.buf), f.B, f.L, _LEVEL_SCALE, _ptr(g.buf), _stream())
+        return g
     for (a, p), (b, _), s in zip(f.planes(), g.planes(), _LEVEL_SCALE):
         C.lb_warm_prolong(_ptr(a), p, f.L, s, _ptr(b), _stream())
     return g
@@ -203,6 +215,12 @@ def extrapolate(f1, f2, w=RICHARDSON):
     is four times larger in f2.  Densities may carry any constant; remove it
     later."""
     g = prolong(f2)
+    if f1.whole() is not None:
+        w = _weights(w)
+        o = Fields(f1.L, f1.B)
+        C.lb_warm_combine_fields(f1.B, f1.L * f1.L, [1.0 + v for v in w], _ptr(f1.buf), [-v for v in w], _ptr(g.buf),
+                                 None, None, _ptr(o.buf), _stream())
+        return o
     for (a, _), (b, _), wi in zip(f1.planes(), g.planes(), _weights(w)):
         C.lb_warm_axpby(a.numel(), 1.0 + wi, _ptr(a), -wi, _ptr(b), _ptr(b), _stream())
     return g
@@ -220,6 +238,11 @@ def extrapolate3(f1, f2, f3, a, b):
     p2 = prolong(f2)
     p3 = prolong(prolong(f3))
     g = Fields(f1.L, f1.B)
+    if f1.whole() is not None:
+        a, b = _weights(a), _weights(b)
+        C.lb_warm_combine_fields(f1.B, f1.L * f1.L, [1.0 + v for v in a], _ptr(f1.buf), [w - v for v, w in zip(a, b)],
+                                 _ptr(p2.buf), [-v for v in b], _ptr(p3.buf), _ptr(g.buf), _stream())
+        return g
     for (x, _), (y, _), (z, _), (o, _), ai, bi in zip(f1.planes(), p2.planes(), p3.planes(), g.planes(),
                                                       _weights(a), _weights(b)):
         C.lb_warm_axpby(x.numel(), 1.0 + ai, _ptr(x), bi - ai, _ptr(y), _ptr(o), _stream())
