@@ -50,17 +50,13 @@ int lb_warm_restrict(const double* src, int32_t planes, int32_t L, double scale,
  * lies 3/4 past X - 1; separable, 4 x 4 taps.  Preserves the plane mean. */
 int lb_warm_prolong(const double* src, int32_t planes, int32_t Lc, double scale, double* dst, void* stream);
 
-/* lb_warm_prolong of the four fields of `batch` problems in one launch: planes
- * in the order density [batch], velocity [2][batch], scalar [batch], with
- * scales[0], [1], [2] (host array) for the density, velocity and scalar ones. */
-int lb_warm_prolong_fields(const double* src, int32_t batch, int32_t Lc, const double scales[3], double* dst,
-                           void* stream);
-
-/* out = a x + b y + c z over fields laid out the same way, n nodes a plane, with
- * a, b, c (host arrays) per density, velocity and scalar; z and c may be NULL
- * (no third term).  out may not alias x, y or z. */
-int lb_warm_combine_fields(int32_t batch, int64_t n, const double a[3], const double* x, const double b[3],
-                           const double* y, const double c[3], const double* z, double* out, void* stream);
+/* dst = a x + b P y + c P z over the four fields of `batch` problems in one
+ * launch, P the prolongation above: planes in the order density [batch],
+ * velocity [2][batch], scalar [batch], and a, b, c (host arrays) per density,
+ * velocity and scalar.  y and z are on the half-size lattice; x and z may be
+ * NULL (no such term; then a or c may be too).  dst may not alias an input. */
+int lb_warm_prolong_fields(int32_t batch, int32_t Lc, const double a[3], const double* x, const double b[3],
+                           const double* y, const double c[3], const double* z, double* dst, void* stream);
 
 /* out[i] = a x[i] + b y[i], i < n (out may alias x or y). */
 int lb_warm_axpby(int64_t n, double a, const double* x, double b, const double* y, double* out, void* stream);
@@ -75,6 +71,12 @@ int lb_warm_axpby(int64_t n, double a, const double* x, double b, const double* 
  * scales.  L even, 2..2048.  One workgroup per plane reads it twice; sums in a
  * fixed order (deterministic). */
 int lb_warm_project(double* data, int32_t planes, int32_t L, int32_t k2max, void* stream);
+
+/* The same over the whole chip, with a workspace of lb_warm_project_work()
+ * doubles on the device, free again once `stream` has passed the call.  The work
+ * size is 0 where the arguments are refused or one workgroup per plane is as fast. */
+int64_t lb_warm_project_work(int32_t planes, int32_t L, int32_t k2max);
+int lb_warm_project_split(double* data, int32_t planes, int32_t L, int32_t k2max, double* work, void* stream);
 
 /* One channel of a pack / unpack: `src` is a [batch][n] slice (image b at
  * src + b n); NULL in lb_warm_pack means a constant channel.  `dst` is used

@@ -207,11 +207,12 @@ SIGNATURES = {
     "lb_read_moments_device": (ctypes.c_int, [_P, _I32, _P, _P, _P]),
     "lb_warm_restrict": (ctypes.c_int, [_P, _I32, _I32, _D, _P, _P]),
     "lb_warm_prolong": (ctypes.c_int, [_P, _I32, _I32, _D, _P, _P]),
-    "lb_warm_prolong_fields": (ctypes.c_int, [_P, _I32, _I32, ctypes.POINTER(_D), _P, _P]),
-    "lb_warm_combine_fields": (ctypes.c_int, [_I32, _I64, ctypes.POINTER(_D), _P, ctypes.POINTER(_D), _P,
+    "lb_warm_prolong_fields": (ctypes.c_int, [_I32, _I32, ctypes.POINTER(_D), _P, ctypes.POINTER(_D), _P,
                                               ctypes.POINTER(_D), _P, _P, _P]),
     "lb_warm_axpby": (ctypes.c_int, [_I64, _D, _P, _D, _P, _P, _P]),
     "lb_warm_project": (ctypes.c_int, [_P, _I32, _I32, _I32, _P]),
+    "lb_warm_project_work": (_I64, [_I32, _I32, _I32]),
+    "lb_warm_project_split": (ctypes.c_int, [_P, _I32, _I32, _I32, _P, _P]),
     "lb_warm_pack": (ctypes.c_int, [ctypes.POINTER(lb_warm_channel), _I32, _I32, _I64, _P, _P]),
     "lb_warm_unpack": (ctypes.c_int, [_P, ctypes.POINTER(lb_warm_channel), _I32, _I32, _I64, _P]),
     "lb_warm_initial_state": (ctypes.c_int, [_P, _P, _P, _P, _P, _I32, _I64, _D, _I32, _P, _P, _P, _P]),
@@ -636,17 +637,11 @@ def lb_warm_prolong(src, planes, Lc, scale, dst, stream=None):
     _wcheck(lib().lb_warm_prolong(src, int(planes), int(Lc), float(scale), dst, stream), "lb_warm_prolong")
 
 
-def lb_warm_prolong_fields(src, batch, Lc, scales, dst, stream=None):
-    """scales: density, velocity, scalar."""
-    _wcheck(lib().lb_warm_prolong_fields(src, int(batch), int(Lc), (_D * 3)(*scales), dst, stream),
-            "lb_warm_prolong_fields")
-
-
-def lb_warm_combine_fields(batch, n, a, x, b, y, c, z, out, stream=None):
-    """a, b, c: density, velocity, scalar (c and z may be None)."""
-    _wcheck(lib().lb_warm_combine_fields(int(batch), int(n), (_D * 3)(*a), x, (_D * 3)(*b), y,
-                                         (_D * 3)(*c) if z is not None else None, z, out, stream),
-            "lb_warm_combine_fields")
+def lb_warm_prolong_fields(batch, Lc, a, x, b, y, c, z, dst, stream=None):
+    """a, b, c: density, velocity, scalar (a and x, or c and z, may be None)."""
+    D3 = _D * 3
+    _wcheck(lib().lb_warm_prolong_fields(int(batch), int(Lc), D3(*a) if a else None, x, D3(*b), y,
+                                         D3(*c) if c else None, z, dst, stream), "lb_warm_prolong_fields")
 
 
 def lb_warm_axpby(n, a, x, b, y, out, stream=None):
@@ -655,6 +650,14 @@ def lb_warm_axpby(n, a, x, b, y, out, stream=None):
 
 def lb_warm_project(data, planes, L, k2max=0, stream=None):
     _wcheck(lib().lb_warm_project(data, int(planes), int(L), int(k2max), stream), "lb_warm_project")
+
+
+def lb_warm_project_work(planes, L, k2max=0):
+    return lib().lb_warm_project_work(int(planes), int(L), int(k2max))
+
+
+def lb_warm_project_split(data, planes, L, k2max, work, stream=None):
+    _wcheck(lib().lb_warm_project_split(data, int(planes), int(L), int(k2max), work, stream), "lb_warm_project_split")
 
 
 def _channels(chs):

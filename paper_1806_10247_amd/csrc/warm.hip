@@ -3,7 +3,7 @@
 // projection that removes the mean and the Nyquist lines, packing of the
 // network's NHWC input and unpacking of its output, and the initial moments.
 // All are bandwidth-bound passes over float64 planes, run once per problem;
-// the plane-wide sums are done by one workgroup per plane in a fixed order so
+// the plane-wide sums are done in a fixed order so
 // results do not depend on timing.
 #include <hip/hip_runtime.h>
 
@@ -60,16 +60,11 @@ __device__ __forceinline__ double plane_scale(const PlaneScales& f, int plane) {
     return plane < f.batch ? f.s[0] : (plane < 3 * f.batch ? f.s[1] : f.s[2]);
 }
 
-__global__ void __launch_bounds__(kBlock) prolong_k(const double* __restrict__ src, int plane0, int Lc,
-                                                    PlaneScales scales, double* __restrict__ dst) {
-    const int L = 2 * Lc, plane = plane0 + (int)blockIdx.y;
-    const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= (uint32_t)L * (uint32_t)L) return;
-    const int y = (int)(r / (uint32_t)L), x = (int)(r - (uint32_t)y * (uint32_t)L);
+// node (x, y) of a plane prolonged from a
+__device__ __forceinline__ double prolong_node(const double* a, int Lc, int x, int y) {
     // first tap and weight row per axis
     const int ox = x & 1, oy = y & 1;
     const int x0 = (x >> 1) - 2 + ox, y0 = (y >> 1) - 2 + oy;
-    const double* a = src + (int64_t)plane * Lc * Lc;
     double acc = 0.0;
     for (int j = 0; j < 4; ++j) {
         const double* row = a + wrap(y0 + j, Lc) * Lc;
@@ -77,20 +72,22 @@ __global__ void __launch_bounds__(kBlock) prolong_k(const double* __restrict__ s
         for (int i = 0; i < 4; ++i) s += kW[ox][i] * row[wrap(x0 + i, Lc)];
         acc += kW[oy][j] * s;
     }
-    dst[(int64_t)plane * L * L + r] = plane_scale(scales, plane) * acc;
+    return acc;
 }
 
-// out = a x + b y + c z over the planes of the fields, a, b, c per field
-__global__ void __launch_bounds__(kBlock) combine_k(int64_t n, int plane0, PlaneScales a, const double* __restrict__ x, PlaneScales b,
-                                                    const double* __restrict__ y, PlaneScales c,
-                                                    const double* __restrict__ z, double* __restrict__ out) {
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r >= n) return;
-    const int plane = plane0 + (int)blockIdx.y;
-    const int64_t i = (int64_t)plane * n + r;
-    double v = plane_scale(a, plane) * x[i] + plane_scale(b, plane) * y[i];
-    if (z) v = v + plane_scale(c, plane) * z[i];
-    out[i] = v;
+// dst = a x + b P y + c P z over the planes, P the prolongation; x and z may be null
+__global__ void __launch_bounds__(kBlock) prolong_k(int plane0, int Lc, PlaneScales a, const double* __restrict__ px,
+                                                    PlaneScales b, const double* __restrict__ py, PlaneScales c,
+                                                    const double* __restrict__ pz, double* __restrict__ dst) {
+    const int L = 2 * Lc, plane = plane0 + (int)blockIdx.y;
+    const uint32_t r = blockIdx.x * kBlock + threadIdx.x;
+    if (r >= (uint32_t)L * (uint32_t)L) return;
+    const int y = (int)(r / (uint32_t)L), x = (int)(r - (uint32_t)y * (uint32_t)L);
+    const int64_t i = (int64_t)plane * L * L + r, o = (int64_t)plane * Lc * Lc;
+    double v = plane_scale(b, plane) * prolong_node(py + o, Lc, x, y);
+    if (px) v = plane_scale(a, plane) * px[i] + v;
+    if (pz) v = v + plane_scale(c, plane) * prolong_node(pz + o, Lc, x, y);
+    dst[i] = v;
 }
 
 __global__ void __launch_bounds__(kBlock) axpby_k(int64_t n, double a, const double* x, double b, const double* y,
@@ -338,6 +335,203 @@ __global__ void __launch_bounds__(kProjBlock) project_k(double* data, int L, int
     }
 }
 
+// The same projection by many workgroups per plane, in two launches with the partial
+// sums in a workspace between them.  project_sums_k: a workgroup of 16 wavefronts takes
+// 16 RPW rows (a wavefront's are 16 apart), sums each of them plainly and, for the low
+// modes, against cos / sin(kx x 2 pi / L), kx = 1, 2 (the modes are separable; a lane's
+// columns have one parity, so the (-1)^x sum is the plain one with the lanes' signs), and
+// writes its part of the (-1)^y column sums.  project_apply_k: the same rows again; every
+// workgroup adds the column parts (at most 32) and forms the plane sums from the row sums
+// by itself: a third launch for them cost more (24 us against 18 for four planes of 256^2
+// with low modes).  Fixed order as above.  Bound by latency, then by memory: four planes of
+// 256^2 take 8.4 us (30 with one workgroup each), 17.7 with low modes (52); of 1024^2
+// 35 and 52 (458 and 805).
+constexpr int kSplitParts = 32;
+__host__ __device__ constexpr int split_rows(int L) { return 16 * ((L + 16 * kSplitParts - 1) / (16 * kSplitParts)); }
+__host__ __device__ constexpr int split_parts(int L) { return (L + split_rows(L) - 1) / split_rows(L); }
+// doubles of a plane: row sums R[y], plain and (low modes) cos, sin, cos 2, sin 2; column parts
+__host__ __device__ constexpr int64_t split_work(int L, bool low) { return (int64_t)((low ? 6 : 2) + split_parts(L)) * L; }
+
+// columns per lane at a time of project_sums_k, within 128 registers
+__host__ __device__ constexpr int sums_columns(int rpw) { return rpw > 2 ? 2 : 4; }
+
+struct LowModes {
+    int8_t n, kx[kMaxLowModes], ky[kMaxLowModes];
+};
+
+// Rows y0, y0 + 16, ... of a plane, columns g + lane + 64 j
+template <int RPW, int J>
+__device__ __forceinline__ void project_load(const double* A, int L, int y0, int g, double (&v)[RPW][J]) {
+#pragma unroll
+    for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int y = y0 + 16 * i, x = g + ((int)threadIdx.x & 63) + 64 * j;
+            v[i][j] = y < L && x < L ? A[(int64_t)y * L + x] : 0.0;
+        }
+}
+
+template <int RPW, bool LOW>
+__global__ void __launch_bounds__(kProjBlock, RPW == 1 && !LOW ? 8 : 4) project_sums_k(const double* __restrict__ data, int L, double* __restrict__ work) {
+    extern __shared__ double lds[];
+    constexpr int J = sums_columns(RPW);
+    double* red = lds;                            // [kProjWaves][64 J]
+    double* ct = red + kProjWaves * 64 * J;       // with low modes: cos(2 pi m / L)
+    double* st = ct + L;                          //   sin(2 pi m / L)
+    const double* A = data + (int64_t)blockIdx.y * L * L;
+    double* rows = work + (int64_t)blockIdx.y * split_work(L, LOW);
+    double* part = rows + (int64_t)((LOW ? 6 : 2) + (int)blockIdx.x) * L;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int y0 = (int)blockIdx.x * 16 * RPW + wave;
+    double sum[RPW][LOW ? 5 : 1] = {};
+    for (int g = 0; g < L; g += 64 * J) {
+        double v[RPW][J], col[J] = {};
+        project_load(A, L, y0, g, v);
+        if constexpr (LOW)
+            if (g == 0) {   // behind the first loads
+                for (int m = threadIdx.x; m < L; m += kProjBlock) sincospi(2.0 * (double)m / (double)L, &st[m], &ct[m]);
+                __syncthreads();
+            }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int x = g + lane + 64 * j, xc = x < L ? x : 0, x2 = twiddle_index(2, xc, L);   // (columns past the end are zeros)
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) {
+                sum[i][0] += v[i][j];
+                col[j] += ((y0 + 16 * i) & 1) ? -v[i][j] : v[i][j];
+                if constexpr (LOW) {
+                    sum[i][1] += v[i][j] * ct[xc];
+                    sum[i][2] += v[i][j] * st[xc];
+                    sum[i][3] += v[i][j] * ct[x2];
+                    sum[i][4] += v[i][j] * st[x2];
+                }
+            }
+        }
+        if (g > 0) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < J; ++j) red[(wave * J + j) * 64 + lane] = col[j];
+        __syncthreads();
+        if (threadIdx.x < 64 * J && g + (int)threadIdx.x < L) {
+            double s = 0.0;
+            for (int w = 0; w < kProjWaves; ++w) s += red[w * 64 * J + threadIdx.x];
+            part[g + threadIdx.x] = s;
+        }
+    }
+    const double sx0 = (lane & 1) ? -1.0 : 1.0, inv = 1.0 / (double)L;   // x is even exactly when lane is
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+        const int y = y0 + 16 * i;
+        const double alt = wave_sum(sx0 * sum[i][0]) * inv;
+#pragma unroll
+        for (int c = 0; c < (LOW ? 5 : 1); ++c) sum[i][c] = wave_sum(sum[i][c]);
+        if (lane == 0 && y < L) {
+            rows[y] = alt;
+#pragma unroll
+            for (int c = 0; c < (LOW ? 5 : 1); ++c) rows[(int64_t)(1 + c) * L + y] = sum[i][c];
+        }
+    }
+}
+
+template <int RPW, bool LOW>
+__global__ void __launch_bounds__(kProjBlock, RPW == 1 ? 8 : 4) project_apply_k(double* __restrict__ data, int L, LowModes modes,
+                                                                                const double* __restrict__ work) {
+    extern __shared__ double lds[];
+    constexpr int J = RPW > 2 || LOW ? 2 : 4, ROWS = 16 * RPW;
+    double* cols = lds;                  // C[x]
+    double* fin = cols + L;              // [kProjSums] plane sums
+    double* coef = fin + kProjSums;      // with low modes: [5][ROWS] row coefficients a0 (with the mean), a1, b1, a2, b2
+    double* ct = coef + 5 * ROWS;        //   cos(2 pi m / L)
+    double* st = ct + L;                 //   sin(2 pi m / L)
+    double* A = data + (int64_t)blockIdx.y * L * L;
+    const double* rows = work + (int64_t)blockIdx.y * split_work(L, LOW);
+    const double* part = rows + (int64_t)(LOW ? 6 : 2) * L;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nparts = split_parts(L);
+    const int y0 = (int)blockIdx.x * ROWS + wave;
+    const double inv = 1.0 / (double)L;
+    double v[RPW][J];
+    project_load(A, L, y0, 0, v);
+    for (int x = threadIdx.x; x < L; x += kProjBlock) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int p = 0; p < nparts; ++p) s += part[(int64_t)p * L + x];
+        cols[x] = s * inv;
+    }
+    if constexpr (LOW) {
+        for (int m = kProjBlock - 1 - threadIdx.x; m < L; m += kProjBlock) sincospi(2.0 * (double)m / (double)L, &st[m], &ct[m]);
+        __syncthreads();
+    }
+    // plane sums, one per wave (the last waves first: the first ones have the columns): q = 0
+    // mean, 1 c, 2 + 2 i and 3 + 2 i the cos and sin coefficients of low mode i
+    for (int q = kProjWaves - 1 - wave; q < 2 + (LOW ? 2 * modes.n : 0); q += kProjWaves) {
+        double s = 0.0;
+        if (q < 2) {
+            for (int y = lane; y < L; y += 64) s += q == 0 ? rows[L + y] : ((y & 1) ? -rows[y] : rows[y]);
+        } else if constexpr (LOW) {
+            const int kx = modes.kx[(q - 2) >> 1], ky = modes.ky[(q - 2) >> 1];
+            const double* cx = rows + (int64_t)(kx == 0 ? 1 : 2 * kx) * L;   // sums against cos(kx x ..), sin(kx x ..)
+            const double* sn = rows + (int64_t)(2 * kx + 1) * L;
+            for (int y = lane; y < L; y += 64) {
+                const int t = twiddle_index(ky, y, L);
+                const double pc = cx[y], ps = kx == 0 ? 0.0 : sn[y];
+                s += (q & 1) ? ps * ct[t] + pc * st[t] : pc * ct[t] - ps * st[t];
+            }
+        }
+        s = wave_sum(s);
+        if (lane == 0) fin[q] = q == 0 ? s * inv * inv : (q == 1 ? s * inv : 2.0 * s * inv * inv);
+    }
+    __syncthreads();
+    const double mean = fin[0], cnn = fin[1];
+    if constexpr (LOW) {
+        if (threadIdx.x < ROWS) {
+            const int y = (int)blockIdx.x * ROWS + threadIdx.x;
+            double a0 = mean, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0;
+            for (int m = 0; m < modes.n; ++m) {
+                const int kx = modes.kx[m], t = twiddle_index(modes.ky[m], y < L ? y : 0, L);
+                const double mc = fin[2 + 2 * m], ms = fin[3 + 2 * m];
+                const double a = mc * ct[t] + ms * st[t], b = ms * ct[t] - mc * st[t];
+                if (kx == 0) {
+                    a0 += a;
+                } else if (kx == 1) {
+                    a1 += a;
+                    b1 += b;
+                } else {
+                    a2 += a;
+                    b2 += b;
+                }
+            }
+            coef[0 * ROWS + threadIdx.x] = a0;
+            coef[1 * ROWS + threadIdx.x] = a1;
+            coef[2 * ROWS + threadIdx.x] = b1;
+            coef[3 * ROWS + threadIdx.x] = a2;
+            coef[4 * ROWS + threadIdx.x] = b2;
+        }
+        __syncthreads();
+    }
+    const double sx0 = (lane & 1) ? -1.0 : 1.0;
+    for (int g = 0; g < L; g += 64 * J) {
+        if (g > 0) project_load(A, L, y0, g, v);
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const int y = y0 + 16 * i, r = wave + 16 * i;
+            if (y >= L) break;
+            const double sy = (y & 1) ? -1.0 : 1.0, ry = rows[y];
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int x = g + lane + 64 * j;
+                if (x < L) {
+                    double low = mean;
+                    if constexpr (LOW) {
+                        const int x2 = twiddle_index(2, x, L);
+                        low = coef[r] + coef[ROWS + r] * ct[x] + coef[2 * ROWS + r] * st[x] + coef[3 * ROWS + r] * ct[x2] +
+                              coef[4 * ROWS + r] * st[x2];
+                    }
+                    A[(int64_t)y * L + x] = v[i][j] - sx0 * ry - sy * (cols[x] - sx0 * cnn) - low;
+                }
+            }
+        }
+    }
+}
+
 struct Channels {
     lb_warm_channel c[LB_WARM_MAX_CHANNELS];
 };
@@ -485,14 +679,20 @@ int grid_for(int64_t total) {
 }
 
 constexpr int kMaxPlanes = 65535;   // of one launch (grid.y)
+// Lattices from which the split projection is taken, by size alone (a problem's result is
+// the same in every batch).  One workgroup per plane against split, 4 planes: 64^2 6.7 and
+// 6.5 us (launch-bound), 96^2 11.1 and 7.4.  With low modes, 4 and 64 planes: 128^2 19 and
+// 15, but 20 and 24; 192^2 38 and 17, 40 and 40; 256^2 52 and 18, 54 and 51.
+constexpr int split_min(bool low) { return low ? 192 : 66; }
 
 int done(hipError_t e) { return e == hipSuccess ? LB_OK : LB_EHIP; }
 
-int launch_prolong(const double* src, int planes, int Lc, const PlaneScales& scales, double* dst, hipStream_t s) {
+int launch_prolong(int planes, int Lc, const PlaneScales& a, const double* x, const PlaneScales& b, const double* y,
+                   const PlaneScales& c, const double* z, double* dst, hipStream_t s) {
     const unsigned blocks = ((unsigned)(2 * Lc) * (unsigned)(2 * Lc) + kBlock - 1) / kBlock;
     for (int p0 = 0; p0 < planes; p0 += kMaxPlanes)
-        hipLaunchKernelGGL(prolong_k, dim3(blocks, (unsigned)std::min(kMaxPlanes, planes - p0)), dim3(kBlock), 0, s, src, p0,
-                           Lc, scales, dst);
+        hipLaunchKernelGGL(prolong_k, dim3(blocks, (unsigned)std::min(kMaxPlanes, planes - p0)), dim3(kBlock), 0, s, p0, Lc, a,
+                           x, b, y, c, z, dst);
     return done(hipGetLastError());
 }
 
@@ -517,27 +717,16 @@ int lb_warm_restrict(const double* src, int32_t planes, int32_t L, double scale,
 
 int lb_warm_prolong(const double* src, int32_t planes, int32_t Lc, double scale, double* dst, void* stream) {
     if (!src || !dst || planes < 1 || Lc < 2 || 2 * Lc > LB_WARM_MAX_L) return LB_EINVAL;
-    return launch_prolong(src, planes, Lc, PlaneScales{{scale, scale, scale}, 0}, dst, (hipStream_t)stream);
+    const PlaneScales one{{scale, scale, scale}, 0}, none{};
+    return launch_prolong(planes, Lc, none, nullptr, one, src, none, nullptr, dst, (hipStream_t)stream);
 }
 
-int lb_warm_prolong_fields(const double* src, int32_t batch, int32_t Lc, const double scales[3], double* dst,
-                           void* stream) {
-    if (!src || !dst || !scales || batch < 1 || batch > (1 << 28) || Lc < 2 || 2 * Lc > LB_WARM_MAX_L) return LB_EINVAL;
-    return launch_prolong(src, 4 * batch, Lc, PlaneScales{{scales[0], scales[1], scales[2]}, batch}, dst, (hipStream_t)stream);
-}
-
-int lb_warm_combine_fields(int32_t batch, int64_t n, const double a[3], const double* x, const double b[3],
-                           const double* y, const double c[3], const double* z, double* out, void* stream) {
-    if (batch < 1 || batch > (1 << 28) || n < 1 || n > (int64_t)LB_WARM_MAX_L * LB_WARM_MAX_L || !a || !x || !b || !y ||
-        (z && !c) || !out)
+int lb_warm_prolong_fields(int32_t batch, int32_t Lc, const double a[3], const double* x, const double b[3], const double* y,
+                           const double c[3], const double* z, double* dst, void* stream) {
+    if (batch < 1 || batch > (1 << 28) || Lc < 2 || 2 * Lc > LB_WARM_MAX_L || (x && !a) || !b || !y || (z && !c) || !dst)
         return LB_EINVAL;
-    const PlaneScales pa{{a[0], a[1], a[2]}, batch}, pb{{b[0], b[1], b[2]}, batch};
-    PlaneScales pc{{0.0, 0.0, 0.0}, batch};
-    if (z) pc = PlaneScales{{c[0], c[1], c[2]}, batch};
-    for (int p0 = 0; p0 < 4 * batch; p0 += kMaxPlanes)
-        hipLaunchKernelGGL(combine_k, dim3((unsigned)((n + kBlock - 1) / kBlock), (unsigned)std::min(kMaxPlanes, 4 * batch - p0)),
-                           dim3(kBlock), 0, (hipStream_t)stream, n, p0, pa, x, pb, y, pc, z, out);
-    return done(hipGetLastError());
+    auto scales = [&](const double* s) { return s ? PlaneScales{{s[0], s[1], s[2]}, batch} : PlaneScales{}; };
+    return launch_prolong(4 * batch, Lc, scales(a), x, scales(b), y, scales(c), z, dst, (hipStream_t)stream);
 }
 
 int lb_warm_axpby(int64_t n, double a, const double* x, double b, const double* y, double* out, void* stream) {
@@ -547,29 +736,39 @@ int lb_warm_axpby(int64_t n, double a, const double* x, double b, const double* 
     return done(hipGetLastError());
 }
 
-int lb_warm_project(double* data, int32_t planes, int32_t L, int32_t k2max, void* stream) {
-    if (!data || planes < 1 || L < 2 || L > LB_WARM_MAX_L || (L & 1)) return LB_EINVAL;
-    if (k2max < 0 || k2max > LB_WARM_MAX_K2) return LB_EINVAL;
-    // one mode of each +-k pair: kx > 0, or kx = 0 and ky > 0; |k| far below the Nyquist lines
-    int m[2 * kMaxLowModes] = {0};
-    int n = 0;
+// The half plane's low modes (one of each +-k pair: kx > 0, or kx = 0 and ky > 0); LB_EINVAL
+// for arguments that a projection refuses.
+static int low_modes(int planes, int L, int k2max, LowModes* m) {
+    if (planes < 1 || L < 2 || L > LB_WARM_MAX_L || (L & 1) || k2max < 0 || k2max > LB_WARM_MAX_K2) return LB_EINVAL;
+    *m = LowModes{};
     for (int kx = 0; kx * kx <= k2max; ++kx)
         for (int ky = -3; ky <= 3; ++ky) {
             if (kx * kx + ky * ky == 0 || kx * kx + ky * ky > k2max) continue;
             if (kx == 0 && ky <= 0) continue;
-            if (2 * kx >= L || 2 * (ky < 0 ? -ky : ky) >= L) return LB_EINVAL;
-            m[2 * n] = kx;
-            m[2 * n + 1] = ky;
-            ++n;
+            if (2 * kx >= L || 2 * (ky < 0 ? -ky : ky) >= L) return LB_EINVAL;   // |k| far below the Nyquist lines
+            m->kx[m->n] = (int8_t)kx;
+            m->ky[m->n++] = (int8_t)ky;
         }
+    return LB_OK;
+}
+
+int lb_warm_project(double* data, int32_t planes, int32_t L, int32_t k2max, void* stream) {
+    LowModes low;
+    if (!data || low_modes(planes, L, k2max, &low) != LB_OK) return LB_EINVAL;
+    const int n = low.n;
+    int m[2 * kMaxLowModes] = {0};
+    for (int i = 0; i < n; ++i) {
+        m[2 * i] = low.kx[i];
+        m[2 * i + 1] = low.ky[i];
+    }
     const size_t lds = project_lds_bytes(L, n);
     const int4 ma = make_int4(m[0], m[1], m[2], m[3]), mb = make_int4(m[4], m[5], m[6], m[7]),
                mc = make_int4(m[8], m[9], m[10], m[11]), md = make_int4(m[12], m[13], m[14], m[15]),
                me = make_int4(m[16], m[17], m[18], m[19]), mf = make_int4(m[20], m[21], m[22], m[23]);
     const int J = project_columns(L, n);
     auto plain = J == 1 ? project_k<1, false> : J == 2 ? project_k<2, false> : project_k<4, false>;
-    auto low = J == 1 ? project_k<1, true> : project_k<2, true>;
-    auto kernel = n > 0 ? low : plain;
+    auto with_low = J == 1 ? project_k<1, true> : project_k<2, true>;
+    auto kernel = n > 0 ? with_low : plain;
     if (lds > 65536) {   // the largest lattices need more than the default dynamic LDS limit
         const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return LB_EHIP;
@@ -577,6 +776,41 @@ int lb_warm_project(double* data, int32_t planes, int32_t L, int32_t k2max, void
     hipLaunchKernelGGL(kernel, dim3(planes), dim3(kProjBlock), lds, (hipStream_t)stream, data, (int)L, n, ma, mb, mc,
                        md, me, mf);
     return done(hipGetLastError());
+}
+
+int64_t lb_warm_project_work(int32_t planes, int32_t L, int32_t k2max) {
+    LowModes low;
+    if (low_modes(planes, L, k2max, &low) != LB_OK || L < split_min(low.n > 0) || planes > kMaxPlanes) return 0;
+    return planes * split_work(L, low.n > 0);
+}
+
+int lb_warm_project_split(double* data, int32_t planes, int32_t L, int32_t k2max, double* work, void* stream) {
+    LowModes low;
+    if (!data || !work || low_modes(planes, L, k2max, &low) != LB_OK || lb_warm_project_work(planes, L, k2max) == 0)
+        return LB_EINVAL;
+    const int rpw = split_rows(L) / 16;
+    const dim3 grid((unsigned)split_parts(L), (unsigned)planes), block(kProjBlock);
+    const hipStream_t st = (hipStream_t)stream;
+    static_assert((kProjWaves * 64 * 4 + 2 * LB_WARM_MAX_L) * sizeof(double) <= 65536, "default dynamic LDS");
+    static_assert((3 * LB_WARM_MAX_L + kProjSums + 5 * 64) * sizeof(double) <= 65536, "default dynamic LDS");
+    static_assert(split_rows(LB_WARM_MAX_L) <= 64, "at most four rows per wavefront");
+    const int table = low.n > 0 ? 2 * L : 0;
+    const size_t lds_sums = (kProjWaves * 64 * sums_columns(rpw) + table) * sizeof(double);
+    const size_t lds_apply = (L + kProjSums + 5 * 16 * rpw + table) * sizeof(double);
+    auto launch = [&](auto sums, auto apply) {
+        hipLaunchKernelGGL(sums, grid, block, lds_sums, st, data, (int)L, work);
+        hipLaunchKernelGGL(apply, grid, block, lds_apply, st, data, (int)L, low, work);
+        return done(hipGetLastError());
+    };
+    if (low.n > 0)
+        return rpw == 1 ? launch(project_sums_k<1, true>, project_apply_k<1, true>)
+             : rpw == 2 ? launch(project_sums_k<2, true>, project_apply_k<2, true>)
+             : rpw == 3 ? launch(project_sums_k<3, true>, project_apply_k<3, true>)
+                        : launch(project_sums_k<4, true>, project_apply_k<4, true>);
+    return rpw == 1 ? launch(project_sums_k<1, false>, project_apply_k<1, false>)
+         : rpw == 2 ? launch(project_sums_k<2, false>, project_apply_k<2, false>)
+         : rpw == 3 ? launch(project_sums_k<3, false>, project_apply_k<3, false>)
+                    : launch(project_sums_k<4, false>, project_apply_k<4, false>);
 }
 
 static int channels_of(const lb_warm_channel* in, int32_t nc, bool unpack, Channels* out) {

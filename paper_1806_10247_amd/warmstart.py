@@ -137,15 +137,36 @@ class Fields:
     def __init__(self, L, B, rho=None, u=None, phi=None):
         n = B * L * L
         self.L, self.B = L, B
-        self.buf = None
+        self.buf = self._parts = None
         if rho is None and u is None and phi is None:
             # one allocation, planes in the order rho, u_x, u_y, phi: plane-wise
             # operations on all fields are one launch
             self.buf = _empty(4 * n)
-            rho, u, phi = self.buf[:n], self.buf[n:3 * n], self.buf[3 * n:]
-        self.rho = rho if rho is not None else _empty(n)
-        self.u = u if u is not None else _empty(2 * n)
-        self.phi = phi if phi is not None else _empty(n)
+        else:
+            self._parts = (rho if rho is not None else _empty(n), u if u is not None else _empty(2 * n),
+                           phi if phi is not None else _empty(n))
+
+    def _part(self, i):
+        if self._parts is None:   # most fields are only passed on whole
+            n = self.B * self.L * self.L
+            self._parts = (self.buf[:n], self.buf[n:3 * n], self.buf[3 * n:])
+        return self._parts[i]
+
+    def _replace(self, i, a):
+        self._part(i)
+        if self._parts[i] is not a:
+            self._parts, self.buf = self._parts[:i] + (a,) + self._parts[i + 1:], None
+
+    rho = property(lambda self: self._part(0), lambda self, a: self._replace(0, a))
+    u = property(lambda self: self._part(1), lambda self, a: self._replace(1, a))
+    phi = property(lambda self: self._part(2), lambda self, a: self._replace(2, a))
+
+    def addresses(self):
+        """Of rho, u and phi."""
+        if self.buf is None:
+            return tuple(a.data_ptr() for a in self._parts)
+        n, p = self.B * self.L * self.L, self.buf.data_ptr()
+        return p, p + 8 * n, p + 24 * n
 
     def planes(self):
         return ((self.rho, self.B), (self.u, 2 * self.B), (self.phi, self.B))
@@ -155,20 +176,16 @@ class Fields:
         run over all 4 B planes for Fields that own one allocation."""
         return ((self.buf, 4 * self.B),) if self.buf is not None else self.planes()
 
-    def whole(self):
-        """The one allocation, if rho, u and phi are (still) its parts, else None."""
-        n = self.B * self.L * self.L
-        if self.buf is None:
-            return None
-        base = self.buf.data_ptr()
-        parts = (self.rho.data_ptr(), self.u.data_ptr(), self.phi.data_ptr())
-        return self.buf if parts == (base, base + 8 * n, base + 24 * n) else None
-
     def project(self, k2max=0):
         """Means and Nyquist lines (and the modes 0 < |k|^2 <= k2max) removed from
         every plane, in place."""
         for a, p in self.spans():
-            C.lb_warm_project(_ptr(a), p, self.L, k2max, _stream())
+            n = C.lb_warm_project_work(p, self.L, k2max)
+            if n:
+                work = _empty(n)
+                C.lb_warm_project_split(_ptr(a), p, self.L, k2max, _ptr(work), _stream())
+            else:
+                C.lb_warm_project(_ptr(a), p, self.L, k2max, _stream())
         return self
 
     @classmethod
@@ -191,11 +208,23 @@ _LEVEL_SCALE = (0.25, 0.5, 1.0)
 def prolong(f):
     """Fields on the 2L lattice from those on L, rescaled (u/2, (rho - .)/4)."""
     g = Fields(2 * f.L, f.B)
-    if f.whole() is not None:
-        C.lb_warm_prolong_fields(_ptr(f.buf), f.B, f.L, _LEVEL_SCALE, _ptr(g.buf), _stream())
+    if f.buf is not None:
+        C.lb_warm_prolong_fields(f.B, f.L, None, None, _LEVEL_SCALE, _ptr(f.buf), None, None, _ptr(g.buf), _stream())
         return g
     for (a, p), (b, _), s in zip(f.planes(), g.planes(), _LEVEL_SCALE):
         C.lb_warm_prolong(_ptr(a), p, f.L, s, _ptr(b), _stream())
+    return g
+
+
+def _combine_prolonged(a, x, b, y, c=None, z=None):
+    """a x + b P y + c P z in one launch, new Fields (P the rescaled prolongation, a, b, c per
+    field); None where the storage or the lattices do not allow it."""
+    if any(f.buf is None for f in (x, y, z) if f is not None) or \
+            any(2 * f.L != x.L or f.B != x.B for f in (y, z) if f is not None):
+        return None
+    g = Fields(x.L, x.B)
+    b, c = ([s * v for s, v in zip(_LEVEL_SCALE, w)] if w else None for w in (b, c))
+    C.lb_warm_prolong_fields(x.B, y.L, a, _ptr(x.buf), b, _ptr(y.buf), c, _ptr(z.buf) if z else None, _ptr(g.buf), _stream())
     return g
 
 
@@ -214,13 +243,11 @@ def extrapolate(f1, f2, w=RICHARDSON):
     number.  w = 1/3 is Richardson's: the leading error, proportional to dx^2,
     is four times larger in f2.  Densities may carry any constant; remove it
     later."""
+    ws = _weights(w)
+    g = _combine_prolonged([1.0 + v for v in ws], f1, [-v for v in ws], f2)
+    if g is not None:
+        return g
     g = prolong(f2)
-    if f1.whole() is not None:
-        w = _weights(w)
-        o = Fields(f1.L, f1.B)
-        C.lb_warm_combine_fields(f1.B, f1.L * f1.L, [1.0 + v for v in w], _ptr(f1.buf), [-v for v in w], _ptr(g.buf),
-                                 None, None, _ptr(o.buf), _stream())
-        return o
     for (a, _), (b, _), wi in zip(f1.planes(), g.planes(), _weights(w)):
         C.lb_warm_axpby(a.numel(), 1.0 + wi, _ptr(a), -wi, _ptr(b), _ptr(b), _stream())
     return g
@@ -235,14 +262,13 @@ def extrapolate3(f1, f2, f3, a, b):
     half- and quarter-size lattices, P the rescaled prolongation), per field
     (density, velocity, scalar) or one number each: the two-level combination
     plus a share b of the next coarser difference.  b = 0 is extrapolate()."""
-    p2 = prolong(f2)
-    p3 = prolong(prolong(f3))
-    g = Fields(f1.L, f1.B)
-    if f1.whole() is not None:
-        a, b = _weights(a), _weights(b)
-        C.lb_warm_combine_fields(f1.B, f1.L * f1.L, [1.0 + v for v in a], _ptr(f1.buf), [w - v for v, w in zip(a, b)],
-                                 _ptr(p2.buf), [-v for v in b], _ptr(p3.buf), _ptr(g.buf), _stream())
+    p3 = prolong(f3)
+    av, bv = _weights(a), _weights(b)
+    g = _combine_prolonged([1.0 + v for v in av], f1, [w - v for v, w in zip(av, bv)], f2, [-v for v in bv], p3)
+    if g is not None:
         return g
+    p2, p3 = prolong(f2), prolong(p3)
+    g = Fields(f1.L, f1.B)
     for (x, _), (y, _), (z, _), (o, _), ai, bi in zip(f1.planes(), p2.planes(), p3.planes(), g.planes(),
                                                       _weights(a), _weights(b)):
         C.lb_warm_axpby(x.numel(), 1.0 + ai, _ptr(x), bi - ai, _ptr(y), _ptr(o), _stream())
@@ -369,8 +395,9 @@ _OUT_SCALE = (RES * U0, RES * U0, RES * PHI0, RES * RHO0)   # u_x, u_y, phi, rho
 
 def _out_channels(guess, est, scales=None):
     n = guess.B * guess.L * guess.L
-    srcs = (_ptr(guess.u), _ptr(guess.u) + 8 * n, _ptr(guess.phi), _ptr(guess.rho))
-    dsts = (_ptr(est.u), _ptr(est.u) + 8 * n, _ptr(est.phi), _ptr(est.rho))
+    (rho, u, phi), (rho_out, u_out, phi_out) = guess.addresses(), est.addresses()
+    srcs = (u, u + 8 * n, phi, rho)
+    dsts = (u_out, u_out + 8 * n, phi_out, rho_out)
     return [dict(src=a, dst=b, scale=s) for a, b, s in zip(srcs, dsts, scales or _OUT_SCALE)]
 
 
@@ -398,9 +425,9 @@ def level_differences(f1, f2, f3):
     prolongation and projection are linear, each difference is taken on the
     coarser lattice and prolonged once: h - q = P (f1 - P f2), q - o =
     P P (f2 - P f3), then projected."""
-    d1 = prolong(_combine(1.0, f1, -1.0, prolong(f2))).project()
-    d2 = prolong(prolong(_combine(1.0, f2, -1.0, prolong(f3)))).project()
-    return d1, d2
+    one = (1.0, 1.0, 1.0), (-1.0, -1.0, -1.0)
+    e1, e2 = (_combine_prolonged(one[0], f, one[1], c) or _combine(1.0, f, -1.0, prolong(c)) for f, c in ((f1, f2), (f2, f3)))
+    return prolong(e1).project(), prolong(prolong(e2)).project()
 
 
 def features_levels(probs, d1, d2, scales, out):
@@ -415,8 +442,9 @@ def features_levels(probs, d1, d2, scales, out):
           dict(src=None, offset=(probs.nu - RATE_MID) / RATE_HALF),
           dict(src=None, offset=(probs.D - RATE_MID) / RATE_HALF)]
     for d, sc in ((d1, scales[:4]), (d2, scales[4:])):
-        ch += [dict(src=_ptr(d.u), scale=1.0 / sc[0]), dict(src=_ptr(d.u) + 8 * n, scale=1.0 / sc[1]),
-               dict(src=_ptr(d.phi), scale=1.0 / sc[2]), dict(src=_ptr(d.rho), scale=1.0 / sc[3])]
+        rho, u, phi = d.addresses()
+        ch += [dict(src=u, scale=1.0 / sc[0]), dict(src=u + 8 * n, scale=1.0 / sc[1]),
+               dict(src=phi, scale=1.0 / sc[2]), dict(src=rho, scale=1.0 / sc[3])]
     C.lb_warm_pack(ch, probs.B, probs.L * probs.L, _ptr(out), _stream())
     return out
 
@@ -491,8 +519,8 @@ def initial_state(probs, est, rho0=1.0, zero_momentum=True):
     half-forced moments are the estimate (j = rho u - F/2, phi - S/2), with the
     total half-forced momentum of a start from rest (zero) when zero_momentum."""
     out = Fields(est.L, est.B)
-    C.lb_warm_initial_state(_ptr(est.rho), _ptr(est.u), _ptr(est.phi), _ptr(probs.F), _ptr(probs.S), est.B,
-                            est.L * est.L, rho0, zero_momentum, _ptr(out.rho), _ptr(out.u), _ptr(out.phi), _stream())
+    C.lb_warm_initial_state(*est.addresses(), _ptr(probs.F), _ptr(probs.S), est.B, est.L * est.L, rho0, zero_momentum,
+                            *out.addresses(), _stream())
     return out
 
 
