@@ -401,7 +401,8 @@ int lb_stream_bench(void* dst, const void* src, size_t bytes, int32_t mode, int3
  * captured HIP graph): workgroups take domains from a work queue and step
  * each to its steady residual r = ||u^n - u^{n-K}|| / (K ||u^n||) < tol
  * (half-forced velocity, float64 reduction), keeping a domain in LDS when its
- * two population buffers fit; finished domains retire.
+ * population buffers fit and stepping a larger one through LDS, several steps
+ * per pass over its memory; finished domains retire.
  */
 typedef struct lb_batch lb_batch;
 
@@ -421,8 +422,8 @@ typedef struct lb_batch_config {
     double omega_bulk, omega_third, omega_fourth;  /* in (0, 2), as lb_config */
     void* stream;            /* hipStream_t; NULL: the batch creates its own    */
     int32_t block;           /* threads per workgroup (64..1024, multiple of 64); 0 = 512 */
-    int32_t lds_policy;      /* 0: LDS-resident domains where they fit; 1: never */
-    int32_t lds_bytes;       /* LDS per workgroup for resident domains; 0 = auto */
+    int32_t lds_policy;      /* 0: domains in or through LDS where they fit; 1: never */
+    int32_t lds_bytes;       /* LDS per workgroup for that; 0 = auto            */
     int32_t routed;          /* 0..ndomains: the domains of longest expected
                                 time in the persistent launch (the steps their
                                 slowest mode needs times a step's time on one

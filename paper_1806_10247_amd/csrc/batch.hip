@@ -6,15 +6,18 @@
 // Each workgroup takes domains from a work queue (one global atomic counter)
 // and runs a domain to completion by itself: domains are independent, so the
 // only synchronisation between time steps is a workgroup barrier.  A domain
-// whose two population buffers fit in the workgroup's LDS is copied in once,
-// stepped entirely in LDS and copied back; a larger one is stepped in its two
-// global-memory buffers.  Every K steps the workgroup reduces the residual
+// that fits in the workgroup's LDS is copied in once, stepped entirely in LDS (in
+// place if its threads can hold what they pull, else between two buffers) and
+// copied back; a larger one is stepped in its two global-memory buffers, several
+// steps per sweep where LDS holds the states between them.  Every K steps the workgroup reduces the residual
 // r = ||u^n - u^{n-K}|| / (K ||u^n||) of the half-forced velocity and stops
 // the domain when r < tol, when u did not change at all in K steps (storage
 // precision reached), at max_steps, or on a non-finite value.  Finished
 // domains retire; when the queue is empty every wave of the grid exits.
 #include <hip/hip_runtime.h>
 #include <math.h>
+
+#include <type_traits>
 
 #include "batch.hpp"
 #include "lattice.hpp"
@@ -23,29 +26,48 @@ namespace casclb {
 
 namespace {
 
-template <class T>
-__device__ __forceinline__ T bld(const T* p) {
-    return *p;
+// Where a thread's node lies and what it pulls from: element offsets into one
+// [9][n] buffer.  A link whose source lies in a wall (both y ends) returns the
+// node's own opposite population; x is periodic.
+struct NodePos {
+    uint32_t node;
+    bool lo, hi;        // next to the lower / upper wall
+    uint32_t xm, xp;    // the node's index with x - 1, x + 1 (wrapped, mod 2^32)
+};
+__device__ __forceinline__ NodePos node_pos(uint32_t node, int x, int y, int nx, int ny) {
+    return {node, y == 0, y == ny - 1, x == 0 ? node + (uint32_t)nx - 1u : node - 1u,
+            x == nx - 1 ? node - (uint32_t)nx + 1u : node + 1u};
+}
+template <int A>
+__device__ __forceinline__ uint32_t pull_index(const NodePos& p, uint32_t n, uint32_t nx) {
+    constexpr int EX = Flow<2>::velocity(A, 0), EY = Flow<2>::velocity(A, 1);
+    const uint32_t at = EX == 0 ? p.node : (EX > 0 ? p.xm : p.xp);
+    if constexpr (EY == 0) return A * n + at;
+    else return (EY > 0 ? p.lo : p.hi) ? Flow<2>::opposite(A) * n + p.node : A * n + at - EY * nx;
 }
 
-// One D2Q9 node of one domain: pull from `src` ([9][n] deviations, order of
-// eq. 15), implicit Lorentz half step, collision, store into `dst`.
-// Returns the half-forced velocity.
+// The element at a 32-bit byte or element offset (a domain's buffer is at most 2^20 x 9 values).
+template <class T>
+__device__ __forceinline__ T& at_byte(T* base, uint32_t i) {
+    using B = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return *reinterpret_cast<T*>(reinterpret_cast<B*>(base) + i);
+}
+template <class T>
+__device__ __forceinline__ T& element(T* base, uint32_t i) {
+    return at_byte(base, i * (uint32_t)sizeof(T));
+}
+
+// Implicit Lorentz half step and collision of one D2Q9 node: raw (order of eq.
+// 15) holds the streamed deviations, out receives the ones to store.  Returns the
+// half-forced velocity.
 template <class Real, class Store>
-__device__ __forceinline__ void batch_node(const Store* src, Store* dst, int n, int nx, int ny, int x, int y,
-                                           const BatchParams& bp, const BatchDomain& dom, Real (&u)[3]) {
+__device__ __forceinline__ void batch_collide(const Store (&raw)[9], const BatchParams& bp, const BatchDomain& dom,
+                                              Store (&out)[9], Real (&u)[3]) {
     constexpr int Q = 9;
-    const int node = x + nx * y;
-    const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
     Real m[Q];
     static_for<Q>([&](auto aa) {
         constexpr int A = decltype(aa)::value;
-        constexpr int EX = Flow<2>::velocity(A, 0), EY = Flow<2>::velocity(A, 1);
-        const int sy = y - EY;
-        const bool wall = sy < 0 || sy >= ny;  // walls on both y ends
-        const int sx = EX == 0 ? x : (EX > 0 ? xm : xp);
-        const int idx = wall ? Flow<2>::opposite(A) * n + node : A * n + sx + nx * sy;
-        m[Flow<2>::grid_of(A)] = static_cast<Real>(bld(src + idx));
+        m[Flow<2>::grid_of(A)] = static_cast<Real>(raw[A]);
     });
     // implicit half step of the velocity-dependent force:
     // rho u_x = j_x + (F_b - s u_x)/2, the step's force is F_b - s u_x
@@ -65,7 +87,56 @@ __device__ __forceinline__ void batch_node(const Store* src, Store* dst, int n, 
     collide_flow<2, Real>(m, Real(bp.rho0), f, f, w, rho_out, u);
     static_for<Q>([&](auto aa) {
         constexpr int A = decltype(aa)::value;
-        dst[A * n + node] = static_cast<Store>(m[Flow<2>::grid_of(A)]);
+        out[A] = static_cast<Store>(m[Flow<2>::grid_of(A)]);
+    });
+}
+
+template <class Store>
+__device__ __forceinline__ void batch_pull(const Store* src, const NodePos& p, uint32_t n, uint32_t nx, Store (&raw)[9]) {
+    static_for<9>([&](auto aa) {
+        constexpr int A = decltype(aa)::value;
+        raw[A] = element(src, pull_index<A>(p, n, nx));
+    });
+}
+
+// The same from global memory: every population plane's base is uniform (scalar
+// registers), so a node's byte offsets are all the vector arithmetic: 26 instructions
+// with the loop's own instead of 53.  Opposites of the links that move along y are two
+// planes apart, which makes one base serve a link's source and its wall value.
+template <class Store>
+__device__ __forceinline__ void batch_pull_global(const Store* src, uint32_t node, uint32_t x, uint32_t n, uint32_t nx,
+                                                  Store (&raw)[9]) {
+    constexpr uint32_t B = sizeof(Store);
+    const uint32_t at = B * node, up = B * (2u * n + nx);
+    const uint32_t xm = at + (x == 0u ? B * (nx - 1u) : 0u - B), xp = at + (x == nx - 1u ? 0u - B * (nx - 1u) : B);
+    const bool lo = node < nx, hi = node >= n - nx;
+    static_for<9>([&](auto aa) {
+        constexpr int A = decltype(aa)::value;
+        constexpr int EX = Flow<2>::velocity(A, 0), EY = Flow<2>::velocity(A, 1);
+        const uint32_t from = EX == 0 ? at : (EX > 0 ? xm : xp);
+        if constexpr (EY == 0) {
+            raw[A] = at_byte(src + A * (int64_t)n, from);
+        } else if constexpr (EY > 0) {
+            static_assert(Flow<2>::opposite(A) == A + 2);
+            raw[A] = at_byte(src + (A * (int64_t)n - nx), lo ? at + up : from);
+        } else {
+            static_assert(Flow<2>::opposite(A) == A - 2);
+            raw[A] = at_byte(src + (A - 2) * (int64_t)n, hi ? at : from + up);
+        }
+    });
+}
+
+// One D2Q9 node of one domain from `src` to `dst` ([9][n] deviations).
+template <class Real, class Store>
+__device__ __forceinline__ void batch_node(const Store* src, Store* dst, int n, int nx, int ny, int x, int y,
+                                           const BatchParams& bp, const BatchDomain& dom, Real (&u)[3]) {
+    const uint32_t node = (uint32_t)(x + nx * y);
+    Store raw[9], out[9];
+    batch_pull(src, node_pos(node, x, y, nx, ny), (uint32_t)n, (uint32_t)nx, raw);
+    batch_collide<Real, Store>(raw, bp, dom, out, u);
+    static_for<9>([&](auto aa) {
+        constexpr int A = decltype(aa)::value;
+        element(dst, (uint32_t)A * (uint32_t)n + node) = out[A];
     });
 }
 
@@ -92,12 +163,125 @@ __device__ __forceinline__ void wg_sum2(double& a, double& b, double* red) {
     }
 }
 
-// Runs one domain to completion with buffers `b0` (holding the state) and
-// `b1`; returns which of the two holds the final state.
+// A node's share of the residual check.
+struct CheckSums {
+    double du2 = 0.0, u2 = 0.0;
+    bool finite = true;
+    template <class Real>
+    __device__ __forceinline__ void add(const Real (&u)[3], Real* uprev, uint32_t node, uint32_t n) {
+        const double ux = (double)u[0], uy = (double)u[1];
+        const double ox = (double)uprev[node], oy = (double)uprev[n + node];
+        uprev[node] = u[0];
+        uprev[n + node] = u[1];
+        du2 += (ux - ox) * (ux - ox) + (uy - oy) * (uy - oy);
+        u2 += ux * ux + uy * uy;
+        finite = finite && isfinite(ux) && isfinite(uy);
+    }
+};
+
+// The stop decision after a check step (0: go on), from every thread's sums.
+__device__ __forceinline__ int check_stop(CheckSums c, bool& have_prev, double& res, const BatchParams& bp, double* red) {
+    double bad = c.finite ? 0.0 : 1.0, unused = 0.0;
+    wg_sum2(c.du2, c.u2, red);
+    wg_sum2(bad, unused, red + 64);
+    int stop = 0;
+    if (bad > 0.0) {
+        stop = kBatchNonFinite;
+    } else if (have_prev) {
+        res = sqrt(c.du2) / ((double)bp.check_interval * sqrt(c.u2));
+        if (c.du2 == 0.0)
+            stop = kBatchStationary;
+        else if (res < bp.tol)
+            stop = kBatchConverged;
+    }
+    have_prev = true;
+    // Every lane holds the same sums; broadcasting the decision from lane 0
+    // makes the loop exit a scalar branch.  Left as a per-lane value the
+    // compiler may build an exec-mask loop around the barriers that re-runs
+    // without the work-queue atomic of the enclosing loop (a hang).
+    return __builtin_amdgcn_readfirstlane(stop);
+}
+
+// kBatchFused steps of a domain in global memory in one sweep over it, the states
+// between them in LDS rings.  Step k of the sweep is 2 nx nodes behind step k - 1, whose
+// last kBatchRing nodes its ring holds: a pull reaches at most 2 nx - 1 nodes (a row and
+// the wrap along x), so blockDim.x + 4 nx nodes must fit.  Every node is stepped
+// once, so one read and one write of the state serve all the steps; the same
+// arithmetic on the same values as one step at a time.  One barrier between a step and the
+// next covers both hazards from three steps on: a ring is overwritten two barriers after
+// it was read; with two steps one more is needed.
+//
+// One step at a time, 256 workgroups' domains overflow the caches and run at the memory's
+// rate: 512 float domains of 4-64 x 16-256 nodes, 200 steps, 6.8 ms = 5 TB/s.  In
+// sweeps 5.0 ms, of which the largest domain (16,384 nodes, started first) takes 4.6 on its
+// CU, bound by vector arithmetic.  129 such domains, whose states the caches hold: 3.9 and
+// 4.1 ms; 149 double ones: 7.0 and 5.7.
 template <class Real, class Store>
-__device__ int run_domain(Store* b0, Store* b1, Real* uprev, const BatchParams& bp, const BatchDomain& dom,
+__device__ __forceinline__ void batch_sweep(const Store* cur, Store* nxt, Store* rings, uint32_t x, uint32_t n, uint32_t nx,
+                                            const BatchParams& bp, const BatchDomain& dom) {
+    constexpr uint32_t T = batch_fused<Real>, M = kBatchRing - 1, B = sizeof(Store);
+    const uint32_t threads = blockDim.x, dx = threads % nx;
+    Store raw[9];
+    if (threadIdx.x < n) batch_pull_global<Store>(cur, threadIdx.x, x, n, nx, raw);
+    for (uint32_t base = 0; base < n + (T - 1) * 2u * nx; base += threads) {
+        const uint32_t node = base + threadIdx.x, x_now = x;
+        Store now[9], out[9];
+        Real u[3];
+        static_for<9>([&](auto aa) { now[decltype(aa)::value] = raw[decltype(aa)::value]; });
+        x += dx;
+        x = min(x, x - nx);   // less nx where x >= nx (unsigned)
+        if (node + threads < n) batch_pull_global<Store>(cur, node + threads, x, n, nx, raw);
+        if (node < n) {
+            batch_collide<Real, Store>(now, bp, dom, out, u);
+            static_for<9>([&](auto aa) {
+                constexpr int A = decltype(aa)::value;
+                rings[A * kBatchRing + (node & M)] = out[A];
+            });
+        }
+        for (uint32_t k = 1; k < T; ++k) {
+            __syncthreads();
+            const Store* from = rings + (k - 1) * 9u * kBatchRing;
+            const uint32_t at = node - k * 2u * nx;   // (before the domain's first node: past its last, mod 2^32)
+            if (at < n) {
+                const uint32_t xm = at + (x_now == 0u ? nx - 1u : 0u - 1u), xp = at + (x_now == nx - 1u ? 0u - (nx - 1u) : 1u);
+                const bool lo = at < nx, hi = at >= n - nx;
+                static_for<9>([&](auto aa) {
+                    constexpr int A = decltype(aa)::value;
+                    constexpr int EX = Flow<2>::velocity(A, 0), EY = Flow<2>::velocity(A, 1);
+                    const uint32_t src = (EX == 0 ? at : (EX > 0 ? xm : xp)) - EY * nx;
+                    if constexpr (EY == 0) now[A] = from[A * kBatchRing + (src & M)];
+                    else now[A] = from[(EY > 0 ? lo : hi) ? Flow<2>::opposite(A) * kBatchRing + (at & M)
+                                                          : A * kBatchRing + (src & M)];
+                });
+                batch_collide<Real, Store>(now, bp, dom, out, u);
+                if (k + 1 < T) {
+                    Store* to = rings + k * 9u * kBatchRing;
+                    static_for<9>([&](auto aa) {
+                        constexpr int A = decltype(aa)::value;
+                        to[A * kBatchRing + (at & M)] = out[A];
+                    });
+                } else {
+                    static_for<9>([&](auto aa) {
+                        constexpr int A = decltype(aa)::value;
+                        at_byte(nxt + A * (int64_t)n, at * B) = out[A];
+                    });
+                }
+            }
+        }
+        if constexpr (T == 2) __syncthreads();
+    }
+}
+
+// Runs one domain to completion with buffers `b0` (holding the state) and
+// `b1`; returns which of the two holds the final state.  GLOBAL: the buffers are in
+// global memory, a thread's next node is loaded while it computes the present one.
+template <class Real, class Store, bool GLOBAL>
+__device__ int run_domain(Store* b0, Store* b1, Store* rings, Real* uprev, const BatchParams& bp, const BatchDomain& dom,
                           double* red, int64_t& steps_out, double& res_out, int& status_out) {
-    const int nx = dom.nx, ny = dom.ny, n = nx * ny;
+    const uint32_t nx = (uint32_t)dom.nx, ny = (uint32_t)dom.ny, n = nx * ny, threads = blockDim.x;
+    // a thread's nodes are `threads` apart: (dx, dy) further, with one carry
+    const uint32_t dy = threads / nx, dx = threads - dy * nx;
+    const uint32_t y_first = threadIdx.x / nx, x_first = threadIdx.x - y_first * nx;
     Store* cur = b0;
     Store* nxt = b1;
     int which = 0;
@@ -105,23 +289,51 @@ __device__ int run_domain(Store* b0, Store* b1, Real* uprev, const BatchParams& 
     double res = INFINITY;
     int status = kBatchMaxSteps;
     int64_t s = 0;
+    int32_t since = 0;   // steps since the last check
     for (; s < bp.max_steps;) {
-        const bool check = ((s + 1) % bp.check_interval) == 0;
-        double du2 = 0.0, u2 = 0.0;
-        bool finite = true;
-        for (int node = threadIdx.x; node < n; node += blockDim.x) {
-            const int y = node / nx, x = node - y * nx;
-            Real u[3];
-            batch_node<Real, Store>(cur, nxt, n, nx, ny, x, y, bp, dom, u);
-            if (check) {
-                const double ux = (double)u[0], uy = (double)u[1];
-                const double ox = (double)uprev[node], oy = (double)uprev[n + node];
-                uprev[node] = u[0];
-                uprev[n + node] = u[1];
-                du2 += (ux - ox) * (ux - ox) + (uy - oy) * (uy - oy);
-                u2 += ux * ux + uy * uy;
-                finite = finite && isfinite(ux) && isfinite(uy);
+        if constexpr (GLOBAL)
+            // as many steps at once as there are before the next check
+            if (rings && since < bp.check_interval - batch_fused<Real> && s + batch_fused<Real> <= bp.max_steps) {
+                batch_sweep<Real, Store>(cur, nxt, rings, x_first, n, nx, bp, dom);
+                __syncthreads();  // the sweep's writes are visible before the next reads them
+                Store* t = cur;
+                cur = nxt;
+                nxt = t;
+                which ^= 1;
+                s += batch_fused<Real>;
+                since += batch_fused<Real>;
+                continue;
             }
+        const bool check = ++since == bp.check_interval;
+        if (check) since = 0;
+        CheckSums sums;
+        uint32_t x = x_first, y = y_first;
+        Store raw[9];
+        if (GLOBAL && threadIdx.x < n) batch_pull_global<Store>(cur, threadIdx.x, x, n, nx, raw);
+        for (uint32_t node = threadIdx.x; node < n; node += threads) {
+            Store now[9], out[9];
+            if constexpr (GLOBAL) {
+                static_for<9>([&](auto aa) { now[decltype(aa)::value] = raw[decltype(aa)::value]; });
+                x += dx;
+                x = min(x, x - nx);   // less nx where x >= nx (unsigned)
+                if (node + threads < n) batch_pull_global<Store>(cur, node + threads, x, n, nx, raw);
+            } else {
+                batch_pull<Store>(cur, node_pos(node, (int)x, (int)y, (int)nx, (int)ny), n, nx, now);
+                x += dx;
+                y += dy;
+                if (x >= nx) {
+                    x -= nx;
+                    ++y;
+                }
+            }
+            Real u[3];
+            batch_collide<Real, Store>(now, bp, dom, out, u);
+            static_for<9>([&](auto aa) {
+                constexpr int A = decltype(aa)::value;
+                if constexpr (GLOBAL) at_byte(nxt + A * (int64_t)n, node * (uint32_t)sizeof(Store)) = out[A];
+                else element(nxt, A * n + node) = out[A];
+            });
+            if (check) sums.add(u, uprev, node, n);
         }
         __syncthreads();  // the step's writes are visible before the next step reads them
         Store* t = cur;
@@ -130,35 +342,81 @@ __device__ int run_domain(Store* b0, Store* b1, Real* uprev, const BatchParams& 
         which ^= 1;
         ++s;
         if (check) {
-            double bad = finite ? 0.0 : 1.0, unused = 0.0;
-            wg_sum2(du2, u2, red);
-            wg_sum2(bad, unused, red + 64);
-            int stop = 0;
-            if (bad > 0.0) {
-                stop = kBatchNonFinite;
-            } else if (have_prev) {
-                res = sqrt(du2) / ((double)bp.check_interval * sqrt(u2));
-                if (du2 == 0.0)
-                    stop = kBatchStationary;
-                else if (res < bp.tol)
-                    stop = kBatchConverged;
-            }
-            // Every lane holds the same sums; broadcasting the decision from lane 0
-            // makes the loop exit a scalar branch.  Left as a per-lane value the
-            // compiler may build an exec-mask loop around the barriers that re-runs
-            // without the work-queue atomic of the enclosing loop (a hang).
-            stop = __builtin_amdgcn_readfirstlane(stop);
+            const int stop = check_stop(sums, have_prev, res, bp, red);
             if (stop) {
                 status = stop;
                 break;
             }
-            have_prev = true;
         }
     }
     steps_out = s;
     res_out = res;
     status_out = status;
     return which;
+}
+
+// The same for a domain of at most R nodes per thread whose one buffer fits in
+// LDS: stepped in place, a step's reads all taken before its writes, with the
+// addresses of every pull formed once.
+template <class Real, class Store, int R>
+__device__ __forceinline__ void run_resident(Store* lds, Real* uprev, const BatchParams& bp, const BatchDomain& dom,
+                                             double* red, int64_t& steps_out, double& res_out, int& status_out) {
+    const int nx = dom.nx, ny = dom.ny, n = nx * ny;
+    uint32_t from[R][9];
+    static_for<R>([&](auto rr) {
+        constexpr int r = decltype(rr)::value;
+        int node = (int)threadIdx.x + r * (int)blockDim.x;
+        node = node < n ? node : n - 1;
+        const int y = node / nx, x = node - y * nx;
+        const NodePos p = node_pos((uint32_t)node, x, y, nx, ny);
+        static_for<9>([&](auto aa) {
+            constexpr int A = decltype(aa)::value;
+            from[r][A] = pull_index<A>(p, (uint32_t)n, (uint32_t)nx);
+        });
+    });
+    bool have_prev = false;
+    double res = INFINITY;
+    int status = kBatchMaxSteps;
+    int64_t s = 0;
+    for (; s < bp.max_steps;) {
+        const bool check = ((s + 1) % bp.check_interval) == 0;
+        CheckSums sums;
+        Store raw[R][9];
+        static_for<R>([&](auto rr) {
+            constexpr int r = decltype(rr)::value;
+            static_for<9>([&](auto aa) {
+                constexpr int A = decltype(aa)::value;
+                raw[r][A] = lds[from[r][A]];
+            });
+        });
+        __syncthreads();
+        static_for<R>([&](auto rr) {
+            constexpr int r = decltype(rr)::value;
+            const int node = (int)threadIdx.x + r * (int)blockDim.x;
+            Store out[9];
+            Real u[3];
+            batch_collide<Real, Store>(raw[r], bp, dom, out, u);
+            if (node < n) {
+                static_for<9>([&](auto aa) {
+                    constexpr int A = decltype(aa)::value;
+                    lds[A * n + node] = out[A];
+                });
+                if (check) sums.add(u, uprev, (uint32_t)node, (uint32_t)n);
+            }
+        });
+        __syncthreads();
+        ++s;
+        if (check) {
+            const int stop = check_stop(sums, have_prev, res, bp, red);
+            if (stop) {
+                status = stop;
+                break;
+            }
+        }
+    }
+    steps_out = s;
+    res_out = res;
+    status_out = status;
 }
 
 }  // namespace
@@ -193,17 +451,27 @@ __global__ void __launch_bounds__(1024) casclb_batch(BatchParams bp) {
         int64_t steps = 0;
         double res = INFINITY;
         int status = 0;
-        if (n <= bp.lds_nodes) {
+        if (n <= bp.resident_nodes) {
+            for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) lds[i] = g0[i];
+            __syncthreads();
+            const int per = (n + (int)blockDim.x - 1) / (int)blockDim.x;
+            if (per <= 1) run_resident<Real, Store, 1>(lds, uprev, bp, dom, red, steps, res, status);
+            else if constexpr (batch_resident_per_thread<Real> == 2)
+                run_resident<Real, Store, 2>(lds, uprev, bp, dom, red, steps, res, status);
+            for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) g0[i] = lds[i];
+            __syncthreads();
+        } else if (n <= bp.lds_nodes) {
             Store* l0 = lds;
             Store* l1 = lds + (int64_t)9 * n;
             for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) l0[i] = g0[i];
             __syncthreads();
-            const int which = run_domain<Real, Store>(l0, l1, uprev, bp, dom, red, steps, res, status);
+            const int which = run_domain<Real, Store, false>(l0, l1, nullptr, uprev, bp, dom, red, steps, res, status);
             const Store* fin = which ? l1 : l0;
             for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) g0[i] = fin[i];
             __syncthreads();
         } else {
-            const int which = run_domain<Real, Store>(g0, g1, uprev, bp, dom, red, steps, res, status);
+            Store* rings = dom.nx <= bp.fused_nx ? lds : nullptr;
+            const int which = run_domain<Real, Store, true>(g0, g1, rings, uprev, bp, dom, red, steps, res, status);
             if (which) {
                 for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) g0[i] = g1[i];
                 __syncthreads();

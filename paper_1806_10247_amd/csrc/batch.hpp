@@ -34,11 +34,25 @@ struct BatchParams {
     int64_t max_steps;
     double tol;
     double rho0, w_bulk, w_third, w_fourth;
-    int32_t lds_nodes;     // domains with at most this many nodes run in LDS
+    int32_t resident_nodes;  // domains with at most this many nodes run in one LDS buffer, in place
+    int32_t lds_nodes;       // domains with at most this many nodes run in two LDS buffers
+    int32_t fused_nx;        // of the others, those at most this wide are stepped batch_fused at a time
     int64_t* out_steps;
     double* out_residual;
     int32_t* out_status;
 };
+
+// Nodes per thread of a domain stepped in place (their pulled values are held in registers).
+template <class Real>
+constexpr int batch_resident_per_thread = sizeof(Real) == 8 ? 1 : 2;
+
+// Steps per sweep over a domain in global memory, and the nodes of the LDS ring that holds the
+// state between two of them: 144 KB of LDS in both storages.
+template <class Real>
+constexpr int batch_fused = sizeof(Real) == 8 ? 2 : 3;
+constexpr int kBatchRing = 2048;
+template <class Real>
+constexpr size_t batch_ring_bytes = (batch_fused<Real> - 1) * 9 * kBatchRing * sizeof(Real);
 
 // Routed domains: stepped together by ordinary (non-persistent) launches, one
 // per time step, each domain tiled over workgroups of kWideBlock nodes.  The

@@ -516,11 +516,18 @@ static BatchParams params_of(lb_batch* b, int64_t max_steps, double tol, int lds
     p.w_bulk = b->cfg.omega_bulk;
     p.w_third = b->cfg.omega_third;
     p.w_fourth = b->cfg.omega_fourth;
+    p.resident_nodes =
+        lds_policy == 0 ? (int32_t)std::min<int64_t>((int64_t)(b->lds_max / (18 * (size_t)b->elem)) * 2,
+                                                     (b->f64 ? batch_resident_per_thread<double>
+                                                             : batch_resident_per_thread<float>) * (int64_t)block)
+                        : 0;
     p.lds_nodes = lds_policy == 0 ? (int32_t)(b->lds_max / (18 * (size_t)b->elem)) : 0;
+    // (the dynamic LDS of the launch is lds_nodes' two buffers)
+    const bool rings = (size_t)p.lds_nodes * 18 * b->elem >= (b->f64 ? batch_ring_bytes<double> : batch_ring_bytes<float>);
+    p.fused_nx = rings ? (kBatchRing - block) / 4 : 0;
     p.out_steps = b->d_steps;
     p.out_residual = b->d_res;
     p.out_status = b->d_status;
-    (void)block;
     return p;
 }
 
