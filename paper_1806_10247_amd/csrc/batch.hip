@@ -202,7 +202,30 @@ __device__ __forceinline__ int check_stop(CheckSums c, bool& have_prev, double& 
     return __builtin_amdgcn_readfirstlane(stop);
 }
 
-// kBatchFused steps of a domain in global memory in one sweep over it, the states
+template <class T>
+using LdsPtr = __attribute__((address_space(3))) T*;
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+    return (uint32_t)(uintptr_t)(LdsPtr<const char>)reinterpret_cast<const char*>(p);
+}
+template <class T>
+__device__ __forceinline__ LdsPtr<T> lds_pointer(uint32_t address) {
+    return (LdsPtr<T>)(uintptr_t)address;
+}
+
+constexpr uint32_t kNoRings = 0xffffffffu;
+
+// Byte address in the ring plane at `base` of a byte offset.  Float rings start at a
+// multiple of the plane's size (batch_ring_align), so the base is or-ed in: one
+// instruction (a later step's vector instructions per node 233 -> 205-214, 5.0 -> 4.8 ms below).
+template <class Store>
+__device__ __forceinline__ uint32_t ring_address(uint32_t offset, uint32_t base) {
+    constexpr uint32_t MB = kBatchRing * sizeof(Store) - 1;
+    uint32_t a = sizeof(Store) == 4 ? (offset & MB) | base : (offset & MB) + base;
+    asm("" : "+v"(a));   // planes as immediate offsets of one address, not an address each
+    return a;
+}
+
+// batch_fused steps of a domain in global memory in one sweep over it, the states
 // between them in LDS rings.  Step k of the sweep is 2 nx nodes behind step k - 1, whose
 // last kBatchRing nodes its ring holds: a pull reaches at most 2 nx - 1 nodes (a row and
 // the wrap along x), so blockDim.x + 4 nx nodes must fit.  Every node is stepped
@@ -213,18 +236,19 @@ __device__ __forceinline__ int check_stop(CheckSums c, bool& have_prev, double& 
 //
 // One step at a time, 256 workgroups' domains overflow the caches and run at the memory's
 // rate: 512 float domains of 4-64 x 16-256 nodes, 200 steps, 6.8 ms = 5 TB/s.  In
-// sweeps 5.0 ms, of which the largest domain (16,384 nodes, started first) takes 4.6 on its
-// CU, bound by vector arithmetic.  129 such domains, whose states the caches hold: 3.9 and
-// 4.1 ms; 149 double ones: 7.0 and 5.7.
+// sweeps 4.8 ms, of which the largest domain (16,384 nodes, started first) takes 4.5 on its
+// CU, bound by vector arithmetic.  129 such domains, whose states the caches hold: 3.9 ms
+// either way; 149 double ones: 7.0 and 5.6.
 template <class Real, class Store>
-__device__ __forceinline__ void batch_sweep(const Store* cur, Store* nxt, Store* rings, uint32_t x, uint32_t n, uint32_t nx,
+__device__ __forceinline__ void batch_sweep(const Store* cur, Store* nxt, uint32_t rings, uint32_t x, uint32_t n, uint32_t nx,
                                             const BatchParams& bp, const BatchDomain& dom) {
-    constexpr uint32_t T = batch_fused<Real>, M = kBatchRing - 1, B = sizeof(Store);
+    constexpr uint32_t T = batch_fused<Real>, B = sizeof(Store), P = kBatchRing * B, two = 2u * P;
     const uint32_t threads = blockDim.x, dx = threads % nx;
     Store raw[9];
     if (threadIdx.x < n) batch_pull_global<Store>(cur, threadIdx.x, x, n, nx, raw);
     for (uint32_t base = 0; base < n + (T - 1) * 2u * nx; base += threads) {
-        const uint32_t node = base + threadIdx.x, x_now = x;
+        const uint32_t node = base + threadIdx.x;
+        const uint32_t to_xm = x == 0u ? B * (nx - 1u) : 0u - B, to_xp = x == nx - 1u ? 0u - B * (nx - 1u) : B;
         Store now[9], out[9];
         Real u[3];
         static_for<9>([&](auto aa) { now[decltype(aa)::value] = raw[decltype(aa)::value]; });
@@ -233,37 +257,42 @@ __device__ __forceinline__ void batch_sweep(const Store* cur, Store* nxt, Store*
         if (node + threads < n) batch_pull_global<Store>(cur, node + threads, x, n, nx, raw);
         if (node < n) {
             batch_collide<Real, Store>(now, bp, dom, out, u);
+            const uint32_t to = ring_address<Store>(B * node, rings);
             static_for<9>([&](auto aa) {
                 constexpr int A = decltype(aa)::value;
-                rings[A * kBatchRing + (node & M)] = out[A];
+                *lds_pointer<Store>(to + A * P) = out[A];
             });
         }
         for (uint32_t k = 1; k < T; ++k) {
             __syncthreads();
-            const Store* from = rings + (k - 1) * 9u * kBatchRing;
+            uint32_t from = rings + (k - 1) * 9u * P, from2 = from + two;
+            asm("" : "+v"(from), "+v"(from2));   // one scalar operand per instruction: the mask
             const uint32_t at = node - k * 2u * nx;   // (before the domain's first node: past its last, mod 2^32)
             if (at < n) {
-                const uint32_t xm = at + (x_now == 0u ? nx - 1u : 0u - 1u), xp = at + (x_now == nx - 1u ? 0u - (nx - 1u) : 1u);
+                // as in batch_pull_global one base per link serves source and wall value
+                const uint32_t here = B * at, xm = here + to_xm, xp = here + to_xp;
                 const bool lo = at < nx, hi = at >= n - nx;
+                const uint32_t own = ring_address<Store>(here, from), own2 = ring_address<Store>(here, from2);
                 static_for<9>([&](auto aa) {
                     constexpr int A = decltype(aa)::value;
                     constexpr int EX = Flow<2>::velocity(A, 0), EY = Flow<2>::velocity(A, 1);
-                    const uint32_t src = (EX == 0 ? at : (EX > 0 ? xm : xp)) - EY * nx;
-                    if constexpr (EY == 0) now[A] = from[A * kBatchRing + (src & M)];
-                    else now[A] = from[(EY > 0 ? lo : hi) ? Flow<2>::opposite(A) * kBatchRing + (at & M)
-                                                          : A * kBatchRing + (src & M)];
+                    const uint32_t src = (EX == 0 ? here : (EX > 0 ? xm : xp)) - EY * (B * nx);
+                    const uint32_t link = A == 0 ? own : ring_address<Store>(src, EY < 0 ? from2 : from);
+                    if constexpr (EY == 0) now[A] = *lds_pointer<const Store>(link + A * P);
+                    else if constexpr (EY > 0) now[A] = *lds_pointer<const Store>((lo ? own2 : link) + A * P);
+                    else now[A] = *lds_pointer<const Store>((hi ? own : link) + (A - 2) * P);
                 });
                 batch_collide<Real, Store>(now, bp, dom, out, u);
                 if (k + 1 < T) {
-                    Store* to = rings + k * 9u * kBatchRing;
+                    const uint32_t to = ring_address<Store>(here, from + 9u * P);
                     static_for<9>([&](auto aa) {
                         constexpr int A = decltype(aa)::value;
-                        to[A * kBatchRing + (at & M)] = out[A];
+                        *lds_pointer<Store>(to + A * P) = out[A];
                     });
                 } else {
                     static_for<9>([&](auto aa) {
                         constexpr int A = decltype(aa)::value;
-                        at_byte(nxt + A * (int64_t)n, at * B) = out[A];
+                        at_byte(nxt + A * (int64_t)n, here) = out[A];
                     });
                 }
             }
@@ -276,7 +305,7 @@ __device__ __forceinline__ void batch_sweep(const Store* cur, Store* nxt, Store*
 // `b1`; returns which of the two holds the final state.  GLOBAL: the buffers are in
 // global memory, a thread's next node is loaded while it computes the present one.
 template <class Real, class Store, bool GLOBAL>
-__device__ int run_domain(Store* b0, Store* b1, Store* rings, Real* uprev, const BatchParams& bp, const BatchDomain& dom,
+__device__ int run_domain(Store* b0, Store* b1, uint32_t rings, Real* uprev, const BatchParams& bp, const BatchDomain& dom,
                           double* red, int64_t& steps_out, double& res_out, int& status_out) {
     const uint32_t nx = (uint32_t)dom.nx, ny = (uint32_t)dom.ny, n = nx * ny, threads = blockDim.x;
     // a thread's nodes are `threads` apart: (dx, dy) further, with one carry
@@ -293,7 +322,7 @@ __device__ int run_domain(Store* b0, Store* b1, Store* rings, Real* uprev, const
     for (; s < bp.max_steps;) {
         if constexpr (GLOBAL)
             // as many steps at once as there are before the next check
-            if (rings && since < bp.check_interval - batch_fused<Real> && s + batch_fused<Real> <= bp.max_steps) {
+            if (rings != kNoRings && since < bp.check_interval - batch_fused<Real> && s + batch_fused<Real> <= bp.max_steps) {
                 batch_sweep<Real, Store>(cur, nxt, rings, x_first, n, nx, bp, dom);
                 __syncthreads();  // the sweep's writes are visible before the next reads them
                 Store* t = cur;
@@ -465,12 +494,13 @@ __global__ void __launch_bounds__(1024) casclb_batch(BatchParams bp) {
             Store* l1 = lds + (int64_t)9 * n;
             for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) l0[i] = g0[i];
             __syncthreads();
-            const int which = run_domain<Real, Store, false>(l0, l1, nullptr, uprev, bp, dom, red, steps, res, status);
+            const int which = run_domain<Real, Store, false>(l0, l1, kNoRings, uprev, bp, dom, red, steps, res, status);
             const Store* fin = which ? l1 : l0;
             for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) g0[i] = fin[i];
             __syncthreads();
         } else {
-            Store* rings = dom.nx <= bp.fused_nx ? lds : nullptr;
+            constexpr uint32_t align = batch_ring_align<Real>;
+            const uint32_t rings = dom.nx <= bp.fused_nx ? (lds_address(lds) + align - 1) / align * align : kNoRings;
             const int which = run_domain<Real, Store, true>(g0, g1, rings, uprev, bp, dom, red, steps, res, status);
             if (which) {
                 for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) g0[i] = g1[i];

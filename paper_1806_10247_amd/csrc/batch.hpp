@@ -47,12 +47,14 @@ template <class Real>
 constexpr int batch_resident_per_thread = sizeof(Real) == 8 ? 1 : 2;
 
 // Steps per sweep over a domain in global memory, and the nodes of the LDS ring that holds the
-// state between two of them: 144 KB of LDS in both storages.
+// state between two of them: 144 KB of LDS in both storages, and the alignment.
 template <class Real>
 constexpr int batch_fused = sizeof(Real) == 8 ? 2 : 3;
 constexpr int kBatchRing = 2048;
 template <class Real>
-constexpr size_t batch_ring_bytes = (batch_fused<Real> - 1) * 9 * kBatchRing * sizeof(Real);
+constexpr uint32_t batch_ring_align = sizeof(Real) == 4 ? kBatchRing * 4 : 16;
+template <class Real>
+constexpr size_t batch_ring_bytes = (batch_fused<Real> - 1) * 9 * kBatchRing * sizeof(Real) + batch_ring_align<Real>;
 
 // Routed domains: stepped together by ordinary (non-persistent) launches, one
 // per time step, each domain tiled over workgroups of kWideBlock nodes.  The
