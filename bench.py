@@ -187,7 +187,9 @@ def run_coupled(torch, C, storage, steps=200, warmup=20, n=4096):
     """The periodic 4096^2 D2Q9 + D2Q5 workload with a Taylor-Green force field
     modulated by cos(w t) and a product source field (both stored per node, in
     the arithmetic type): whole-run throughput over `steps` steps (a residual
-    check every 100) and bytes per update with the force and source fields."""
+    check every 100) and bytes per update with the force and source fields.  Runs
+    of plain steps go several steps per launch, the states between them on chip:
+    the algorithmic rate (bytes per update times updates) can exceed the memory's."""
     from casclb_inputs import coupled_2d, product_source_2d, vortex_force_2d
     w = coupled_2d(n)
     stream = torch.cuda.current_stream()
