@@ -71,8 +71,10 @@ struct lb_ctx {
     void* u_prev = nullptr;
     double* partials = nullptr;   // [max blocks][kDiagSlots]
     int64_t partial_blocks = 0;
-    double* diag_dev = nullptr;   // kDiagSlots doubles
-    double* diag_host = nullptr;  // pinned copy of the last completed check
+    // kDiagSlots doubles of the last completed check in pinned memory, and their address on
+    // the device: the sums are written there by the reduction itself (no copy after it)
+    double* diag_host = nullptr;
+    double* diag_dev = nullptr;
     hipEvent_t diag_event = nullptr;
     bool prev_valid = false;      // u_prev holds the previous check's velocity
     bool check_pending = false;
@@ -359,7 +361,6 @@ static void release(lb_ctx* c) {
     if (c->source_field) (void)hipFree(c->source_field);
     if (c->u_prev) (void)hipFree(c->u_prev);
     if (c->partials) (void)hipFree(c->partials);
-    if (c->diag_dev) (void)hipFree(c->diag_dev);
     if (c->wall_dev) (void)hipFree(c->wall_dev);
     if (c->diag_host) (void)hipHostFree(c->diag_host);
     if (c->diag_event) (void)hipEventDestroy(c->diag_event);
@@ -426,7 +427,6 @@ int lb_create(lb_ctx** out, const lb_config* cfg) {
         c->partial_blocks = maxb;
         ALLOC(c->partials, (size_t)maxb * kDiagSlots * sizeof(double));
     }
-    ALLOC(c->diag_dev, kDiagSlots * sizeof(double));
     ALLOC(c->wall_dev, kWallTable * sizeof(double));
     // previous check's u* (dims planes) and, on the coupled lattice, phi* (one more plane)
     if (cfg->residual_interval > 0)
@@ -438,6 +438,11 @@ int lb_create(lb_ctx** out, const lb_config* cfg) {
         goto error;
     }
     memset(c->diag_host, 0, kDiagSlots * sizeof(double));
+    e = hipHostGetDevicePointer((void**)&c->diag_dev, c->diag_host, 0);
+    if (e != hipSuccess) {
+        rc = fail(nullptr, LB_EHIP, "hipHostGetDevicePointer failed: %s", hipGetErrorString(e));
+        goto error;
+    }
     e = hipMemcpy(c->wall_dev, c->wall_table, sizeof(c->wall_table), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         rc = fail(nullptr, LB_EHIP, "hipMemcpy failed: %s", hipGetErrorString(e));
@@ -1049,8 +1054,6 @@ int lb_step(lb_ctx* c, int64_t nsteps) {
         HIP_OR_FAIL(c, launch_step(c->cfg.lattice, c->cfg.storage, a, c->block, check, c->stream));
         if (check) {
             HIP_OR_FAIL(c, launch_reduce(c->partials, c->geo_step.grid_blocks, c->diag_dev, c->stream));
-            HIP_OR_FAIL(c, hipMemcpyAsync(c->diag_host, c->diag_dev, kDiagSlots * sizeof(double),
-                                          hipMemcpyDeviceToHost, c->stream));
             HIP_OR_FAIL(c, hipEventRecord(c->diag_event, c->stream));
             c->check_pending = true;
             c->check_valid = c->prev_valid;
