@@ -246,7 +246,10 @@ int lb_set_source_time(lb_ctx* ctx, int32_t mode, double omega);
 /* Enqueues nsteps >= 0 time steps on the context's stream (one fused kernel
  * launch per step, plus a reduction every residual_interval steps; on a 2D
  * lattice whose launch shape is left automatic (block_x, rows_per_thread and
- * x_pairs 0) several steps per launch, with bit-identical results).  Returns
+ * x_pairs 0) several steps per launch, with bit-identical results).  While the
+ * stream is being recorded into a HIP graph an even number of steps leaves the
+ * state in the buffer it was in, so each replay continues the one before (the
+ * step counter advances while recording, not with replays).  Returns
  * LB_ENONFINITE if a residual check that has already completed found a NaN or
  * infinity (the steps are then not enqueued). */
 int lb_step(lb_ctx* ctx, int64_t nsteps);

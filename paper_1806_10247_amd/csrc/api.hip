@@ -954,9 +954,18 @@ static bool multi_applies(const lb_ctx* c) {
            (uint64_t)c->plane * 2 * c->real_bytes < (1ull << 32);
 }
 
+// Whether the context's stream is being recorded into a graph.
+static bool capturing(const lb_ctx* c) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return c->stream && hipStreamIsCapturing(c->stream, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
+}
+
 // Tiling for the next of `plain` >= 2 steps (false: one step per launch), chosen on first
-// use and again when a field is set or cleared.
-static bool multi_shape(lb_ctx* c, int64_t plain, MultiShape* out) {
+// use and again when a field is set or cleared.  owed < 0: as few launches as the best
+// length allows.  Otherwise (a recording) the run's launches, each of which swaps the
+// buffers, get the parity of its steps, so that replaying an even number of steps starts
+// where the last replay ended; owed is the parity of the run's steps and launches so far.
+static bool multi_shape(lb_ctx* c, int64_t plain, int owed, MultiShape* out) {
     if (plain < 2 || !multi_applies(c)) return false;
     const int fields = (c->force_field ? 1 : 0) + (c->source_field ? 2 : 0);
     if (c->multi_fields != fields) {
@@ -975,9 +984,13 @@ static bool multi_shape(lb_ctx* c, int64_t plain, MultiShape* out) {
         }
     }
     if (c->multi_most < 2) return false;
-    // as few launches as the best length allows, of about equal length
-    const int64_t launches = (plain + c->multi_most - 1) / c->multi_most;
-    int k = (int)((plain + launches - 1) / launches);
+    // launches of about equal length
+    auto length = [&](int64_t most) {
+        int64_t launches = (plain + most - 1) / most;
+        if (owed >= 0 && ((launches + plain + owed) & 1)) ++launches;
+        return (int)((plain + launches - 1) / launches);
+    };
+    int k = length(c->multi_most);
     while (k >= 2 && !c->multi_ok[k]) --k;
     if (k < 2) return false;
     *out = c->multi[k];
@@ -985,7 +998,7 @@ static bool multi_shape(lb_ctx* c, int64_t plain, MultiShape* out) {
     // tables of what changes from step to step
     if (!out->hx && !out->hy && c->force_mode == LB_TIME_CONSTANT && c->source_mode == LB_TIME_CONSTANT &&
         !stochastic_rounding(c))
-        out->steps = (int)std::min<int64_t>(plain, 256);
+        out->steps = length(256);
     return true;
 }
 
@@ -1021,16 +1034,18 @@ int lb_step(lb_ctx* c, int64_t nsteps) {
         return fail(c, LB_ENONFINITE, "non-finite values found by the residual check after step %lld",
                     (long long)c->check_step);
     const int K = c->cfg.residual_interval;
+    int owed = c->dims == 2 && capturing(c) ? 0 : -1;
     for (int64_t s = 0; s < nsteps; ++s) {
         // plain steps before the next residual check (or the end of the call)
         int64_t plain = nsteps - s;
         if (K > 0) plain = std::min(plain, (int64_t)(K - 1 - c->step % K));
         MultiShape shape;
-        while (multi_shape(c, plain, &shape)) {
+        while (multi_shape(c, plain, owed, &shape)) {
             const int rc = multi_step(c, shape);
             if (rc) return rc;
             s += shape.steps;
             plain -= shape.steps;
+            if (owed >= 0) owed ^= (shape.steps + 1) & 1;
         }
         if (s >= nsteps) break;
         if (graphs_apply(c)) {
