@@ -450,8 +450,14 @@ __device__ __forceinline__ void run_resident(Store* lds, Real* uprev, const Batc
 
 }  // namespace
 
-template <class Real, class Store>
-__global__ void __launch_bounds__(1024) casclb_batch(BatchParams bp) {
+// SMALL: domains of at most one node per thread, or no LDS and at most four: nothing to sweep
+// and little to load ahead, and without that code the registers (float 123 -> 80, double 128
+// and 40 bytes of scratch -> 115) leave room for a third workgroup of 512 threads per CU.
+// 2000 domains of 1-8 x 4-64 nodes without LDS, 100 steps: 524 -> 288 us in float, 584 -> 448
+// in double; with larger domains loading ahead is worth more (600 domains of up to 16,384
+// nodes, workgroups of 256 threads: 3.2 ms against 4.1).
+template <class Real, class Store, bool SMALL>
+__global__ void __launch_bounds__(1024, SMALL && sizeof(Real) == 4 ? 6 : 4) casclb_batch(BatchParams bp) {
     extern __shared__ unsigned char lds_raw[];
     __shared__ int s_next;
     __shared__ double red[160];
@@ -484,12 +490,12 @@ __global__ void __launch_bounds__(1024) casclb_batch(BatchParams bp) {
             for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) lds[i] = g0[i];
             __syncthreads();
             const int per = (n + (int)blockDim.x - 1) / (int)blockDim.x;
-            if (per <= 1) run_resident<Real, Store, 1>(lds, uprev, bp, dom, red, steps, res, status);
+            if (SMALL || per <= 1) run_resident<Real, Store, 1>(lds, uprev, bp, dom, red, steps, res, status);
             else if constexpr (batch_resident_per_thread<Real> == 2)
                 run_resident<Real, Store, 2>(lds, uprev, bp, dom, red, steps, res, status);
             for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) g0[i] = lds[i];
             __syncthreads();
-        } else if (n <= bp.lds_nodes) {
+        } else if (!SMALL && n <= bp.lds_nodes) {
             Store* l0 = lds;
             Store* l1 = lds + (int64_t)9 * n;
             for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) l0[i] = g0[i];
@@ -501,7 +507,7 @@ __global__ void __launch_bounds__(1024) casclb_batch(BatchParams bp) {
         } else {
             constexpr uint32_t align = batch_ring_align<Real>;
             const uint32_t rings = dom.nx <= bp.fused_nx ? (lds_address(lds) + align - 1) / align * align : kNoRings;
-            const int which = run_domain<Real, Store, true>(g0, g1, rings, uprev, bp, dom, red, steps, res, status);
+            const int which = run_domain<Real, Store, !SMALL>(g0, g1, rings, uprev, bp, dom, red, steps, res, status);
             if (which) {
                 for (int i = threadIdx.x; i < 9 * n; i += blockDim.x) g0[i] = g1[i];
                 __syncthreads();
@@ -738,21 +744,20 @@ hipError_t launch_wide_gather(bool f64, const WideParams& p, int ntiles, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_batch(bool f64, const BatchParams& bp, int grid, int block, size_t lds_bytes, hipStream_t s) {
+template <class Real>
+static auto batch_kernel(bool small) {
+    return small ? casclb_batch<Real, Real, true> : casclb_batch<Real, Real, false>;
+}
+
+hipError_t launch_batch(bool f64, bool small, const BatchParams& bp, int grid, int block, size_t lds_bytes, hipStream_t s) {
     hipLaunchKernelGGL(casclb_batch_reset, dim3(1), dim3(64), 0, s, bp.queue);
-    if (f64)
-        hipLaunchKernelGGL((casclb_batch<double, double>), dim3(grid), dim3(block), lds_bytes, s, bp);
-    else
-        hipLaunchKernelGGL((casclb_batch<float, float>), dim3(grid), dim3(block), lds_bytes, s, bp);
+    hipLaunchKernelGGL(f64 ? batch_kernel<double>(small) : batch_kernel<float>(small), dim3(grid), dim3(block), lds_bytes, s, bp);
     return hipGetLastError();
 }
 
-hipError_t batch_set_lds_limit(bool f64, size_t lds_bytes) {
-    if (f64)
-        return hipFuncSetAttribute((const void*)casclb_batch<double, double>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    return hipFuncSetAttribute((const void*)casclb_batch<float, float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds_bytes);
+hipError_t batch_set_lds_limit(bool f64, bool small, size_t lds_bytes) {
+    const auto kernel = f64 ? batch_kernel<double>(small) : batch_kernel<float>(small);
+    return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
 }
 
 hipError_t launch_batch_moments(bool f64, const BatchParams& bp, int id, int n, double* rho, double* u,

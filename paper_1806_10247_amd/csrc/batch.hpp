@@ -97,8 +97,10 @@ hipError_t launch_wide_close(const WideParams& p, int64_t steps, hipStream_t s);
 // they are in the second).
 hipError_t launch_wide_gather(bool f64, const WideParams& p, int ntiles, hipStream_t s);
 
-hipError_t launch_batch(bool f64, const BatchParams& bp, int grid, int block, size_t lds_bytes, hipStream_t s);
-hipError_t batch_set_lds_limit(bool f64, size_t lds_bytes);
+// small: every domain of the queue has at most one node per thread, or four where there is no LDS
+// (bp.lds_nodes 0).
+hipError_t launch_batch(bool f64, bool small, const BatchParams& bp, int grid, int block, size_t lds_bytes, hipStream_t s);
+hipError_t batch_set_lds_limit(bool f64, bool small, size_t lds_bytes);
 hipError_t launch_batch_moments(bool f64, const BatchParams& bp, int id, int n, double* rho, double* u,
                                 hipStream_t s);
 hipError_t launch_batch_zero(bool f64, void* pool, int64_t n, hipStream_t s);

@@ -48,6 +48,7 @@ struct lb_batch {
     // (max_steps, tol) the device-side domain order was computed for
     int64_t o_steps = -1;
     double o_tol = -1;
+    int32_t largest = 0;      // nodes of the largest domain of the queue
     double* staging = nullptr;
     size_t staging_bytes = 0;
     // routed domains (the `routed` of longest expected time in the persistent
@@ -573,6 +574,8 @@ static int upload_order(lb_batch* b, int64_t max_steps, double tol) {
     BHIP(b, hipStreamSynchronize(b->stream));
     if (!order.empty())
         BHIP(b, hipMemcpy(b->d_order, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice));
+    b->largest = 0;
+    for (int32_t i : order) b->largest = std::max(b->largest, b->dom[i].nx * b->dom[i].ny);
     b->o_steps = max_steps;
     b->o_tol = tol;
     return LB_OK;
@@ -586,10 +589,11 @@ static int launch_run(lb_batch* b, int64_t max_steps, double tol, int block, int
     const BatchParams p = params_of(b, max_steps, tol, policy, block);
     if (p.ndomains == 0) return LB_OK;
     const size_t lds = policy == 0 ? (size_t)p.lds_nodes * 18 * b->elem : 0;
-    if (lds) BHIP(b, batch_set_lds_limit(b->f64, lds));
+    const bool small = b->largest <= (p.lds_nodes > 0 ? block : 4 * block);
+    if (lds) BHIP(b, batch_set_lds_limit(b->f64, small, lds));
     const int grid = grid_of(b, block, lds);
     if (!use_graph) {
-        BHIP(b, launch_batch(b->f64, p, grid, block, lds, b->stream));
+        BHIP(b, launch_batch(b->f64, small, p, grid, block, lds, b->stream));
         return LB_OK;
     }
     if (!b->exec || b->g_steps != max_steps || b->g_tol != tol || b->g_block != block || b->g_policy != policy) {
@@ -598,7 +602,7 @@ static int launch_run(lb_batch* b, int64_t max_steps, double tol, int block, int
         b->exec = nullptr;
         b->graph = nullptr;
         BHIP(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-        hipError_t e = launch_batch(b->f64, p, grid, block, lds, b->stream);
+        hipError_t e = launch_batch(b->f64, small, p, grid, block, lds, b->stream);
         hipError_t e2 = hipStreamEndCapture(b->stream, &b->graph);
         if (e != hipSuccess) return bfail(b, LB_EHIP, "batch launch during capture: %s", hipGetErrorString(e));
         if (e2 != hipSuccess) return bfail(b, LB_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e2));
