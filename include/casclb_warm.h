@@ -74,7 +74,9 @@ int lb_warm_project(double* data, int32_t planes, int32_t L, int32_t k2max, void
 
 /* The same over the whole chip, with a workspace of lb_warm_project_work()
  * doubles on the device, free again once `stream` has passed the call.  The work
- * size is 0 where the arguments are refused or one workgroup per plane is as fast. */
+ * size is 0 where the arguments are refused or one workgroup per plane is as fast
+ * (by L alone for up to 256 planes, so a plane's result does not depend on the
+ * number beside it; always above). */
 int64_t lb_warm_project_work(int32_t planes, int32_t L, int32_t k2max);
 int lb_warm_project_split(double* data, int32_t planes, int32_t L, int32_t k2max, double* work, void* stream);
 

@@ -343,9 +343,12 @@ __global__ void __launch_bounds__(kProjBlock) project_k(double* data, int L, int
 // writes its part of the (-1)^y column sums.  project_apply_k: the same rows again; every
 // workgroup adds the column parts (at most 32) and forms the plane sums from the row sums
 // by itself: a third launch for them cost more (24 us against 18 for four planes of 256^2
-// with low modes).  Fixed order as above.  Bound by latency, then by memory: four planes of
-// 256^2 take 8.4 us (30 with one workgroup each), 17.7 with low modes (52); of 1024^2
-// 35 and 52 (458 and 805).
+// with low modes).  About 512 workgroups, each stepping through every gridDim.x-th part of
+// its plane, so that many planes do not repeat the plane sums for every part (256 planes of
+// 256^2: 71 us, 131 with low modes; one workgroup per part 85 and 193).  Fixed order as
+// above, whatever the number of workgroups (two fit a CU; up to 768 take a part each).
+// Bound by latency, then by memory: four planes of 256^2 take 8.4 us (30 with one workgroup
+// each), 17.7 with low modes (52); of 1024^2 35 and 52 (458 and 805).
 constexpr int kSplitParts = 32;
 __host__ __device__ constexpr int split_rows(int L) { return 16 * ((L + 16 * kSplitParts - 1) / (16 * kSplitParts)); }
 __host__ __device__ constexpr int split_parts(int L) { return (L + split_rows(L) - 1) / split_rows(L); }
@@ -380,54 +383,57 @@ __global__ void __launch_bounds__(kProjBlock, RPW == 1 && !LOW ? 8 : 4) project_
     double* st = ct + L;                          //   sin(2 pi m / L)
     const double* A = data + (int64_t)blockIdx.y * L * L;
     double* rows = work + (int64_t)blockIdx.y * split_work(L, LOW);
-    double* part = rows + (int64_t)((LOW ? 6 : 2) + (int)blockIdx.x) * L;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int y0 = (int)blockIdx.x * 16 * RPW + wave;
-    double sum[RPW][LOW ? 5 : 1] = {};
-    for (int g = 0; g < L; g += 64 * J) {
-        double v[RPW][J], col[J] = {};
-        project_load(A, L, y0, g, v);
-        if constexpr (LOW)
-            if (g == 0) {   // behind the first loads
-                for (int m = threadIdx.x; m < L; m += kProjBlock) sincospi(2.0 * (double)m / (double)L, &st[m], &ct[m]);
-                __syncthreads();
-            }
+    const double sx0 = (lane & 1) ? -1.0 : 1.0, inv = 1.0 / (double)L;   // x is even exactly when lane is
+    for (int b = blockIdx.x; b < split_parts(L); b += gridDim.x) {
+        double* part = rows + (int64_t)((LOW ? 6 : 2) + b) * L;
+        const int y0 = b * 16 * RPW + wave;
+        double sum[RPW][LOW ? 5 : 1] = {};
+        for (int g = 0; g < L; g += 64 * J) {
+            double v[RPW][J], col[J] = {};
+            project_load(A, L, y0, g, v);
+            const bool first = g == 0 && b == (int)blockIdx.x;
+            if constexpr (LOW)
+                if (first) {   // behind the first loads
+                    for (int m = threadIdx.x; m < L; m += kProjBlock) sincospi(2.0 * (double)m / (double)L, &st[m], &ct[m]);
+                    __syncthreads();
+                }
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int x = g + lane + 64 * j, xc = x < L ? x : 0, x2 = twiddle_index(2, xc, L);   // (columns past the end are zeros)
+            for (int j = 0; j < J; ++j) {
+                const int x = g + lane + 64 * j, xc = x < L ? x : 0, x2 = twiddle_index(2, xc, L);   // (columns past the end are zeros)
 #pragma unroll
-            for (int i = 0; i < RPW; ++i) {
-                sum[i][0] += v[i][j];
-                col[j] += ((y0 + 16 * i) & 1) ? -v[i][j] : v[i][j];
-                if constexpr (LOW) {
-                    sum[i][1] += v[i][j] * ct[xc];
-                    sum[i][2] += v[i][j] * st[xc];
-                    sum[i][3] += v[i][j] * ct[x2];
-                    sum[i][4] += v[i][j] * st[x2];
+                for (int i = 0; i < RPW; ++i) {
+                    sum[i][0] += v[i][j];
+                    col[j] += ((y0 + 16 * i) & 1) ? -v[i][j] : v[i][j];
+                    if constexpr (LOW) {
+                        sum[i][1] += v[i][j] * ct[xc];
+                        sum[i][2] += v[i][j] * st[xc];
+                        sum[i][3] += v[i][j] * ct[x2];
+                        sum[i][4] += v[i][j] * st[x2];
+                    }
                 }
             }
+            if (!first) __syncthreads();
+#pragma unroll
+            for (int j = 0; j < J; ++j) red[(wave * J + j) * 64 + lane] = col[j];
+            __syncthreads();
+            if (threadIdx.x < 64 * J && g + (int)threadIdx.x < L) {
+                double s = 0.0;
+                for (int w = 0; w < kProjWaves; ++w) s += red[w * 64 * J + threadIdx.x];
+                part[g + threadIdx.x] = s;
+            }
         }
-        if (g > 0) __syncthreads();
 #pragma unroll
-        for (int j = 0; j < J; ++j) red[(wave * J + j) * 64 + lane] = col[j];
-        __syncthreads();
-        if (threadIdx.x < 64 * J && g + (int)threadIdx.x < L) {
-            double s = 0.0;
-            for (int w = 0; w < kProjWaves; ++w) s += red[w * 64 * J + threadIdx.x];
-            part[g + threadIdx.x] = s;
-        }
-    }
-    const double sx0 = (lane & 1) ? -1.0 : 1.0, inv = 1.0 / (double)L;   // x is even exactly when lane is
+        for (int i = 0; i < RPW; ++i) {
+            const int y = y0 + 16 * i;
+            const double alt = wave_sum(sx0 * sum[i][0]) * inv;
 #pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        const int y = y0 + 16 * i;
-        const double alt = wave_sum(sx0 * sum[i][0]) * inv;
+            for (int c = 0; c < (LOW ? 5 : 1); ++c) sum[i][c] = wave_sum(sum[i][c]);
+            if (lane == 0 && y < L) {
+                rows[y] = alt;
 #pragma unroll
-        for (int c = 0; c < (LOW ? 5 : 1); ++c) sum[i][c] = wave_sum(sum[i][c]);
-        if (lane == 0 && y < L) {
-            rows[y] = alt;
-#pragma unroll
-            for (int c = 0; c < (LOW ? 5 : 1); ++c) rows[(int64_t)(1 + c) * L + y] = sum[i][c];
+                for (int c = 0; c < (LOW ? 5 : 1); ++c) rows[(int64_t)(1 + c) * L + y] = sum[i][c];
+            }
         }
     }
 }
@@ -446,10 +452,9 @@ __global__ void __launch_bounds__(kProjBlock, RPW == 1 ? 8 : 4) project_apply_k(
     const double* rows = work + (int64_t)blockIdx.y * split_work(L, LOW);
     const double* part = rows + (int64_t)(LOW ? 6 : 2) * L;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nparts = split_parts(L);
-    const int y0 = (int)blockIdx.x * ROWS + wave;
     const double inv = 1.0 / (double)L;
     double v[RPW][J];
-    project_load(A, L, y0, 0, v);
+    project_load(A, L, (int)blockIdx.x * ROWS + wave, 0, v);
     for (int x = threadIdx.x; x < L; x += kProjBlock) {
         double s = 0.0;
 #pragma unroll 8
@@ -480,52 +485,55 @@ __global__ void __launch_bounds__(kProjBlock, RPW == 1 ? 8 : 4) project_apply_k(
         if (lane == 0) fin[q] = q == 0 ? s * inv * inv : (q == 1 ? s * inv : 2.0 * s * inv * inv);
     }
     __syncthreads();
-    const double mean = fin[0], cnn = fin[1];
-    if constexpr (LOW) {
-        if (threadIdx.x < ROWS) {
-            const int y = (int)blockIdx.x * ROWS + threadIdx.x;
-            double a0 = mean, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0;
-            for (int m = 0; m < modes.n; ++m) {
-                const int kx = modes.kx[m], t = twiddle_index(modes.ky[m], y < L ? y : 0, L);
-                const double mc = fin[2 + 2 * m], ms = fin[3 + 2 * m];
-                const double a = mc * ct[t] + ms * st[t], b = ms * ct[t] - mc * st[t];
-                if (kx == 0) {
-                    a0 += a;
-                } else if (kx == 1) {
-                    a1 += a;
-                    b1 += b;
-                } else {
-                    a2 += a;
-                    b2 += b;
-                }
-            }
-            coef[0 * ROWS + threadIdx.x] = a0;
-            coef[1 * ROWS + threadIdx.x] = a1;
-            coef[2 * ROWS + threadIdx.x] = b1;
-            coef[3 * ROWS + threadIdx.x] = a2;
-            coef[4 * ROWS + threadIdx.x] = b2;
-        }
-        __syncthreads();
-    }
-    const double sx0 = (lane & 1) ? -1.0 : 1.0;
-    for (int g = 0; g < L; g += 64 * J) {
-        if (g > 0) project_load(A, L, y0, g, v);
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-            const int y = y0 + 16 * i, r = wave + 16 * i;
-            if (y >= L) break;
-            const double sy = (y & 1) ? -1.0 : 1.0, ry = rows[y];
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int x = g + lane + 64 * j;
-                if (x < L) {
-                    double low = mean;
-                    if constexpr (LOW) {
-                        const int x2 = twiddle_index(2, x, L);
-                        low = coef[r] + coef[ROWS + r] * ct[x] + coef[2 * ROWS + r] * st[x] + coef[3 * ROWS + r] * ct[x2] +
-                              coef[4 * ROWS + r] * st[x2];
+    const double mean = fin[0], cnn = fin[1], sx0 = (lane & 1) ? -1.0 : 1.0;
+    for (int b = blockIdx.x; b < nparts; b += gridDim.x) {
+        const int y0 = b * ROWS + wave;
+        if constexpr (LOW) {
+            if (b > (int)blockIdx.x) __syncthreads();   // the last rows' coefficients are read
+            if (threadIdx.x < ROWS) {
+                const int y = b * ROWS + threadIdx.x;
+                double a0 = mean, a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0;
+                for (int m = 0; m < modes.n; ++m) {
+                    const int kx = modes.kx[m], t = twiddle_index(modes.ky[m], y < L ? y : 0, L);
+                    const double mc = fin[2 + 2 * m], ms = fin[3 + 2 * m];
+                    const double a = mc * ct[t] + ms * st[t], b = ms * ct[t] - mc * st[t];
+                    if (kx == 0) {
+                        a0 += a;
+                    } else if (kx == 1) {
+                        a1 += a;
+                        b1 += b;
+                    } else {
+                        a2 += a;
+                        b2 += b;
                     }
-                    A[(int64_t)y * L + x] = v[i][j] - sx0 * ry - sy * (cols[x] - sx0 * cnn) - low;
+                }
+                coef[0 * ROWS + threadIdx.x] = a0;
+                coef[1 * ROWS + threadIdx.x] = a1;
+                coef[2 * ROWS + threadIdx.x] = b1;
+                coef[3 * ROWS + threadIdx.x] = a2;
+                coef[4 * ROWS + threadIdx.x] = b2;
+            }
+            __syncthreads();
+        }
+        for (int g = 0; g < L; g += 64 * J) {
+            if (g > 0 || b > (int)blockIdx.x) project_load(A, L, y0, g, v);
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) {
+                const int y = y0 + 16 * i, r = wave + 16 * i;
+                if (y >= L) break;
+                const double sy = (y & 1) ? -1.0 : 1.0, ry = rows[y];
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const int x = g + lane + 64 * j;
+                    if (x < L) {
+                        double low = mean;
+                        if constexpr (LOW) {
+                            const int x2 = twiddle_index(2, x, L);
+                            low = coef[r] + coef[ROWS + r] * ct[x] + coef[2 * ROWS + r] * st[x] + coef[3 * ROWS + r] * ct[x2] +
+                                  coef[4 * ROWS + r] * st[x2];
+                        }
+                        A[(int64_t)y * L + x] = v[i][j] - sx0 * ry - sy * (cols[x] - sx0 * cnn) - low;
+                    }
                 }
             }
         }
@@ -610,8 +618,8 @@ __global__ void __launch_bounds__(kProjBlock) initial_state_k(const double* drho
 // The same in three launches that use the whole chip, for problems of many nodes
 // and outputs apart from the inputs: partial sums (kInitParts workgroups per
 // problem, left in the first kInitParts nodes of the outputs), every other node,
-// then those first nodes.  One problem of 64^2: 9.7 us in one launch, 9.9 in
-// three; 90^2: 18 and 10; 256^2: 109 and 10 (launch-bound: the kernels take 4 + 4 + 2).
+// then those first nodes.  One problem of 256^2: 109 us in one launch, 10 in three
+// (launch-bound: the kernels take 4 + 4 + 2).
 constexpr int kInitParts = 64;
 struct InitArgs {
     const double *drho, *u, *phi, *F, *S;
@@ -679,11 +687,15 @@ int grid_for(int64_t total) {
 }
 
 constexpr int kMaxPlanes = 65535;   // of one launch (grid.y)
-// Lattices from which the split projection is taken, by size alone (a problem's result is
-// the same in every batch).  One workgroup per plane against split, 4 planes: 64^2 6.7 and
-// 6.5 us (launch-bound), 96^2 11.1 and 7.4.  With low modes, 4 and 64 planes: 128^2 19 and
-// 15, but 20 and 24; 192^2 38 and 17, 40 and 40; 256^2 52 and 18, 54 and 51.
-constexpr int split_min(bool low) { return low ? 192 : 66; }
+// Lattices from which the split projection is taken, by size alone up to kSplitPlanes planes
+// (a problem's result is the same in every batch of up to 64).  us with one workgroup per
+// plane and split, 4 planes and 256: 128^2 12.2 and 7.5, but 15.4 and 25.8; 160^2 19.4 and
+// 8.1, 29.7 and 35.6; 256^2 31 and 8.8, 62 and 71; with low modes 160^2 34 and 17, but 45
+// and 82; 192^2 38 and 18, 52 and 97; 256^2 52 and 18, 76 and 131; 1024^2 805 and 54,
+// 1476 and 1565.  (The whole chip has work with 256 planes: above that one workgroup each
+// is faster up to 384^2 and as fast beyond.)
+constexpr int split_min(bool low) { return low ? 192 : 160; }
+constexpr int kSplitPlanes = 256, kSplitGroups = 512;
 
 int done(hipError_t e) { return e == hipSuccess ? LB_OK : LB_EHIP; }
 
@@ -780,7 +792,7 @@ int lb_warm_project(double* data, int32_t planes, int32_t L, int32_t k2max, void
 
 int64_t lb_warm_project_work(int32_t planes, int32_t L, int32_t k2max) {
     LowModes low;
-    if (low_modes(planes, L, k2max, &low) != LB_OK || L < split_min(low.n > 0) || planes > kMaxPlanes) return 0;
+    if (low_modes(planes, L, k2max, &low) != LB_OK || L < split_min(low.n > 0) || planes > kSplitPlanes) return 0;
     return planes * split_work(L, low.n > 0);
 }
 
@@ -789,7 +801,9 @@ int lb_warm_project_split(double* data, int32_t planes, int32_t L, int32_t k2max
     if (!data || !work || low_modes(planes, L, k2max, &low) != LB_OK || lb_warm_project_work(planes, L, k2max) == 0)
         return LB_EINVAL;
     const int rpw = split_rows(L) / 16;
-    const dim3 grid((unsigned)split_parts(L), (unsigned)planes), block(kProjBlock);
+    const int parts = split_parts(L);
+    const int groups = 2 * parts * planes <= 3 * kSplitGroups ? parts : (kSplitGroups + planes - 1) / planes;
+    const dim3 grid((unsigned)groups, (unsigned)planes), block(kProjBlock);
     const hipStream_t st = (hipStream_t)stream;
     static_assert((kProjWaves * 64 * 4 + 2 * LB_WARM_MAX_L) * sizeof(double) <= 65536, "default dynamic LDS");
     static_assert((3 * LB_WARM_MAX_L + kProjSums + 5 * 64) * sizeof(double) <= 65536, "default dynamic LDS");
@@ -848,19 +862,26 @@ int lb_warm_initial_state(const double* drho, const double* u, const double* phi
     if (!drho || !u || !F || !rho_out || !u_out || batch < 1 || n < 1) return LB_EINVAL;
     if ((phi == nullptr) != (phi_out == nullptr)) return LB_EINVAL;
     const int64_t all = (int64_t)batch * n;
-    const InitArgs a{drho, u, phi, F, S, n, all, rho0, rho_out, u_out, phi_out};
     // outputs that share memory with an input are written only after every sum: one workgroup each
     bool apart = true;
     for (const double* in : {drho, phi, S})
         apart = apart && !overlap(in, all, rho_out, all) && !overlap(in, all, u_out, 2 * all) && !overlap(in, all, phi_out, all);
     for (const double* in : {u, F})
         apart = apart && !overlap(in, 2 * all, rho_out, all) && !overlap(in, 2 * all, u_out, 2 * all) && !overlap(in, 2 * all, phi_out, all);
-    // from where three launches cost less than one: 64^2 nodes
-    if (zero_momentum && apart && n >= 4096 && batch <= kMaxPlanes) {
-        hipLaunchKernelGGL(initial_sums_k, dim3(kInitParts, (unsigned)batch), dim3(kBlock), 0, (hipStream_t)stream, a);
-        hipLaunchKernelGGL(initial_rest_k, dim3((unsigned)((n - kInitParts + kBlock - 1) / kBlock), (unsigned)batch),
-                           dim3(kBlock), 0, (hipStream_t)stream, a);
-        hipLaunchKernelGGL(initial_first_k, dim3((unsigned)batch), dim3(kInitParts), 0, (hipStream_t)stream, a);
+    // from where three launches, about 5 us of host time each, cost less than one: us in one
+    // launch and in three, 64^2 12.5 and 15.5, 88^2 15.5 and 15, 96^2 18 and 15 (64 problems
+    // 21.6 and 20.4)
+    if (zero_momentum && apart && n >= 7744) {
+        for (int64_t b0 = 0; b0 < batch; b0 += kMaxPlanes) {
+            const unsigned bs = (unsigned)std::min<int64_t>(kMaxPlanes, batch - b0);
+            const int64_t o = b0 * n;
+            const InitArgs a{drho + o, u + o, phi ? phi + o : nullptr, F + o, S ? S + o : nullptr, n, all, rho0,
+                             rho_out + o, u_out + o, phi_out ? phi_out + o : nullptr};
+            hipLaunchKernelGGL(initial_sums_k, dim3(kInitParts, bs), dim3(kBlock), 0, (hipStream_t)stream, a);
+            hipLaunchKernelGGL(initial_rest_k, dim3((unsigned)((n - kInitParts + kBlock - 1) / kBlock), bs), dim3(kBlock), 0,
+                               (hipStream_t)stream, a);
+            hipLaunchKernelGGL(initial_first_k, dim3(bs), dim3(kInitParts), 0, (hipStream_t)stream, a);
+        }
         return done(hipGetLastError());
     }
     hipLaunchKernelGGL(initial_state_k, dim3(batch), dim3(kProjBlock), 0, (hipStream_t)stream, drho, u, phi, F, S,

@@ -55,6 +55,7 @@ choices select() made (network on or off, reset cycles).
     python -m paper_1806_10247_amd.warmstart evaluate --weights weights.npz --cases 8
 """
 import argparse
+import functools
 import json
 import math
 import sys
@@ -95,6 +96,11 @@ def _ptr(t):
 def _stream():
     import torch
     return torch.cuda.current_stream().cuda_stream
+
+
+@functools.lru_cache(maxsize=64)
+def _project_work(planes, L, k2max):
+    return C.lb_warm_project_work(planes, L, k2max)
 
 
 def _empty(*shape):
@@ -180,7 +186,7 @@ class Fields:
         """Means and Nyquist lines (and the modes 0 < |k|^2 <= k2max) removed from
         every plane, in place."""
         for a, p in self.spans():
-            n = C.lb_warm_project_work(p, self.L, k2max)
+            n = _project_work(p, self.L, k2max)
             if n:
                 work = _empty(n)
                 C.lb_warm_project_split(_ptr(a), p, self.L, k2max, _ptr(work), _stream())
