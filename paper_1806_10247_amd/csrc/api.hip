@@ -63,7 +63,7 @@ struct lb_ctx {
     // several steps per launch (2D lattices): tiling per number of steps, the best number
     MultiShape multi[kMultiMaxSteps + 1];
     bool multi_ok[kMultiMaxSteps + 1] = {};
-    int multi_most = 0, multi_fields = -1;   // fields the choice was made for (bit 0 force, bit 1 source)
+    int multi_most = 0, multi_settings = -1;   // what the choice was made for (bits: force and source field, walls or heating)
     static constexpr int kGraphCache = 8;
     StepGraph graphs[kGraphCache];
     uint64_t graph_clock = 0;
@@ -704,6 +704,9 @@ static void time_factors(int mode, double omega, int64_t n, double* pre, double*
     }
 }
 
+// Walls that move or hold the scalar, or viscous heating (the EXT kernels).
+static bool step_extras(const lb_ctx* c) { return c->walls_used || c->heat != 0.0; }
+
 static StepArgs make_args_p(const lb_ctx* c, const Geometry& g, int64_t n, int parity) {
     StepArgs a;
     memset(&a, 0, sizeof(a));   // padding too: captured arguments are compared bytewise
@@ -734,7 +737,7 @@ static StepArgs make_args_p(const lb_ctx* c, const Geometry& g, int64_t n, int p
     a.partials = c->partials;
     a.walls = c->wall_dev;
     a.heat = c->heat;
-    a.ext = (c->walls_used || c->heat != 0.0) ? 1 : 0;
+    a.ext = step_extras(c) ? 1 : 0;
     a.lorentz = c->lorentz;
     a.div_nx = FastDiv((uint32_t)c->cfg.nx);
     a.sr = stochastic_rounding(c) ? 1 : 0;
@@ -886,7 +889,44 @@ static int graph_for(lb_ctx* c, int p, int n, hipGraphExec_t* out) {
 struct MultiChoice {
     MultiShape shape;
     double us;
+    double half_us;   // float16: the estimate that half_one_us is compared with
 };
+
+// Float16 lattices move half of float32's bytes a step, and their several-step launch does
+// more arithmetic than the model above has (the random bits; with moving or fixed-value
+// walls or heating the look-ups per link and step).  For them one and several are compared:
+//   one        3.5 us + bytes / (fill x rate), fill = the share of the blocks' lanes that
+//              have nodes, rate in pairs of nodes 5.0 TB/s (5.7 for rows of whole 128-byte
+//              lines of states beyond the last-level cache), one node per thread 3.3 (3.6 for
+//              whole lines, 4.0 beyond the cache)
+//   several    as above with the arithmetic times 1.2 on D2Q9 + D2Q5 and on states that fit
+//              the L2s, 1.36 on other D2Q9, 1.12 times that beyond the last-level cache; 2.5
+//              with such walls (1.55 on states that fit the L2s).
+// Measured, us per step, several / one: D2Q9 2048^2 29 / 32, 2500^2 42 / 49, 3072^2 70 / 63,
+// 4096^2 121 / 106, with a force field 125 / 136; D2Q9 + D2Q5 4096^2 164 / 165, with fields
+// 172 / 217; with walls 512^2 5.9 / 7.6, 768^2 11.0 / 11.8, 1024^2 20.7 / 15.0, 4096^2 291 /
+// 163 (314 / 237 with walls on x), 64 x 65536 70 / 81, 3001 x 3000 159 / 164; D2Q9 with walls
+// 900^2 9.7 / 11.0, 2048^2 48 / 33.  Of 300 sizes and settings measured the slower one is
+// taken by more than 5% in 15, at most by 17%.
+constexpr double kL2Bytes = 36 << 20, kLastLevelBytes = 256 << 20;   // states held there at their rate
+
+static double state_bytes(const lb_ctx* c) { return 2.0 * c->plane * (c->q + c->qs) * c->elem; }
+
+static double half_one_us(const lb_ctx* c) {
+    const bool pairs = c->geo_step.xpair != 0;
+    const double fields = (c->force_field ? 2 : 0) + (c->source_field ? 1 : 0);
+    const double bytes = (double)c->n * (2 * (c->q + c->qs) * c->elem + fields * c->real_bytes);
+    const double fill = (double)(pairs ? c->cfg.nx / 2 : c->cfg.nx) / ((double)c->geo_step.x_blocks * c->block);
+    const bool lines = c->cfg.nx * c->elem % 128 == 0, beyond = state_bytes(c) > kLastLevelBytes;
+    const double rate = pairs ? (lines && beyond ? 5.7 : 5.0) : (!lines ? 3.3 : (beyond ? 4.0 : 3.6));
+    return 3.5 + bytes / (fill * rate * 1e6);
+}
+
+static double half_arithmetic(const lb_ctx* c) {
+    const bool l2 = state_bytes(c) <= kL2Bytes;
+    if (step_extras(c)) return l2 ? 1.55 : 2.5;
+    return (c->qs || l2 ? 1.2 : 1.36) * (state_bytes(c) > kLastLevelBytes ? 1.12 : 1.0);
+}
 
 static bool multi_tile(const lb_ctx* c, int steps, int block, int tx, MultiChoice* out) {
     const int nx = (int)c->cfg.nx, ny = (int)c->cfg.ny, halo = steps - 1;
@@ -925,6 +965,7 @@ static bool multi_tile(const lb_ctx* c, int steps, int block, int tx, MultiChoic
     if (t.hx && t.tx * c->elem % 64) mem *= 1.25;
     const double valu = steps * (0.2 + 0.4 * waves) * (c->qs ? 1.0 : 0.65);
     out->us = (4.0 + (c->elem == 8 ? 0.75 * mem + 1.1 * valu : std::max(mem, valu))) / steps;
+    out->half_us = (4.0 + std::max(mem, valu * half_arithmetic(c))) / steps;
     out->shape = t;
     return true;
 }
@@ -961,27 +1002,28 @@ static bool capturing(const lb_ctx* c) {
 }
 
 // Tiling for the next of `plain` >= 2 steps (false: one step per launch), chosen on first
-// use and again when a field is set or cleared.  owed < 0: as few launches as the best
+// use and again when a field, walls or heating are set or cleared.  owed < 0: as few launches as the best
 // length allows.  Otherwise (a recording) the run's launches, each of which swaps the
 // buffers, get the parity of its steps, so that replaying an even number of steps starts
 // where the last replay ended; owed is the parity of the run's steps and launches so far.
 static bool multi_shape(lb_ctx* c, int64_t plain, int owed, MultiShape* out) {
     if (plain < 2 || !multi_applies(c)) return false;
-    const int fields = (c->force_field ? 1 : 0) + (c->source_field ? 2 : 0);
-    if (c->multi_fields != fields) {
-        c->multi_fields = fields;
+    const int settings = (c->force_field ? 1 : 0) + (c->source_field ? 2 : 0) + (step_extras(c) ? 4 : 0);
+    if (c->multi_settings != settings) {
+        c->multi_settings = settings;
         c->multi_most = 0;
-        double us = 1e30;
+        MultiChoice best{};
         for (int k = 2; k <= kMultiMaxSteps; ++k) {
             MultiChoice m;
             c->multi_ok[k] = multi_best(c, k, &m);
             if (!c->multi_ok[k]) continue;
             c->multi[k] = m.shape;
-            if (m.us < us) {
-                us = m.us;
+            if (c->multi_most < 2 || m.us < best.us) {
+                best = m;
                 c->multi_most = k;
             }
         }
+        if (c->elem == 2 && half_one_us(c) < best.half_us) c->multi_most = 0;
     }
     if (c->multi_most < 2) return false;
     // launches of about equal length

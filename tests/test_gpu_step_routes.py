@@ -1,4 +1,5 @@
-"""lb_step and HIP graphs: steps that a caller records and replays."""
+"""lb_step's routes: steps that a caller records and replays, and settings that
+change the route between runs."""
 import numpy as np
 import pytest
 
@@ -41,3 +42,24 @@ def test_recorded_steps_replayed(lattice, shape, storage, steps):
             for a, b in zip(rec.populations(), one.populations()):   # eager work between the replays
                 if a is not None:
                     assert np.array_equal(a, b), np.abs(a - b).max()
+
+
+@pytest.mark.parametrize("lattice,shape,walls", [("D2Q9_D2Q5", (1024, 1030, 1), (False, True, False)),
+                                                 ("D2Q9_D2Q5", (1001, 1000, 1), (True, True, False)),
+                                                 ("D2Q9", (96, 11000, 1), (False, True, False))])
+def test_float16_steps_as_walls_are_set_and_cleared(lattice, shape, walls):
+    """Moving walls make large float16 lattices take one step per launch, and resting
+    ones several again: the same bits as single launches throughout."""
+    case = Case(lattice, shape, walls=walls, nu=0.06, D=0.04, force=(2e-5, -1e-5, 0.0), source=2e-5, seed=4)
+    f, g = _state(case)
+    with case.gpu("f16", residual_interval=9) as s, case.gpu("f16", residual_interval=9, block_x=64) as one:
+        for c in (s, one):
+            c.write_populations(f, g)
+        for speed in (0.0, 0.03, 0.0):
+            for c in (s, one):
+                c.set_wall_velocity(1, 1, speed)
+                c.step(11)
+            for a, b in zip(s.populations(), one.populations()):
+                if a is not None:
+                    assert np.array_equal(a, b), np.abs(a - b).max()
+            assert s.residual()[1] == one.residual()[1]
