@@ -362,11 +362,16 @@ typedef struct lb_info {
     int32_t q_scalar;        /* scalar populations per node (0 or 5)         */
     int64_t plane_stride;    /* elements between population planes           */
     int32_t elem_bytes;      /* bytes per stored population                  */
-    int32_t block_x;         /* threads per block of the step kernel         */
+    int32_t block_x;         /* threads per block of step_kernel             */
     double bytes_per_update; /* algorithmic HBM bytes per lattice update      */
     void* buf_current;       /* device buffer holding the stored state        */
     void* buf_other;         /* the second buffer                             */
-    const char* step_kernel; /* name of the step kernel                       */
+    const char* step_kernel; /* kernel of plain steps with the present fields and
+                                walls: casclb_multistep where runs of at least
+                                two take several steps per launch (single steps
+                                and residual checks are then the rows'), the
+                                rows' casclb_step / _xpair, or the flat index's
+                                casclb_step_flat / _flat_pair                 */
 } lb_info;
 
 /* Layout and cost figures of a context (host only). */

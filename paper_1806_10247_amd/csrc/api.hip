@@ -61,9 +61,9 @@ struct lb_ctx {
         StepArgs args[2];
     };
     // several steps per launch (2D lattices): tiling per number of steps, the best number
-    MultiShape multi[kMultiMaxSteps + 1];
-    bool multi_ok[kMultiMaxSteps + 1] = {};
-    int multi_most = 0, multi_settings = -1;   // what the choice was made for (bits: force and source field, walls or heating)
+    mutable MultiShape multi[kMultiMaxSteps + 1];
+    mutable bool multi_ok[kMultiMaxSteps + 1] = {};
+    mutable int multi_most = 0, multi_settings = -1;   // what the choice was made for (bits: force and source field, walls or heating)
     static constexpr int kGraphCache = 8;
     StepGraph graphs[kGraphCache];
     uint64_t graph_clock = 0;
@@ -1001,13 +1001,11 @@ static bool capturing(const lb_ctx* c) {
     return c->stream && hipStreamIsCapturing(c->stream, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
 }
 
-// Tiling for the next of `plain` >= 2 steps (false: one step per launch), chosen on first
-// use and again when a field, walls or heating are set or cleared.  owed < 0: as few launches as the best
-// length allows.  Otherwise (a recording) the run's launches, each of which swaps the
-// buffers, get the parity of its steps, so that replaying an even number of steps starts
-// where the last replay ended; owed is the parity of the run's steps and launches so far.
-static bool multi_shape(lb_ctx* c, int64_t plain, int owed, MultiShape* out) {
-    if (plain < 2 || !multi_applies(c)) return false;
+// The number of steps per launch of least modelled time (0: one step per launch) and the
+// tilings up to it, chosen on first use and again when a field, walls or heating are set
+// or cleared.
+static int multi_choose(const lb_ctx* c) {
+    if (!multi_applies(c)) return 0;
     const int settings = (c->force_field ? 1 : 0) + (c->source_field ? 2 : 0) + (step_extras(c) ? 4 : 0);
     if (c->multi_settings != settings) {
         c->multi_settings = settings;
@@ -1025,7 +1023,16 @@ static bool multi_shape(lb_ctx* c, int64_t plain, int owed, MultiShape* out) {
         }
         if (c->elem == 2 && half_one_us(c) < best.half_us) c->multi_most = 0;
     }
-    if (c->multi_most < 2) return false;
+    return c->multi_most;
+}
+
+// Tiling for the next of `plain` >= 2 steps (false: one step per launch).  owed < 0: as few
+// launches as the best length allows.  Otherwise (a recording) the run's launches, each of
+// which swaps the buffers, get the parity of its steps, so that replaying an even number of
+// steps starts where the last replay ended; owed is the parity of the run's steps and
+// launches so far.
+static bool multi_shape(const lb_ctx* c, int64_t plain, int owed, MultiShape* out) {
+    if (plain < 2 || multi_choose(c) < 2) return false;
     // launches of about equal length
     auto length = [&](int64_t most) {
         int64_t launches = (plain + most - 1) / most;
@@ -1334,20 +1341,27 @@ int lb_get_info(const lb_ctx* c, lb_info* info) {
     info->q_scalar = c->qs;
     info->plane_stride = c->plane;
     info->elem_bytes = c->elem;
-    info->block_x = c->block;
+    const int many = multi_choose(c);
+    info->block_x = many ? c->multi[many].block : c->block;
     double b = 2.0 * (c->q + c->qs) * c->elem;
     if (c->force_field) b += (double)c->dims * c->real_bytes;
     if (c->source_field) b += (double)c->real_bytes;
     info->bytes_per_update = b;
     info->buf_current = c->buf[c->cur];
     info->buf_other = c->buf[c->cur ^ 1];
-    static const char* names[12] = {"casclb_step<D2Q9,f64>", "casclb_step<D2Q9,f32dev>", "casclb_step<D2Q9,f16dev>",
-                                   "casclb_step<D2Q9_D2Q5,f64>", "casclb_step<D2Q9_D2Q5,f32dev>", "casclb_step<D2Q9_D2Q5,f16dev>",
-                                   "casclb_step<D3Q27,f64>", "casclb_step<D3Q27,f32dev>", "casclb_step<D3Q27,f16dev>",
-                                   "casclb_step<D3Q15,f64>", "casclb_step<D3Q15,f32dev>", "casclb_step<D3Q15,f16dev>"};
-    static const char* pair_names[4] = {"casclb_step_xpair<D2Q9,f16dev>", "casclb_step_xpair<D2Q9_D2Q5,f16dev>",
-                                        "casclb_step_xpair<D3Q27,f16dev>", "casclb_step_xpair<D3Q15,f16dev>"};
-    info->step_kernel = c->geo_step.xpair ? pair_names[c->cfg.lattice] : names[c->cfg.lattice * 3 + c->cfg.storage];
+#define STORAGES(kernel, lat) kernel "<" lat ",f64>", kernel "<" lat ",f32dev>", kernel "<" lat ",f16dev>"
+    static const char* rows[4][3] = {{STORAGES("casclb_step", "D2Q9")}, {STORAGES("casclb_step", "D2Q9_D2Q5")},
+                                     {STORAGES("casclb_step", "D3Q27")}, {STORAGES("casclb_step", "D3Q15")}};
+    static const char* flat[2][3] = {{STORAGES("casclb_step_flat", "D3Q27")}, {STORAGES("casclb_step_flat", "D3Q15")}};
+    static const char* several[2][3] = {{STORAGES("casclb_multistep", "D2Q9")}, {STORAGES("casclb_multistep", "D2Q9_D2Q5")}};
+#undef STORAGES
+    static const char* pairs[4] = {"casclb_step_xpair<D2Q9,f16dev>", "casclb_step_xpair<D2Q9_D2Q5,f16dev>",
+                                   "casclb_step_xpair<D3Q27,f16dev>", "casclb_step_xpair<D3Q15,f16dev>"};
+    static const char* flat_pairs[2] = {"casclb_step_flat_pair<D3Q27,f16dev>", "casclb_step_flat_pair<D3Q15,f16dev>"};
+    const int lat = c->cfg.lattice, st = c->cfg.storage;
+    if (many) info->step_kernel = several[lat][st];
+    else if (c->geo_step.flat) info->step_kernel = c->geo_step.xpair ? flat_pairs[lat - kD3Q27] : flat[lat - kD3Q27][st];
+    else info->step_kernel = c->geo_step.xpair ? pairs[lat] : rows[lat][st];
     return LB_OK;
 }
 

@@ -63,3 +63,41 @@ def test_float16_steps_as_walls_are_set_and_cleared(lattice, shape, walls):
                 if a is not None:
                     assert np.array_equal(a, b), np.abs(a - b).max()
             assert s.residual()[1] == one.residual()[1]
+
+
+def _kernel(lattice, shape, storage, walls=(False, False, False), setup=lambda s: None, **cfg):
+    with Case(lattice, shape, walls=walls).gpu(storage, residual_interval=0, **cfg) as s:
+        setup(s)
+        info = s.info()
+        return info.step_kernel.decode(), info.block_x
+
+
+def test_info_names_the_kernel_of_the_steps():
+    """lb_get_info names the kernel that plain steps run, for every kind of route."""
+    from paper_1806_10247_amd import capi as C
+    for st, tag in (("f64", "f64"), ("f32", "f32dev"), ("f16", "f16dev")):
+        for lat in ("D2Q9", "D2Q9_D2Q5"):
+            assert _kernel(lat, (64, 64, 1), st)[0] == f"casclb_multistep<{lat},{tag}>"
+            assert _kernel(lat, (64, 64, 1), st)[1] in (256, 512, 1024)
+            assert _kernel(lat, (63, 64, 1), st, block_x=64) == (f"casclb_step<{lat},{tag}>", 64)
+            assert _kernel(lat, (64, 64, 1), st, rows_per_thread=2)[0] == f"casclb_step<{lat},{tag}>"
+        for lat in ("D3Q27", "D3Q15"):
+            assert _kernel(lat, (63, 20, 20), st) == (f"casclb_step_flat<{lat},{tag}>", 64)
+            assert _kernel(lat, (63, 20, 20), st, block_x=128) == (f"casclb_step<{lat},{tag}>", 128)
+    assert _kernel("D3Q27", (64, 20, 20), "f64")[0] == "casclb_step<D3Q27,f64>"
+    assert _kernel("D3Q27", (128, 20, 20), "f32")[0] == "casclb_step<D3Q27,f32dev>"
+    assert _kernel("D3Q27", (64, 20, 20), "f16")[0] == "casclb_step_flat_pair<D3Q27,f16dev>"
+    assert _kernel("D3Q15", (64, 20, 20), "f16")[0] == "casclb_step_flat<D3Q15,f16dev>"
+    assert _kernel("D3Q27", (64, 20, 20), "f16", x_pairs=2)[0] == "casclb_step_xpair<D3Q27,f16dev>"
+    assert _kernel("D2Q9", (64, 64, 1), "f16", x_pairs=2)[0] == "casclb_step_xpair<D2Q9,f16dev>"
+    # large float16 lattices with a moving wall take one step per launch, and several again without
+    moving, y = (lambda s: s.set_wall_velocity(1, 1, 0.1)), (False, True, False)
+    assert _kernel("D2Q9_D2Q5", (2048, 1024, 1), "f16", y)[0] == "casclb_multistep<D2Q9_D2Q5,f16dev>"
+    assert _kernel("D2Q9_D2Q5", (2048, 1024, 1), "f16", y, moving)[0] == "casclb_step_xpair<D2Q9_D2Q5,f16dev>"
+    assert _kernel("D2Q9_D2Q5", (2048, 1024, 1), "f32", y, moving)[0] == "casclb_multistep<D2Q9_D2Q5,f32dev>"
+    assert _kernel("D2Q9_D2Q5", (256, 256, 1), "f16", y, moving)[0] == "casclb_multistep<D2Q9_D2Q5,f16dev>"
+    with Case("D2Q9_D2Q5", (2048, 1024, 1), walls=y).gpu("f16", residual_interval=0) as s:
+        for speed, kernel in ((0.1, "casclb_step_xpair"), (0.0, "casclb_multistep"), (0.1, "casclb_step_xpair")):
+            s.set_wall_velocity(1, 1, speed)
+            assert s.info().step_kernel.decode() == f"{kernel}<D2Q9_D2Q5,f16dev>"
+    assert _kernel("D2Q9", (64, 64, 1), "f64", flags=C.LB_FLAG_XCD_REMAP)[0] == "casclb_multistep<D2Q9,f64>"
