@@ -53,7 +53,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "MLUPS + % HBM peak, D3Q27 256^3 FP32 vs FP64; warm-start steps-to-steady"
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, vendor figure
-KERNEL_SOURCES = ["paper_1806_10247_amd/csrc/kernels.hip", "paper_1806_10247_amd/csrc/node.hpp",
+KERNEL_SOURCES = ["paper_1806_10247_amd/csrc/kernels.hip", "paper_1806_10247_amd/csrc/step_flat.hip",
+                  "paper_1806_10247_amd/csrc/multistep.hip", "paper_1806_10247_amd/csrc/node.hpp",
                   "paper_1806_10247_amd/csrc/lattice.hpp", "paper_1806_10247_amd/csrc/common.hpp"]
 
 
@@ -95,8 +96,8 @@ def priming_steps(warmup):
 def launch_flags(C, storage):
     """Launch options the benchmark uses per storage: float64 takes the XCD-ordered
     block mapping (each of the 8 XCDs a contiguous range of rows), measured 1.7%
-    faster on the 256^3 duct and 6.6% on the 4096^2 coupled workload; the 4- and
-    2-byte storages are faster without it."""
+    faster on the 256^3 duct (the several-step launches of the 4096^2 workload
+    always have such an order); the 4- and 2-byte storages are faster without it."""
     return C.LB_FLAG_XCD_REMAP if storage == C.LB_STORE_F64 else 0
 
 
@@ -183,13 +184,19 @@ def run_storage(torch, C, storage, steps, warmup, n=256, lattice=None, single=50
         torch.cuda.empty_cache()
 
 
+def pct_hbm_peak(kernel, algorithmic_gbs):
+    """Share of the memory's peak in per cent; None for steps that share a pass over memory."""
+    return None if kernel.startswith("casclb_multistep") else round(100 * algorithmic_gbs / HBM_PEAK_GBS, 2)
+
+
 def run_coupled(torch, C, storage, steps=200, warmup=20, n=4096):
     """The periodic 4096^2 D2Q9 + D2Q5 workload with a Taylor-Green force field
     modulated by cos(w t) and a product source field (both stored per node, in
     the arithmetic type): whole-run throughput over `steps` steps (a residual
-    check every 100) and bytes per update with the force and source fields.  Runs
-    of plain steps go several steps per launch, the states between them on chip:
-    the algorithmic rate (bytes per update times updates) can exceed the memory's."""
+    check every 100) and bytes per update with the force and source fields.  Where
+    plain steps go several per launch, the states between them on chip, the
+    algorithmic rate (bytes per update times updates) is no memory traffic and no
+    share of the memory's peak is given."""
     from casclb_inputs import coupled_2d, product_source_2d, vortex_force_2d
     w = coupled_2d(n)
     stream = torch.cuda.current_stream()
@@ -220,7 +227,7 @@ def run_coupled(torch, C, storage, steps=200, warmup=20, n=4096):
         C.lb_read_moments_device(ctx, C.LB_MOMENTS_HALF_FORCED, None, u_dev.data_ptr(), phi_dev.data_ptr())
         torch.cuda.synchronize()
         return {"mlups": mlups, "ms_per_step": ms / steps, "bytes_per_update": info.bytes_per_update,
-                "algorithmic_gbs": gbs, "pct_hbm_peak": round(100 * gbs / HBM_PEAK_GBS, 2),
+                "algorithmic_gbs": gbs, "pct_hbm_peak": pct_hbm_peak(info.step_kernel.decode(), gbs),
                 "kernel": info.step_kernel.decode(), "steps_total": int(C.lb_get_step(ctx)), "u": u_dev,
                 "phi": phi_dev, "workload": w}
     finally:
