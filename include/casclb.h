@@ -141,15 +141,16 @@ typedef struct lb_config {
 #define LB_FLAG_XCD_REMAP 2        /* launch order that hands each of the 8 XCDs a
                                       contiguous range of rows (used when the block
                                       count is a multiple of 8)                   */
-#define LB_FLAG_DEBUG_POISON 4     /* debugging aid: before every step lb_step fills
-                                      the whole buffer the step writes with NaN bit
-                                      patterns (all bytes 0xFF), so a node the step
-                                      kernel leaves unwritten shows up as NaN in the
-                                      stored state and in the next residual check
+#define LB_FLAG_DEBUG_POISON 4     /* debugging aid: before every launch lb_step fills
+                                      the whole buffer it writes with NaN bit patterns
+                                      (all bytes 0xFF), so a node the step kernel
+                                      leaves unwritten shows up as NaN in the stored
+                                      state and in the next residual check
                                       (LB_ENONFINITE).  Results are otherwise
-                                      unchanged; steps are launched one by one
-                                      (no captured step graphs) and cost one more
-                                      full-buffer write each                      */
+                                      unchanged; the kernels are those of a context
+                                      without the flag, launched one by one (no
+                                      captured step graphs), each with one more
+                                      full-buffer write                           */
 #define LB_FLAG_F16_NEAREST 8      /* float16 storage: round stores to nearest instead
                                       of stochastically.  A per-step change smaller
                                       than half a float16 unit of the stored value is

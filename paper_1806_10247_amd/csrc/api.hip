@@ -987,12 +987,11 @@ static bool multi_best(const lb_ctx* c, int steps, MultiChoice* best) {
     return found;
 }
 
-// Whether the lattice is stepped several steps per launch: 2D, no debugging fill, the
-// launch shape left to the library, every byte offset within 32 bits.
+// Whether the lattice may be stepped several steps per launch: 2D, the launch shape left to
+// the library, every byte offset within 32 bits.
 static bool multi_applies(const lb_ctx* c) {
-    return c->dims == 2 && !(c->cfg.flags & LB_FLAG_DEBUG_POISON) && !c->cfg.block_x && !c->cfg.rows_per_thread &&
-           !c->cfg.x_pairs && (uint64_t)c->plane * (c->q + c->qs) * c->elem < (1ull << 32) &&
-           (uint64_t)c->plane * 2 * c->real_bytes < (1ull << 32);
+    return c->dims == 2 && !c->cfg.block_x && !c->cfg.rows_per_thread && !c->cfg.x_pairs &&
+           (uint64_t)c->plane * (c->q + c->qs) * c->elem < (1ull << 32) && (uint64_t)c->plane * 2 * c->real_bytes < (1ull << 32);
 }
 
 // Whether the context's stream is being recorded into a graph.
@@ -1051,6 +1050,13 @@ static bool multi_shape(const lb_ctx* c, int64_t plain, int owed, MultiShape* ou
     return true;
 }
 
+// Debugging aid: NaN patterns over the whole buffer that the next launch writes.
+static int poison(lb_ctx* c) {
+    if (c->cfg.flags & LB_FLAG_DEBUG_POISON)
+        HIP_OR_FAIL(c, launch_fill_u16(c->buf[c->cur ^ 1], lb_required_bytes(&c->cfg) / 2, 0xFFFFu, c->stream));
+    return LB_OK;
+}
+
 static int multi_step(lb_ctx* c, const MultiShape& t) {
     MultiArgs m;
     memset(&m, 0, sizeof(m));
@@ -1067,6 +1073,8 @@ static int multi_step(lb_ctx* c, const MultiShape& t) {
         m.factors[s][3] = a.s_tot;
         m.seeds[s] = a.sr_seed;
     }
+    const int rc = poison(c);
+    if (rc) return rc;
     HIP_OR_FAIL(c, launch_multistep(c->cfg.lattice, c->cfg.storage, m, c->stream));
     c->step += t.steps;
     c->cur ^= 1;   // one launch, one swap
@@ -1113,8 +1121,8 @@ int lb_step(lb_ctx* c, int64_t nsteps) {
         }
         const bool check = K > 0 && (c->step + 1) % K == 0;
         StepArgs a = make_args(c, c->geo_step, c->step);
-        if (c->cfg.flags & LB_FLAG_DEBUG_POISON)
-            HIP_OR_FAIL(c, launch_fill_u16(c->buf[c->cur ^ 1], lb_required_bytes(&c->cfg) / 2, 0xFFFFu, c->stream));
+        const int rc = poison(c);
+        if (rc) return rc;
         HIP_OR_FAIL(c, launch_step(c->cfg.lattice, c->cfg.storage, a, c->block, check, c->stream));
         if (check) {
             HIP_OR_FAIL(c, launch_reduce(c->partials, c->geo_step.grid_blocks, c->diag_dev, c->stream));

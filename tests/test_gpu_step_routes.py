@@ -101,3 +101,36 @@ def test_info_names_the_kernel_of_the_steps():
             s.set_wall_velocity(1, 1, speed)
             assert s.info().step_kernel.decode() == f"{kernel}<D2Q9_D2Q5,f16dev>"
     assert _kernel("D2Q9", (64, 64, 1), "f64", flags=C.LB_FLAG_XCD_REMAP)[0] == "casclb_multistep<D2Q9,f64>"
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("lattice,shape,walls", [("D2Q9", (4, 64, 1), (False, True, False)),
+                                                 ("D2Q9_D2Q5", (70, 66, 1), (False, False, False)),
+                                                 ("D2Q9_D2Q5", (257, 130, 3), (True, True, False))])
+def test_poison_covers_the_several_step_launches(lattice, shape, walls, storage):
+    """LB_FLAG_DEBUG_POISON on a lattice that takes several steps per launch: the same
+    kernel, every node written by it, the padding of the buffer it wrote poisoned."""
+    import torch
+
+    from paper_1806_10247_amd import capi as C
+    case = Case(lattice, shape, walls=walls, nu=0.06, D=0.04, force=(2e-5, -1e-5, 0.0), source=2e-5, seed=5)
+    f, g = _state(case)
+    plane = case.N + 24
+    need = plane * (14 if g is not None else 9) * {"f64": 8, "f32": 4, "f16": 2}[storage]
+    bufs = [torch.zeros(need, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    flags = C.LB_FLAG_DEBUG_POISON | C.LB_FLAG_EXTERNAL_BUFFERS
+    with case.gpu(storage, residual_interval=7, flags=flags, plane_pad=24) as p, \
+            case.gpu(storage, residual_interval=7, plane_pad=24) as s:
+        C.lb_bind_buffers(p.ctx, bufs[0].data_ptr(), bufs[1].data_ptr(), need)
+        assert p.info().step_kernel == s.info().step_kernel and b"multistep" in p.info().step_kernel
+        for c in (p, s):
+            c.write_populations(f, g)
+            c.step(11)   # six steps, a check, four steps
+        for a, b in zip(p.populations(), s.populations()):
+            if a is not None:
+                assert np.isfinite(a).all() and np.array_equal(a, b)
+        (rp, np_, tp), (rs, ns, ts) = p.residual(), s.residual()
+        assert rp == rs and np_ == ns and np.array_equal(tp, ts)
+        dt = {"f64": torch.float64, "f32": torch.float32, "f16": torch.float16}[storage]
+        now = next(b for b in bufs if b.data_ptr() == p.info().buf_current).view(dt).view(-1, plane)
+        assert torch.isfinite(now[:, :case.N]).all() and torch.isnan(now[:, case.N:]).all()
