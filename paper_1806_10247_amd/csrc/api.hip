@@ -1091,7 +1091,8 @@ int lb_step(lb_ctx* c, int64_t nsteps) {
         return fail(c, LB_ENONFINITE, "non-finite values found by the residual check after step %lld",
                     (long long)c->check_step);
     const int K = c->cfg.residual_interval;
-    int owed = c->dims == 2 && capturing(c) ? 0 : -1;
+    const bool recording = capturing(c);   // step graphs cannot be launched into a recording
+    int owed = recording ? 0 : -1;
     for (int64_t s = 0; s < nsteps; ++s) {
         // plain steps before the next residual check (or the end of the call)
         int64_t plain = nsteps - s;
@@ -1105,7 +1106,7 @@ int lb_step(lb_ctx* c, int64_t nsteps) {
             if (owed >= 0) owed ^= (shape.steps + 1) & 1;
         }
         if (s >= nsteps) break;
-        if (graphs_apply(c)) {
+        if (!recording && graphs_apply(c)) {
             while (plain >= kGraphMinSteps) {
                 const int n = (int)std::min<int64_t>(plain, kGraphSteps);
                 hipGraphExec_t ge = nullptr;

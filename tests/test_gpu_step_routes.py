@@ -44,6 +44,32 @@ def test_recorded_steps_replayed(lattice, shape, storage, steps):
                     assert np.array_equal(a, b), np.abs(a - b).max()
 
 
+@pytest.mark.parametrize("steps", [4, 10, 80])
+@pytest.mark.parametrize("lattice,shape,cfg", [("D3Q27", (12, 10, 9), {}), ("D3Q15", (64, 5, 6), {}),
+                                               ("D2Q9", (70, 66, 1), {"block_x": 64})])
+def test_recorded_single_steps_replayed(lattice, shape, cfg, steps):
+    """The same where every step is a launch: runs that would replay a step graph are
+    recorded launch by launch."""
+    import torch
+    case = Case(lattice, shape, nu=0.06, force=(2e-5, -1e-5, 1e-5), seed=3)
+    f0 = case.perturbed_state(case.oracle())[0]
+    side = torch.cuda.Stream()
+    with case.gpu("f64", residual_interval=0, stream=side.cuda_stream, **cfg) as rec, \
+            case.gpu("f64", residual_interval=0, **cfg) as one:
+        for s in (rec, one):
+            s.write_populations(f0)
+            s.step(steps)
+            s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            rec.step(steps)
+        for _ in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            one.step(steps)
+            assert np.array_equal(rec.populations()[0], one.populations()[0])
+
+
 @pytest.mark.parametrize("lattice,shape,walls", [("D2Q9_D2Q5", (1024, 1030, 1), (False, True, False)),
                                                  ("D2Q9_D2Q5", (1001, 1000, 1), (True, True, False)),
                                                  ("D2Q9", (96, 11000, 1), (False, True, False))])
