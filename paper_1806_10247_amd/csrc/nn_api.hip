@@ -594,11 +594,16 @@ int lb_unet_forward(lb_unet* n, const float* x_dev, int32_t batch, float* y_dev)
     if (rc) return rc;
     UHIP(n, hipSetDevice(n->cfg.device));
     // the first and the last layer read and write the caller's arrays, so only the layers
-    // between them, whose buffers do not change, are replayed from a graph
+    // between them, whose buffers do not change, are replayed from a graph (launched one by
+    // one into a recording of the caller's, which takes no graph launches)
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool recording = n->stream && hipStreamIsCapturing(n->stream, &status) == hipSuccess &&
+                           status == hipStreamCaptureStatusActive;
     hipGraphExec_t ge = nullptr;
-    if ((rc = middle_graph(n, batch, &ge))) return rc;
+    if (!recording && (rc = middle_graph(n, batch, &ge))) return rc;
     if ((rc = forward_first(n, x_dev, batch, false))) return rc;
-    UHIP(n, hipGraphLaunch(ge, n->stream));
+    if (!recording) UHIP(n, hipGraphLaunch(ge, n->stream));
+    else if ((rc = forward_middle(n, batch, false))) return rc;
     return forward_last(n, batch, view(y_dev, n->cfg.out_channels, 0));
 }
 
