@@ -160,3 +160,54 @@ def test_poison_covers_the_several_step_launches(lattice, shape, walls, storage)
         dt = {"f64": torch.float64, "f32": torch.float32, "f16": torch.float16}[storage]
         now = next(b for b in bufs if b.data_ptr() == p.info().buf_current).view(dt).view(-1, plane)
         assert torch.isfinite(now[:, :case.N]).all() and torch.isnan(now[:, case.N:]).all()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+@pytest.mark.parametrize("lattice,shape,walls,fields", [("D2Q9", (300, 45, 1), (False, True, False), False),
+                                                        ("D2Q9_D2Q5", (37, 29, 1), (True, True, False), False),
+                                                        ("D2Q9", (64, 48, 1), (False, False, False), True),
+                                                        ("D2Q9_D2Q5", (64, 40, 1), (False, False, False), True),
+                                                        ("D2Q9_D2Q5", (32, 8, 3), (False, False, False), False)])
+def test_step_graphs_single_launches_and_several_steps_agree(lattice, shape, walls, fields, storage):
+    """2D lattices over runs of both parities and lengths, with residual checks: an
+    explicit block_x and forcing constant in time replays step graphs, a cos(0 t) factor
+    launches every step by itself, and the automatic shape takes several steps per launch.
+    The same bits."""
+    from casclb_inputs import noise
+    n = int(np.prod(shape))
+    out = []
+    for time, cfg, kernel in (((0, 0.0), {"block_x": 64}, b"casclb_step<"), ((1, 0.0), {"block_x": 64}, b"casclb_step<"),
+                              ((0, 0.0), {}, b"casclb_multistep<")):
+        case = Case(lattice, shape, walls=walls, nu=0.06, D=0.03, omega_bulk=1.1, force=(1e-5, -2e-5, 0.0), source=1e-5,
+                    force_field=noise((2, n), 1e-4, seed=1) if fields else None,
+                    source_field=noise(n, 1e-4, seed=2) if fields else None, force_time=time, source_time=time, seed=6)
+        f, g = _state(case)
+        with case.gpu(storage, residual_interval=70, **cfg) as s:
+            assert s.info().step_kernel.startswith(kernel)
+            s.write_populations(f, g)
+            for steps in (333, 97, 29, 140):
+                s.step(steps)
+            out.append(s.populations() + (s.residual(),))
+    for got in out[1:]:
+        for a, b in zip(out[0][:2], got[:2]):
+            if a is not None:
+                assert np.isfinite(a).all() and np.array_equal(a, b)
+        (r0, n0, t0), (r1, n1, t1) = out[0][2], got[2]
+        # the automatic shape's blocks differ: sums of n terms of size <= 1 in two orders of float64
+        assert n0 == n1 and abs(r0 - r1) <= 1e-10 * abs(r0) and np.allclose(t0, t1, rtol=0, atol=1e-15 * n * 14)
+
+
+def test_flat_and_row_contexts_take_their_routes():
+    """The sizes that the flat and the several-step kernels are compared with the rows at
+    do run those kernels."""
+    import test_gpu_flat as F
+    import test_gpu_multistep as M
+    for st in ("f64", "f32", "f16"):
+        for lat in ("D3Q27", "D3Q15"):
+            for shape in F.SHAPES:
+                assert _kernel(lat, shape, st)[0].startswith("casclb_step_flat")
+                assert _kernel(lat, shape, st, block_x=64)[0].startswith(("casclb_step<", "casclb_step_xpair<"))
+        for lat in ("D2Q9", "D2Q9_D2Q5"):
+            for shape in M.SHAPES:
+                assert _kernel(lat, shape, st)[0].startswith("casclb_multistep<")
+                assert _kernel(lat, shape, st, block_x=64)[0].startswith(("casclb_step<", "casclb_step_xpair<"))
