@@ -52,8 +52,9 @@ struct lb_unet {
     float *out = nullptr, *g_out = nullptr;
     float* wpart = nullptr;                  // weight-gradient partial sums of one layer (wgrad_mfma)
     int64_t wpart_n = 0;
-    std::vector<float*> lpart;               // per layer (wgrad_lds), summed together at the end
-    std::vector<int64_t> lpart_n;
+    std::vector<float*> lpart;               // per layer (wgrad_lds), summed together at the end;
+    std::vector<int64_t> lpart_n;            // null until training first runs (split_buffers)
+    bool lpart_tried = false;
     ReduceTable reduce{};
     float* bpart = nullptr;
     int32_t bpart_blocks = 0;
@@ -263,14 +264,11 @@ int lb_unet_create(lb_unet** out, const lb_unet_config* cfg) {
             const int32_t splits = wgrad_splits(P, &cpw);
             const int co = up_to(y.co, 16), ci = up_to(y.ci, 16);
             const int64_t ls = wgrad_lds_splits((int32_t)B, n->lv[y.level].h, n->lv[y.level].w, co, ci);
-            // the general path's scratch only where the LDS path may not apply (its offsets are 32-bit)
-            if (ls == 0 || P * (int64_t)(512 * 4) >= ((int64_t)1 << 32)) wmax = std::max(wmax, (int64_t)splits * co * 9 * ci);
+            wmax = std::max(wmax, (int64_t)splits * co * 9 * ci);
             n->lpart.push_back(nullptr);
             n->lpart_n.push_back(ls * ((int64_t)co * 9 * ci + co));
             bmax = std::max(bmax, bias_grad_blocks(P) * (int32_t)y.co);
         }
-        for (size_t k = 0; k < n->lpart.size(); ++k)
-            if (n->lpart_n[k]) UALLOC(n->lpart[k], n->lpart_n[k]);
         n->wpart_n = wmax;
         UALLOC(n->wpart, wmax);
         n->bpart_blocks = 4096;
@@ -437,8 +435,36 @@ static WgradArgs wgrad_args(lb_unet* n, int layer, View g, View x, View x2, int 
     return a;
 }
 
+// Whether the caller is recording the network's stream into a graph.
+static bool recording(const lb_unet* n) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return n->stream && hipStreamIsCapturing(n->stream, &status) == hipSuccess && status == hipStreamCaptureStatusActive;
+}
+
+// The LDS weight gradients' partial sums of all layers (108 MB for the warm start's network
+// at batch 16, 256^2), which only training needs: allocated by its first call, not by
+// lb_unet_create.  Without them (no memory, or nothing may be allocated because the first
+// call is being recorded) the general path with its one shared buffer runs.
+static void split_buffers(lb_unet* n) {
+    if (n->lpart_tried || recording(n)) return;
+    n->lpart_tried = true;
+    int64_t total = 0;
+    for (int64_t k : n->lpart_n) total += (k + 3) / 4 * 4;
+    float* base = nullptr;
+    if (total == 0 || hipMalloc((void**)&base, (size_t)total * sizeof(float)) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    n->allocs.push_back(base);
+    for (size_t k = 0; k < n->lpart.size(); ++k) {
+        if (n->lpart_n[k] == 0) continue;
+        n->lpart[k] = base;
+        base += (n->lpart_n[k] + 3) / 4 * 4;
+    }
+}
+
 static bool wgrad_lds_applies(const lb_unet* n, int layer, const WgradArgs& a) {
-    return a.splits > 0 && wgrad_lds_fits(a) &&
+    return a.splits > 0 && n->lpart[layer] && wgrad_lds_fits(a) &&
            (int64_t)a.splits * ((int64_t)a.co_pad16 * 9 * a.ci_pad16 + a.co_pad16) <= n->lpart_n[layer];
 }
 
@@ -596,13 +622,11 @@ int lb_unet_forward(lb_unet* n, const float* x_dev, int32_t batch, float* y_dev)
     // the first and the last layer read and write the caller's arrays, so only the layers
     // between them, whose buffers do not change, are replayed from a graph (launched one by
     // one into a recording of the caller's, which takes no graph launches)
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    const bool recording = n->stream && hipStreamIsCapturing(n->stream, &status) == hipSuccess &&
-                           status == hipStreamCaptureStatusActive;
+    const bool record = recording(n);
     hipGraphExec_t ge = nullptr;
-    if (!recording && (rc = middle_graph(n, batch, &ge))) return rc;
+    if (!record && (rc = middle_graph(n, batch, &ge))) return rc;
     if ((rc = forward_first(n, x_dev, batch, false))) return rc;
-    if (!recording) UHIP(n, hipGraphLaunch(ge, n->stream));
+    if (!record) UHIP(n, hipGraphLaunch(ge, n->stream));
     else if ((rc = forward_middle(n, batch, false))) return rc;
     return forward_last(n, batch, view(y_dev, n->cfg.out_channels, 0));
 }
@@ -673,6 +697,7 @@ static int backward(lb_unet* n, int batch) {
 }
 
 static int loss_grad(lb_unet* n, const float* x, const float* target, int batch) {
+    split_buffers(n);
     int rc = forward_first(n, x, batch, true);
     if (!rc) rc = forward_middle(n, batch, true);
     if (!rc) rc = forward_last(n, batch, view(n->out, n->out_cs, 0));
