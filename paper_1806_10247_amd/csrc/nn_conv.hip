@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "nn.hpp"
+#include "nn_tile.hpp"
 
 namespace casclb {
 namespace nn {
@@ -71,33 +72,6 @@ __device__ __forceinline__ f32x4 masked(f32x4 v, const View& m, size_t px, int c
 }
 
 enum Input { kBf16 = 0, kF32 = 1, kRaw = 2 };
-
-template <int CI, int TW, int T>
-struct Tile {
-    static constexpr int TPR = TW / 16;            // matrix-core tiles per pixel row
-    static constexpr int R = T / TPR;              // pixel rows per wavefront
-    static constexpr int TH = 4 * R;
-    static constexpr int HW = TW + 2, HH = TH + 2, NP = HW * HH;
-    static constexpr int PS = CI + 8;              // LDS elements per pixel
-    static constexpr int CPP = CI / 8;             // 8-channel pieces per pixel
-    static constexpr int S = (9 * CI + 31) / 32;   // K slices
-    static constexpr int KPAD = 32 * S;
-    static constexpr int tap_of(int q) { return q / CPP > 8 ? 8 : q / CPP; }
-    // LDS offset of piece q minus 8 (q mod 4), a function of its tap only within a slice
-    static constexpr int offset(int q) {
-        const int tap = tap_of(q), slice = q / 4;
-        return ((tap / 3) * HW + tap % 3) * PS + 32 * slice - CI * tap;
-    }
-    static constexpr int split(int s) {            // first lane group of slice s in its second tap (4: none)
-        for (int g = 1; g < 4; ++g)
-            if (tap_of(4 * s + g) != tap_of(4 * s)) return g;
-        return 4;
-    }
-    static constexpr int live(int s) {             // lane groups of slice s before the end of K
-        const int left = 9 * CPP - 4 * s;
-        return left < 4 ? left : 4;
-    }
-};
 
 // Pieces of one tile's input held in registers between their loads and their
 // LDS stores: all of a thread's pieces, loads issued together.
@@ -190,7 +164,7 @@ struct Staged<16, TW, T, kRaw> {
     }
     __device__ __forceinline__ void store(const ConvArgs& a, bf16_t* tile, uint32_t img_row, int y0, int x0) {
         const uint32_t cr = (uint32_t)a.cin_raw, inner_n = G::HH * (TW / 4) * cr;
-        float* inner = reinterpret_cast<float*>(tile + G::NP * G::PS);   // [HH][TW * cr]
+        float* inner = reinterpret_cast<float*>(tile + G::LDS);          // [HH][TW * cr]
         float* edge = inner + G::HH * TW * cr;                           // [HH][2][cr]
 #pragma unroll
         for (int r = 0; r < N; ++r) {
@@ -388,7 +362,7 @@ hipError_t launch_nu(const ConvArgs& a, hipStream_t s) {
     b.div_w = FastDiv((uint32_t)(a.w / TW));
     b.div_h = FastDiv((uint32_t)(a.h / G::TH));
     b.y_vec = a.y.cs % 4 == 0 && a.y.co % 4 == 0 && ((uintptr_t)a.y.base & 15) == 0;
-    size_t lds = (size_t)G::NP * G::PS * sizeof(bf16_t);
+    size_t lds = (size_t)G::LDS * sizeof(bf16_t);
     if (XM == kRaw) {
         b.div_raw = FastDiv((uint32_t)(TW / 4 * a.cin_raw));
         b.div_cin = FastDiv((uint32_t)a.cin_raw);
