@@ -99,8 +99,7 @@ __global__ void __launch_bounds__(256) conv3x3_mfma(ConvArgs a) {
             if (a.relu) v = fmaxf(v, 0.0f);
             const int64_t q = p0 + 4 * grp + j;
             if constexpr (YF32) {
-                float* dst = at<float>(a.y, q, o);
-                *dst = a.accumulate ? *dst + v : v;
+                *at<float>(a.y, q, o) = v;
             } else {
                 *at<bf16_t>(a.y, q, o) = f2bf(v);
             }
@@ -284,7 +283,7 @@ __global__ void __launch_bounds__(64 * kReduceWaves) wgrad_reduce(ReduceTable t)
         for (int w = 1; w < kReduceWaves; ++w) s += red[w][lane];
         if (e >= weights) {
             const int o = (int)(e - weights);
-            if (o < a.co) a.bias_out[o] = a.accumulate ? a.bias_out[o] + s : s;
+            if (o < a.co) a.bias_out[o] = s;
             return;
         }
         const int c = (int)(e % a.ci_pad16);
@@ -292,7 +291,7 @@ __global__ void __launch_bounds__(64 * kReduceWaves) wgrad_reduce(ReduceTable t)
         const int o = (int)(e / ((int64_t)9 * a.ci_pad16));
         if (o < a.co && c < a.ci) {
             const int64_t i = ((int64_t)o * 9 + tap) * a.ci + c;
-            a.out[i] = a.accumulate ? a.out[i] + s : s;
+            a.out[i] = s;
         }
     }
 }
@@ -328,15 +327,14 @@ __global__ void __launch_bounds__(256) bias_partial(View g, int64_t pixels, int 
     }
 }
 
-__global__ void __launch_bounds__(256) bias_reduce(const float* partials, int blocks, int co, float* db,
-                                                   int accumulate) {
+__global__ void __launch_bounds__(256) bias_reduce(const float* partials, int blocks, int co, float* db) {
     // one workgroup per channel: threads take interleaved blocks, fixed-order tree
     __shared__ float lds[256];
     const int o = blockIdx.x;
     float s = 0.0f;
     for (int b = threadIdx.x; b < blocks; b += 256) s += partials[(int64_t)b * co + o];
     const float t = block_sum_f32(s, lds);
-    if (threadIdx.x == 0) db[o] = accumulate ? db[o] + t : t;
+    if (threadIdx.x == 0) db[o] = t;
 }
 
 // ---------------------------------------------------------------------------
@@ -588,7 +586,7 @@ hipError_t launch_wgrad(const WgradArgs& a, hipStream_t s) {
 }
 
 void reduce_entry(ReduceTable* t, const WgradArgs& a) {
-    t->e[t->count++] = {a.partials, a.out, a.bias_out, a.splits, a.co, a.ci, a.co_pad16, a.ci_pad16, a.accumulate, 0};
+    t->e[t->count++] = {a.partials, a.out, a.bias_out, a.splits, a.co, a.ci, a.co_pad16, a.ci_pad16, 0};
 }
 
 hipError_t launch_wgrad_reduce(const ReduceTable& table, hipStream_t s) {
@@ -610,12 +608,12 @@ int32_t bias_grad_blocks(int64_t pixels) {
 }
 
 hipError_t launch_bias_grad(View g, int64_t pixels, int32_t co, float* partials, int32_t max_blocks, float* db,
-                            int32_t accumulate, hipStream_t s) {
+                            hipStream_t s) {
     const int co16 = (co + 15) / 16 * 16;
     int32_t blocks = bias_grad_blocks(pixels);
     if (blocks > max_blocks) blocks = max_blocks;
     hipLaunchKernelGGL(bias_partial, dim3((unsigned)blocks), dim3(256), 0, s, g, pixels, co, co16, partials);
-    hipLaunchKernelGGL(bias_reduce, dim3((unsigned)co), dim3(256), 0, s, partials, blocks, co, db, accumulate);
+    hipLaunchKernelGGL(bias_reduce, dim3((unsigned)co), dim3(256), 0, s, partials, blocks, co, db);
     return hipGetLastError();
 }
 

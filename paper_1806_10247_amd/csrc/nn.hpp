@@ -23,8 +23,7 @@ struct View {
 //     channels past the layer's inputs must hold finite values, their weights are 0)
 //  wt: bf16 [co_pad32][kpad], k = tap*ci_pad + c, tap = 3*a + c_x (a: row offset + 1),
 //     kpad = 9*ci_pad rounded up to 32, zero past 9*ci_pad and past the real outputs
-//  bias: fp32 [co] or null; y: bf16 or fp32 view; writes channels [0, co);
-//  accumulate: y += result (fp32 output only).
+//  bias: fp32 [co] or null; y: bf16 or fp32 view; writes channels [0, co).
 struct ConvArgs {
     View x;
     View y;
@@ -32,7 +31,7 @@ struct ConvArgs {
     const float* bias;
     int32_t n, h, w;
     int32_t ci_pad, kpad, co, co_pad32;
-    int32_t relu, accumulate;
+    int32_t relu;
     // launch_conv_lds only:
     View x2;            // base != null: input channels [c_split, ci_pad) come from this bf16 view at half
                         // resolution (nearest 2x upsampling fused into the load), [0, c_split) from x
@@ -57,15 +56,14 @@ hipError_t launch_conv(const ConvArgs& a, bool x_f32, bool y_f32, hipStream_t s)
 
 // The same convolution (bf16, fp32 or raw fp32 input, bf16 or fp32 output) with
 // the input tile and its circular halo staged in LDS.  Needs w a multiple of 16,
-// h of 8, ci_pad a multiple of 16 up to 128 (or 160, 192) and no accumulation
-// (conv_lds_fits).
+// h of 8 and ci_pad a multiple of 16 up to 128 (or 160, 192) (conv_lds_fits).
 bool conv_lds_fits(const ConvArgs& a);
 hipError_t launch_conv_lds(const ConvArgs& a, bool x_f32, bool y_f32, hipStream_t s);
 
 // Weight gradient dW[o][tap][c] = sum_p g[p][o] x[p shifted by tap][c] over
 // N x H x W pixels: g fp32 view (co channels), x bf16 view (ci channels).
 // Writes split partial sums to `partials` [splits][co_pad16][9][ci_pad16] and
-// then their ordered sum into out [co][3][3][ci] (fp32, `accumulate`: +=).
+// then their ordered sum into out [co][3][3][ci] (fp32).
 struct WgradArgs {
     View g;
     View x;
@@ -77,7 +75,6 @@ struct WgradArgs {
     float* partials;
     float* out;
     float* bias_out;        // != null: the records end with co_pad16 bias sums, whose totals go here
-    int32_t accumulate;
     FastDiv div_w, div_h;   // set by the launchers
 };
 int32_t wgrad_splits(int64_t pixels, int32_t* chunks_per_wave);
@@ -97,7 +94,7 @@ struct ReduceTable {
         const float* partials;
         float* out;
         float* bias_out;   // null: the records hold no bias sums
-        int32_t splits, co, ci, co_pad16, ci_pad16, accumulate;
+        int32_t splits, co, ci, co_pad16, ci_pad16;
         int32_t first_block;   // set by launch_wgrad_reduce
     } e[kMaxLayers];
     int32_t count;
@@ -106,9 +103,9 @@ void reduce_entry(ReduceTable* t, const WgradArgs& a);
 hipError_t launch_wgrad_reduce(const ReduceTable& t, hipStream_t s);
 
 // Bias gradient db[o] = sum_p g[p][o], o < co; two ordered passes via partials
-// [blocks][co]; `accumulate`: db += sum.
+// [blocks][co].
 hipError_t launch_bias_grad(View g, int64_t pixels, int32_t co, float* partials, int32_t max_blocks, float* db,
-                            int32_t accumulate, hipStream_t s);
+                            hipStream_t s);
 int32_t bias_grad_blocks(int64_t pixels);
 
 // Elementwise / resampling (all over N x H x W output pixels, `c` channels):

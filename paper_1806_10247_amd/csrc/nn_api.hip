@@ -1,6 +1,7 @@
 // C ABI of the warm-start surrogate network (include/casclb_unet.h): buffer
 // layout, the forward pass, the backward pass in reverse layer order and the
-// Adam update, all as launches of the kernels in nn.hip on one stream.
+// Adam update, all as launches of the kernels in nn_conv.hip, nn_wgrad.hip and
+// nn.hip on one stream.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdarg.h>
@@ -350,7 +351,6 @@ static int conv_tiled(lb_unet* n, const Layer& y, View x, View out, bool out_f32
     a.co = y.co;
     a.co_pad32 = y.co_pad32;
     a.relu = relu ? 1 : 0;
-    a.accumulate = 0;
     a.x2 = x2;
     a.c_split = x2.base ? c_split : y.ci_pad;
     a.pool = pool;
@@ -377,7 +377,6 @@ static int conv(lb_unet* n, const Layer& y, View x, bool x_f32, View out, bool o
     a.co = y.co;
     a.co_pad32 = y.co_pad32;
     a.relu = relu ? 1 : 0;
-    a.accumulate = 0;
     UHIP(n, launch_conv(a, x_f32, out_f32, n->stream));
     return LB_OK;
 }
@@ -485,7 +484,7 @@ static int wgrad(lb_unet* n, int layer, View g, View x, int batch, View x2 = Vie
         return ufail(n, LB_EINVAL, "internal: weight-gradient scratch too small");
     a.partials = n->wpart;
     UHIP(n, launch_wgrad(a, n->stream));
-    UHIP(n, launch_bias_grad(g, P, y.co, n->bpart, n->bpart_blocks, n->g + y.b_off, 0, n->stream));
+    UHIP(n, launch_bias_grad(g, P, y.co, n->bpart, n->bpart_blocks, n->g + y.b_off, n->stream));
     return LB_OK;
 }
 

@@ -419,7 +419,7 @@ hipError_t launch_xm(const ConvArgs& a, hipStream_t s) {
 bool conv_lds_fits(const ConvArgs& a) {
     const int32_t ci = a.ci_pad;
     if (!(ci >= 16 && ci % 16 == 0 && (ci <= 128 || ci == 160 || ci == 192))) return false;
-    if (a.w % 16 || a.h % 8 || a.kpad != (9 * ci + 31) / 32 * 32 || a.accumulate) return false;
+    if (a.w % 16 || a.h % 8 || a.kpad != (9 * ci + 31) / 32 * 32) return false;
     // pixel numbers and element offsets within an image row are 32-bit
     return (int64_t)a.n * a.h * a.w < ((int64_t)1 << 31);
 }

@@ -1,7 +1,9 @@
-// Index arithmetic of the LDS-tiled convolution (nn.hip), written with 32-bit
-// offsets and 24-bit multiplies (full-rate instructions on gfx950) instead of
-// 64-bit pixel x stride products.  Host and device: the host side checks the
-// bounds that make them exact (conv_tiled_offsets_fit).
+// Index arithmetic of convolution kernels, written with 32-bit offsets and 24-bit
+// multiplies (full-rate instructions on gfx950) instead of 64-bit pixel x stride
+// products; exact within the stated bounds (tests/nn_index_check.cpp).  Host and
+// device.  The plain convolution (nn.hip) steps through K with TapCursor and
+// tap_row; no kernel uses the others now (nn_conv.hip decodes K at compile time,
+// nn_tile.hpp).
 #pragma once
 
 #include <hip/hip_runtime.h>
