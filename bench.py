@@ -464,10 +464,10 @@ def run_batch(torch, C, steps, n_domains=4096, to_tol=True):
             "nodes_total": int(nodes.sum()),
             "bytes_per_update_hbm_resident": bpu,
             "algorithmic_gbs_if_all_hbm": round(glups * bpu, 1),
-            "frac_hbm_peak_if_all_hbm": round(glups * bpu / HBM_PEAK_GBS, 4),
+            "frac_hbm_peak_if_all_hbm": None,  # no share of the peak: a sweep moves a domain once in three steps
             "block": int(block),
             "lds_resident_small_domains": int(policy) == 0,
-            "kernel": "casclb::casclb_batch<float, float>",
+            "kernel": "casclb::casclb_batch<float, float, false>",
             "to_tolerance": steady,
         }
     finally:
