@@ -140,7 +140,10 @@ typedef struct lb_config {
                                       caller must lb_bind_buffers before use      */
 #define LB_FLAG_XCD_REMAP 2        /* launch order that hands each of the 8 XCDs a
                                       contiguous range of rows (used when the block
-                                      count is a multiple of 8)                   */
+                                      count is a multiple of 8; any count over flat
+                                      node indices).  Launches of several steps of a 2D lattice
+                                      hand out their tiles in such an order with or
+                                      without it                                  */
 #define LB_FLAG_DEBUG_POISON 4     /* debugging aid: before every launch lb_step fills
                                       the whole buffer it writes with NaN bit patterns
                                       (all bytes 0xFF), so a node the step kernel

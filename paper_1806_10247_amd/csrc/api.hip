@@ -324,6 +324,8 @@ static Geometry make_geometry(const lb_ctx* c, int block, int rows, bool xpair =
 // 64^3 float32 13.4 / 10.9, float64 23.0 / 24.3; 96^3 float32 41 / 38; 128^3 float32 83 /
 // 84, float64 160 / 166, float16 55 / 50; 256^3 float64 1350 / 1390, float16 390 / 372.
 // Every byte offset must fit 32 bits; an explicit launch shape asks for the row kernels.
+// float64 rows of whole lines that are shorter than 64 nodes (16, 32, 48) were not measured
+// over flat indices; they stay with the rows.
 static bool flat_of(const lb_config* c, int64_t plane) {
     if (dims_of(c->lattice) != 3 || c->block_x || c->rows_per_thread || c->x_pairs) return false;
     const int elem = elem_of(c->storage);
@@ -884,8 +886,9 @@ static int graph_for(lb_ctx* c, int p, int n, hipGraphExec_t* out) {
 // added).  Measured on MI355X against one step per launch, us per step, D2Q9 + D2Q5 with
 // fields: float32 64^2 3.27 -> 1.27 (4 x 4 tiles, K = 7), 256^2 4.30 -> 2.2 (16 x 16, 4),
 // 1000^2 29.1 -> 11.4 and 4096^2 356 -> 168 (32 x 20, 4); float64 4096^2 784 -> 356
-// (26 x 26, 4); float16 4096^2 216 -> 159 (32 x 24, 3).  The model is within 20% of the
-// measured times over these sizes; the least modelled time per step is taken.
+// (26 x 26, 4); float16 4096^2 216 -> 159 (32 x 24, 3).  The model is within 25% of the
+// measured times over these sizes (the farthest: float32 D2Q9 4096^2, 93 us modelled for 116);
+// the least modelled time per step is taken.
 struct MultiChoice {
     MultiShape shape;
     double us;
